@@ -106,7 +106,6 @@ static int snap_dir(dg_snapshot *sn, const Dir &d, int32_t n, hipStream_t s) {
     DG_TRY(snap_save(sn, d.dcol, d.dm, s));
     DG_TRY(snap_save(sn, d.dw, d.dm, s));
     DG_TRY(snap_save(sn, d.deg, n, s));
-    DG_TRY(snap_save(sn, d.ntomb, n, s));
     DG_TRY(snap_save(sn, d.ttomb, ntiles(d.m), s));
     sn->scalars.push_back(d.m);
     sn->scalars.push_back(d.dm);
@@ -124,7 +123,6 @@ static int load_dir(const dg_snapshot *sn, size_t &idx, size_t &si, Dir &d, hipS
     DG_TRY(snap_load(sn, idx, d.dcol, s));
     DG_TRY(snap_load(sn, idx, d.dw, s));
     DG_TRY(snap_load(sn, idx, d.deg, s));
-    DG_TRY(snap_load(sn, idx, d.ntomb, s));
     DG_TRY(snap_load(sn, idx, d.ttomb, s));
     d.m = sn->scalars[si++];
     d.dm = sn->scalars[si++];

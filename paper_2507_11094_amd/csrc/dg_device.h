@@ -219,12 +219,18 @@ constexpr int CH_T = 256;
 constexpr int CH_IPT = 8;
 constexpr int CH = CH_T * CH_IPT;
 
+// Kernels that append or count per element and have nothing to gain from several
+// elements per thread run WIDE_T threads per block instead, for the same reason: a
+// quarter of the atomics of 256-thread blocks, and as many loads in flight.
+constexpr int WIDE_T = 1024;
+
 struct BlockScratch {
-    int64_t w[CH_T / WAVE];
+    int64_t w[WIDE_T / WAVE];
     int64_t base;
 };
 
-// Exclusive prefix of v over the block (thread order); *total = block sum.
+// Exclusive prefix of v over the block of T threads (thread order); *total = block sum.
+template <int T = CH_T>
 __device__ __forceinline__ int64_t block_scan_excl(int64_t v, int64_t *total, BlockScratch &s) {
     const int l = lane_id(), wv = threadIdx.x / WAVE;
     const int64_t incl = wave_incl_scan(v);
@@ -232,7 +238,7 @@ __device__ __forceinline__ int64_t block_scan_excl(int64_t v, int64_t *total, Bl
     __syncthreads();
     int64_t before = 0, tot = 0;
 #pragma unroll
-    for (int q = 0; q < CH_T / WAVE; ++q) {
+    for (int q = 0; q < T / WAVE; ++q) {
         const int64_t x = s.w[q];
         if (q < wv) before += x;
         tot += x;
@@ -243,9 +249,10 @@ __device__ __forceinline__ int64_t block_scan_excl(int64_t v, int64_t *total, Bl
 }
 
 // First of v consecutive slots of `counter` for this thread (one atomic per block).
+template <int T = CH_T>
 __device__ __forceinline__ int64_t block_reserve(int64_t *counter, int64_t v, BlockScratch &s) {
     int64_t tot;
-    const int64_t ex = block_scan_excl(v, &tot, s);
+    const int64_t ex = block_scan_excl<T>(v, &tot, s);
     if (threadIdx.x == 0)
         s.base = tot > 0 ? (int64_t)atomicAdd((unsigned long long *)counter, (unsigned long long)tot) : 0;
     __syncthreads();
@@ -255,15 +262,34 @@ __device__ __forceinline__ int64_t block_reserve(int64_t *counter, int64_t v, Bl
 }
 
 // Slot of a true predicate (one atomic per block and call; all threads call).
+template <int T = CH_T>
 __device__ __forceinline__ int64_t block_append(int64_t *counter, bool pred, BlockScratch &s) {
-    return block_reserve(counter, pred ? 1 : 0, s);
+    return block_reserve<T>(counter, pred ? 1 : 0, s);
 }
 
 // counter += sum of v over the block (one atomic per block).
+template <int T = CH_T>
 __device__ __forceinline__ void block_count(int64_t *counter, int64_t v, BlockScratch &s) {
     int64_t tot;
-    (void)block_scan_excl(v, &tot, s);
+    (void)block_scan_excl<T>(v, &tot, s);
     if (threadIdx.x == 0 && tot) atomicAdd((unsigned long long *)counter, (unsigned long long)tot);
+}
+
+// counter = max(counter, v over the block) for v >= 0: at most one atomic per
+// block, and none when the counter already holds as much (it only rises, so a
+// stale read can only cause an atomic that changes nothing).
+template <int T = CH_T>
+__device__ __forceinline__ void block_raise(int64_t *counter, int64_t v, BlockScratch &s) {
+    v = wave_max(v);
+    if (lane_id() == 0) s.w[threadIdx.x / WAVE] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int q = 1; q < T / WAVE; ++q) v = max(v, s.w[q]);
+        if (v > __atomic_load_n(counter, __ATOMIC_RELAXED))
+            atomicMax((unsigned long long *)counter, (unsigned long long)v);
+    }
+    __syncthreads();
 }
 
 __device__ __forceinline__ uint64_t sssp_pack(int32_t dist, int32_t parent) {

@@ -92,7 +92,6 @@ struct Dir {
     DBuf<int32_t> dcol, dw;   // [dm] diff entries (flags in dcol)
     int64_t dm = 0;           // diff entries, tombstones included
     DBuf<int32_t> deg;        // [n] live degree
-    DBuf<int32_t> ntomb;      // [n] base tombstones per row
     DBuf<int32_t> ttomb;      // [ceil(m/TILE)] base tombstones per merge tile
     int64_t tomb_base = 0;    // host mirrors
     int64_t tomb_diff = 0;

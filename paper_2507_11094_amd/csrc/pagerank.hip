@@ -48,6 +48,12 @@ static inline int grid_for(int64_t n) {
     return (int)(g < 1 ? 1 : (g > 8192 ? 8192 : g));
 }
 
+// Blocks of WIDE_T threads (kernels that append to or add into one shared counter).
+static inline int grid_wide(int64_t n) {
+    const int64_t g = (n + WIDE_T - 1) / WIDE_T;
+    return (int)(g < 1 ? 1 : (g > 512 ? 512 : g));
+}
+
 constexpr int APPLY_GROUPS = 1024;
 
 __global__ void k_pr_init(int32_t n, double *x, double *contrib, const int32_t *deg) {
@@ -517,8 +523,8 @@ struct ReachOp {
 };
 
 // Mark a list of vertices with stamp st; append the first-time ones to out.
-__global__ void k_mark_list(int64_t n, const int32_t *a, int32_t *stamp, int32_t st, int32_t *out,
-                            int64_t *count) {
+__global__ __launch_bounds__(WIDE_T) void k_mark_list(int64_t n, const int32_t *a, int32_t *stamp, int32_t st,
+                                                      int32_t *out, int64_t *count) {
     __shared__ BlockScratch sc;
     for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < n; base += gstride()) {
         int64_t i = base + threadIdx.x;
@@ -528,7 +534,7 @@ __global__ void k_mark_list(int64_t n, const int32_t *a, int32_t *stamp, int32_t
             v = a[i];
             p = atomicExch(&stamp[v], st) != st;
         }
-        int64_t slot = block_append(count, p, sc);
+        int64_t slot = block_append<WIDE_T>(count, p, sc);
         if (p) out[slot] = v;
     }
 }
@@ -815,16 +821,16 @@ static int ensure_pr_ws(dg_graph *g) {
 }
 
 // Total entries (base + diff, tombstones included) of the rows of A.
-__global__ void k_sum_degrees(const int32_t *A, int64_t na, const int64_t *na_p, const int64_t *off,
-                              const int64_t *doff, int64_t *out) {
+__global__ __launch_bounds__(WIDE_T) void k_sum_degrees(const int32_t *A, int64_t na, const int64_t *na_p,
+                                                        const int64_t *off, const int64_t *doff, int64_t *out) {
+    __shared__ BlockScratch sc;
     if (na_p) na = *na_p;
     int64_t acc = 0;
     for (int64_t i = gtid(); i < na; i += gstride()) {
         int32_t v = A[i];
         acc += (off[v + 1] - off[v]) + (doff[v + 1] - doff[v]);
     }
-    acc = wave_sum(acc);
-    if (lane_id() == 0 && acc) atomicAdd((unsigned long long *)out, (unsigned long long)acc);
+    block_count<WIDE_T>(out, acc, sc);
 }
 
 // Jacobi on A (nullptr = all n vertices) until the L1 step <= tol or max_iter.
@@ -1327,10 +1333,10 @@ static int pr_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
     DG_TRY(next_stamp(g, &st_s));
     DG_TRY(counters_clear(g));
     if (adel > 0)
-        hipLaunchKernelGGL(k_mark_list, dim3(grid_for(adel)), dim3(256), 0, s, adel, ws.adu.p,
+        hipLaunchKernelGGL(k_mark_list, dim3(grid_wide(adel)), dim3(WIDE_T), 0, s, adel, ws.adu.p,
                            ws.stamp.p, st_s, S, ws.dcnt + C_AUX0);
     if (ains > 0)
-        hipLaunchKernelGGL(k_mark_list, dim3(grid_for(ains)), dim3(256), 0, s, ains, ws.aiu.p,
+        hipLaunchKernelGGL(k_mark_list, dim3(grid_wide(ains)), dim3(WIDE_T), 0, s, ains, ws.aiu.p,
                            ws.stamp.p, st_s, S, ws.dcnt + C_AUX0);
     // the tails' share x / outdeg changed: refresh it before any Jacobi step (the
     // count of distinct tails stays on the device; grids sized for every changed arc)
@@ -1344,7 +1350,7 @@ static int pr_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
     // form without expanding (both forms reach the same ranks; this only picks the
     // cheaper one).  One read brings the tail count and that sum.
     if (mode == 0)
-        hipLaunchKernelGGL(k_sum_degrees, dim3(grid_for(adel + ains)), dim3(256), 0, s, S, (int64_t)0,
+        hipLaunchKernelGGL(k_sum_degrees, dim3(grid_wide(adel + ains)), dim3(WIDE_T), 0, s, S, (int64_t)0,
                            ws.dcnt + C_AUX0, g->fwd.off.p, g->fwd.doff.p, ws.dcnt + C_AUX1);
     DG_HIP(hipGetLastError());
     DG_TRY(counters_read(g));
@@ -1363,10 +1369,10 @@ static int pr_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
         DG_TRY(next_stamp(g, &st_a));
         DG_TRY(counters_clear(g));
         if (adel > 0)
-            hipLaunchKernelGGL(k_mark_list, dim3(grid_for(adel)), dim3(256), 0, s, adel, ws.adv.p,
+            hipLaunchKernelGGL(k_mark_list, dim3(grid_wide(adel)), dim3(WIDE_T), 0, s, adel, ws.adv.p,
                                ws.stamp.p, st_a, Alist, ws.dcnt + C_F0);
         if (ains > 0)
-            hipLaunchKernelGGL(k_mark_list, dim3(grid_for(ains)), dim3(256), 0, s, ains, ws.aiv.p,
+            hipLaunchKernelGGL(k_mark_list, dim3(grid_wide(ains)), dim3(WIDE_T), 0, s, ains, ws.aiv.p,
                                ws.stamp.p, st_a, Alist, ws.dcnt + C_F0);
         DG_HIP(hipGetLastError());
         DG_TRY(counters_read(g));
@@ -1412,7 +1418,7 @@ static int pr_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
         DG_TRY(scan_excl(g, flags, pos, g->n + 1));
         hipLaunchKernelGGL(k_compact_flags, dim3(grid_for(g->n)), dim3(256), 0, s, g->n, flags, pos, Alist);
         DG_TRY(counters_clear(g));
-        hipLaunchKernelGGL(k_sum_degrees, dim3(grid_for(na)), dim3(256), 0, s, Alist, na, (const int64_t *)nullptr,
+        hipLaunchKernelGGL(k_sum_degrees, dim3(grid_wide(na)), dim3(WIDE_T), 0, s, Alist, na, (const int64_t *)nullptr,
                            g->rev->off.p, g->rev->doff.p, ws.dcnt + C_AUX0);
         DG_HIP(hipGetLastError());
         DG_TRY(counters_read(g));

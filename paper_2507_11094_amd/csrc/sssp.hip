@@ -108,8 +108,8 @@ __global__ void k_sssp_init(int32_t n, uint64_t *key, int32_t source) {
 }
 
 // OnDelete: (u, v) deleted and parent[v] == u  ->  v := (INF, -1), v is a seed.
-__global__ void k_sssp_on_delete(int64_t na, const int32_t *adu, const int32_t *adv, uint64_t *key,
-                                 int32_t *seeds, int64_t *count) {
+__global__ __launch_bounds__(WIDE_T) void k_sssp_on_delete(int64_t na, const int32_t *adu, const int32_t *adv,
+                                                           uint64_t *key, int32_t *seeds, int64_t *count) {
     __shared__ BlockScratch sc;
     for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < na; base += gstride()) {
         int64_t i = base + threadIdx.x;
@@ -122,14 +122,14 @@ __global__ void k_sssp_on_delete(int64_t na, const int32_t *adu, const int32_t *
                 cut = true;
             }
         }
-        int64_t slot = block_append(count, cut, sc);
+        int64_t slot = block_append<WIDE_T>(count, cut, sc);
         if (cut) seeds[slot] = v;
     }
 }
 
 // After the pull: cut vertices that now have a finite distance start the push.
-__global__ void k_sssp_pulled(int64_t nc, const int32_t *cut, const uint64_t *key, int32_t *stamp,
-                              int32_t st, int32_t *front, int64_t *count) {
+__global__ __launch_bounds__(WIDE_T) void k_sssp_pulled(int64_t nc, const int32_t *cut, const uint64_t *key,
+                                                        int32_t *stamp, int32_t st, int32_t *front, int64_t *count) {
     __shared__ BlockScratch sc;
     for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < nc; base += gstride()) {
         int64_t i = base + threadIdx.x;
@@ -139,15 +139,15 @@ __global__ void k_sssp_pulled(int64_t nc, const int32_t *cut, const uint64_t *ke
             v = cut[i];
             p = sssp_dist(key[v]) < INF && atomicExch(&stamp[v], st) != st;
         }
-        int64_t slot = block_append(count, p, sc);
+        int64_t slot = block_append<WIDE_T>(count, p, sc);
         if (p) front[slot] = v;
     }
 }
 
 // OnAdd: each inserted arc relaxes its head once; improved heads join the push.
-__global__ void k_sssp_on_add(int64_t na, const int32_t *aiu, const int32_t *aiv, const int32_t *aiw,
-                              uint64_t *key, int32_t *stamp, int32_t st, int32_t *front,
-                              int64_t *count) {
+__global__ __launch_bounds__(WIDE_T) void k_sssp_on_add(int64_t na, const int32_t *aiu, const int32_t *aiv,
+                                                        const int32_t *aiw, uint64_t *key, int32_t *stamp,
+                                                        int32_t st, int32_t *front, int64_t *count) {
     __shared__ BlockScratch sc;
     for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < na; base += gstride()) {
         int64_t i = base + threadIdx.x;
@@ -163,7 +163,7 @@ __global__ void k_sssp_on_add(int64_t na, const int32_t *aiu, const int32_t *aiv
                 if (cand < old && sssp_dist(cand) < sssp_dist(old)) p = atomicExch(&stamp[v], st) != st;
             }
         }
-        int64_t slot = block_append(count, p, sc);
+        int64_t slot = block_append<WIDE_T>(count, p, sc);
         if (p) front[slot] = v;
     }
 }
@@ -188,6 +188,12 @@ __global__ void k_sssp_unpack(int32_t n, const uint64_t *key, const int32_t *per
 static inline int grid_for(int64_t n) {
     int64_t g = (n + 255) / 256;
     return (int)(g < 1 ? 1 : (g > 8192 ? 8192 : g));
+}
+
+// Blocks of WIDE_T threads (kernels that append to or raise one shared counter).
+static inline int grid_wide(int64_t n) {
+    const int64_t g = (n + WIDE_T - 1) / WIDE_T;
+    return (int)(g < 1 ? 1 : (g > 512 ? 512 : g));
 }
 
 static int heavy_deg(dg_graph *g) { return g->cfg.heavy_degree > 0 ? g->cfg.heavy_degree : 512; }
@@ -240,8 +246,9 @@ static ExpandArgs with_tally(ExpandArgs a, int64_t *tally) {
 // fixed point is the same.
 
 // Improved vertices (count on the device) -> near (dist < T) or the far pile.
-__global__ void k_nf_split(const int64_t *nn_p, const int32_t *N, const uint64_t *key, int32_t T, int32_t *near,
-                           int64_t *nnear, int32_t *far, int64_t *nfar, int32_t *farflag, int32_t fst) {
+__global__ __launch_bounds__(WIDE_T) void k_nf_split(const int64_t *nn_p, const int32_t *N, const uint64_t *key,
+                                                     int32_t T, int32_t *near, int64_t *nnear, int32_t *far,
+                                                     int64_t *nfar, int32_t *farflag, int32_t fst) {
     __shared__ BlockScratch sc;
     const int64_t nn = *nn_p;
     for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < nn; base += gstride()) {
@@ -253,27 +260,29 @@ __global__ void k_nf_split(const int64_t *nn_p, const int32_t *N, const uint64_t
             pn = sssp_dist(key[v]) < T;
             pf = !pn && atomicExch(&farflag[v], fst) != fst;
         }
-        const int64_t sn = block_append(nnear, pn, sc);
+        const int64_t sn = block_append<WIDE_T>(nnear, pn, sc);
         if (pn) near[sn] = v;
-        const int64_t sf = block_append(nfar, pf, sc);
+        const int64_t sf = block_append<WIDE_T>(nfar, pf, sc);
         if (pf) far[sf] = v;
     }
 }
 
 // Smallest distance >= T in the far pile, as INF - d through a max (0: none).
-__global__ void k_nf_min(int64_t nf, const int32_t *far, const uint64_t *key, int32_t T, int64_t *out) {
+__global__ __launch_bounds__(WIDE_T) void k_nf_min(int64_t nf, const int32_t *far, const uint64_t *key, int32_t T,
+                                                   int64_t *out) {
+    __shared__ BlockScratch sc;
     int64_t best = 0;
     for (int64_t i = gtid(); i < nf; i += gstride()) {
         const int32_t d = sssp_dist(key[far[i]]);
         if (d >= T && d < INF) best = max(best, (int64_t)(INF - d));
     }
-    best = wave_max_i32((int32_t)best);
-    if (lane_id() == 0 && best > 0) atomicMax((unsigned long long *)out, (unsigned long long)best);
+    block_raise<WIDE_T>(out, best, sc);
 }
 
 // Next bucket: entries in [T0, T1) go near, entries >= T1 stay, the rest are stale.
-__global__ void k_nf_refill(int64_t nf, const int32_t *far, const uint64_t *key, int32_t T0, int32_t T1,
-                            int32_t *near, int64_t *nnear, int32_t *far2, int64_t *nfar2, int32_t *farflag) {
+__global__ __launch_bounds__(WIDE_T) void k_nf_refill(int64_t nf, const int32_t *far, const uint64_t *key,
+                                                      int32_t T0, int32_t T1, int32_t *near, int64_t *nnear,
+                                                      int32_t *far2, int64_t *nfar2, int32_t *farflag) {
     __shared__ BlockScratch sc;
     for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < nf; base += gstride()) {
         const int64_t i = base + threadIdx.x;
@@ -286,21 +295,22 @@ __global__ void k_nf_refill(int64_t nf, const int32_t *far, const uint64_t *key,
             pn = !pk && d >= T0;
             if (!pk) farflag[v] = 0;
         }
-        const int64_t sn = block_append(nnear, pn, sc);
+        const int64_t sn = block_append<WIDE_T>(nnear, pn, sc);
         if (pn) near[sn] = v;
-        const int64_t sk = block_append(nfar2, pk, sc);
+        const int64_t sk = block_append<WIDE_T>(nfar2, pk, sc);
         if (pk) far2[sk] = v;
     }
 }
 
-__global__ void k_nf_seed_min(int64_t nf, const int32_t *F, const uint64_t *key, int64_t *out) {
+__global__ __launch_bounds__(WIDE_T) void k_nf_seed_min(int64_t nf, const int32_t *F, const uint64_t *key,
+                                                        int64_t *out) {
+    __shared__ BlockScratch sc;
     int64_t best = 0;
     for (int64_t i = gtid(); i < nf; i += gstride()) {
         const int32_t d = sssp_dist(key[F[i]]);
         if (d < INF) best = max(best, (int64_t)(INF - d));
     }
-    best = wave_max_i32((int32_t)best);
-    if (lane_id() == 0 && best > 0) atomicMax((unsigned long long *)out, (unsigned long long)best);
+    block_raise<WIDE_T>(out, best, sc);
 }
 
 static int sssp_push_nearfar(dg_graph *g, uint64_t *key, int64_t nf, int32_t delta, dg_batch_stats *st) {
@@ -318,7 +328,7 @@ static int sssp_push_nearfar(dg_graph *g, uint64_t *key, int64_t nf, int32_t del
     int32_t *A = ws.f0.p, *B = ws.f1.p, *far = ws.far0.p, *far2 = ws.far1.p;
     // first threshold: nearest seed + delta (every seed is relaxed in the first round)
     DG_TRY(counters_clear(g));
-    hipLaunchKernelGGL(k_nf_seed_min, dim3(grid_for(nf)), dim3(256), 0, s, nf, A, key, ws.dcnt + C_AUX2);
+    hipLaunchKernelGGL(k_nf_seed_min, dim3(grid_wide(nf)), dim3(WIDE_T), 0, s, nf, A, key, ws.dcnt + C_AUX2);
     DG_HIP(hipGetLastError());
     DG_TRY(counters_read(g));
     if (ws.hcnt[C_AUX2] == 0) return DG_OK;
@@ -333,7 +343,7 @@ static int sssp_push_nearfar(dg_graph *g, uint64_t *key, int64_t nf, int32_t del
             DG_TRY(counters_clear(g));
             RelaxOp op{key, ws.stamp.p, stv, B, ws.dcnt + C_F1};
             DG_TRY(launch_expand(s, with_tally(make_args(g, g->fwd, A, nnear), ws.dcnt + C_EDGES), op, 8192));
-            hipLaunchKernelGGL(k_nf_split, dim3(4096), dim3(256), 0, s, ws.dcnt + C_F1, B, key, T, A,
+            hipLaunchKernelGGL(k_nf_split, dim3(512), dim3(WIDE_T), 0, s, ws.dcnt + C_F1, B, key, T, A,
                                ws.dcnt + C_F0, far + nfar, ws.dcnt + C_AUX1, ws.farflag.p, fst);
             DG_HIP(hipGetLastError());
             DG_TRY(counters_read(g));
@@ -345,13 +355,13 @@ static int sssp_push_nearfar(dg_graph *g, uint64_t *key, int64_t nf, int32_t del
         }
         if (nfar == 0) break;
         DG_TRY(counters_clear(g));
-        hipLaunchKernelGGL(k_nf_min, dim3(grid_for(nfar)), dim3(256), 0, s, nfar, far, key, T, ws.dcnt + C_AUX2);
+        hipLaunchKernelGGL(k_nf_min, dim3(grid_wide(nfar)), dim3(WIDE_T), 0, s, nfar, far, key, T, ws.dcnt + C_AUX2);
         DG_HIP(hipGetLastError());
         DG_TRY(counters_read(g));
         const int64_t best = ws.hcnt[C_AUX2];
         const int32_t T1 = best == 0 ? INF : (int32_t)std::min<int64_t>((int64_t)(INF - best) + delta, INF);
         DG_TRY(counters_clear(g));
-        hipLaunchKernelGGL(k_nf_refill, dim3(grid_for(nfar)), dim3(256), 0, s, nfar, far, key, T, T1, A,
+        hipLaunchKernelGGL(k_nf_refill, dim3(grid_wide(nfar)), dim3(WIDE_T), 0, s, nfar, far, key, T, T1, A,
                            ws.dcnt + C_F0, far2, ws.dcnt + C_AUX1, ws.farflag.p);
         DG_HIP(hipGetLastError());
         DG_TRY(counters_read(g));
@@ -507,7 +517,7 @@ int sssp_pre_delete(dg_query *q, int64_t adel) {
     q->nseeds = 0;
     if (adel <= 0) return DG_OK;
     DG_TRY(counters_clear(g));
-    hipLaunchKernelGGL(k_sssp_on_delete, dim3(grid_for(adel)), dim3(256), 0, g->stream, adel,
+    hipLaunchKernelGGL(k_sssp_on_delete, dim3(grid_wide(adel)), dim3(WIDE_T), 0, g->stream, adel,
                        g->ws.adu.p, g->ws.adv.p, q->key.p, q->inval.p, g->ws.dcnt + C_AUX0);
     DG_HIP(hipGetLastError());
     DG_TRY(counters_read(g));
@@ -613,8 +623,9 @@ struct RelaxOpD {
     __device__ SinkTarget sink() const { return SinkTarget{next, ncount}; }
 };
 
-__global__ void k_sssp_pulled_d(const int64_t *nc_p, const int32_t *cut, const uint64_t *key, int32_t *stamp,
-                                const int64_t *stp, int32_t *front, int64_t *count) {
+__global__ __launch_bounds__(WIDE_T) void k_sssp_pulled_d(const int64_t *nc_p, const int32_t *cut,
+                                                          const uint64_t *key, int32_t *stamp, const int64_t *stp,
+                                                          int32_t *front, int64_t *count) {
     __shared__ BlockScratch sc;
     const int64_t nc = *nc_p;
     const int32_t st = (int32_t)*stp;
@@ -626,13 +637,15 @@ __global__ void k_sssp_pulled_d(const int64_t *nc_p, const int32_t *cut, const u
             v = cut[i];
             p = sssp_dist(key[v]) < INF && atomicExch(&stamp[v], st) != st;
         }
-        int64_t slot = block_append(count, p, sc);
+        int64_t slot = block_append<WIDE_T>(count, p, sc);
         if (p) front[slot] = v;
     }
 }
 
-__global__ void k_sssp_on_add_d(const int64_t *na_p, const int32_t *aiu, const int32_t *aiv, const int32_t *aiw,
-                                uint64_t *key, int32_t *stamp, const int64_t *stp, int32_t *front, int64_t *count) {
+__global__ __launch_bounds__(WIDE_T) void k_sssp_on_add_d(const int64_t *na_p, const int32_t *aiu,
+                                                          const int32_t *aiv, const int32_t *aiw, uint64_t *key,
+                                                          int32_t *stamp, const int64_t *stp, int32_t *front,
+                                                          int64_t *count) {
     __shared__ BlockScratch sc;
     const int64_t na = *na_p;
     const int32_t st = (int32_t)*stp;
@@ -650,7 +663,7 @@ __global__ void k_sssp_on_add_d(const int64_t *na_p, const int32_t *aiu, const i
                 if (cand < old && sssp_dist(cand) < sssp_dist(old)) p = atomicExch(&stamp[v], st) != st;
             }
         }
-        int64_t slot = block_append(count, p, sc);
+        int64_t slot = block_append<WIDE_T>(count, p, sc);
         if (p) front[slot] = v;
     }
 }
@@ -678,15 +691,16 @@ __global__ void k_nfd_reset(int64_t *ctr) {
 }
 
 // Smallest finite distance of the seeds, as INF - d through a max (0: none).
-__global__ void k_nfd_seed_min(const int64_t *nf_p, const int32_t *F, const uint64_t *key, int64_t *out) {
+__global__ __launch_bounds__(WIDE_T) void k_nfd_seed_min(const int64_t *nf_p, const int32_t *F, const uint64_t *key,
+                                                         int64_t *out) {
+    __shared__ BlockScratch sc;
     const int64_t nf = *nf_p;
     int64_t best = 0;
     for (int64_t i = gtid(); i < nf; i += gstride()) {
         const int32_t d = sssp_dist(key[F[i]]);
         if (d < INF) best = max(best, (int64_t)(INF - d));
     }
-    best = wave_max_i32((int32_t)best);
-    if (lane_id() == 0 && best > 0) atomicMax((unsigned long long *)out, (unsigned long long)best);
+    block_raise<WIDE_T>(out, best, sc);
 }
 
 // First threshold: nearest seed + delta (INF when no seed is finite: nothing moves).
@@ -724,8 +738,9 @@ __global__ void k_nfd_step(int64_t *ctr, int32_t delta, const int64_t *in_cnt, i
 }
 
 // Relaxed vertices (count at ctr[R_NB]) -> next near frontier (dist < T) or the pile.
-__global__ void k_nfd_split(const int32_t *N, const uint64_t *key, int64_t *ctr, int32_t *near, int64_t *nnear,
-                            int32_t *far0, int32_t *far1, int32_t *farflag) {
+__global__ __launch_bounds__(WIDE_T) void k_nfd_split(const int32_t *N, const uint64_t *key, int64_t *ctr,
+                                                      int32_t *near, int64_t *nnear, int32_t *far0, int32_t *far1,
+                                                      int32_t *farflag) {
     __shared__ BlockScratch sc;
     const int64_t nn = ctr[R_NB];
     const int32_t T = (int32_t)ctr[R_T], fst = (int32_t)ctr[R_FST];
@@ -739,9 +754,9 @@ __global__ void k_nfd_split(const int32_t *N, const uint64_t *key, int64_t *ctr,
             pn = sssp_dist(key[v]) < T;
             pf = !pn && atomicExch(&farflag[v], fst) != fst;
         }
-        const int64_t sn = block_append(nnear, pn, sc);
+        const int64_t sn = block_append<WIDE_T>(nnear, pn, sc);
         if (pn) near[sn] = v;
-        const int64_t sf = block_append(ctr + R_NF, pf, sc);
+        const int64_t sf = block_append<WIDE_T>(ctr + R_NF, pf, sc);
         if (pf) far[sf] = v;
     }
 }
@@ -750,8 +765,9 @@ __global__ void k_nfd_split(const int32_t *N, const uint64_t *key, int64_t *ctr,
 // not (the split is done, so the near count is final here; the refill that appends
 // to it reads the decision from R_ADV).  Then: smallest pile distance >= T, as
 // INF - d through a max (0: none).
-__global__ void k_nfd_min(int64_t *ctr, const int64_t *nnear, const int32_t *far0, const int32_t *far1,
-                          const uint64_t *key) {
+__global__ __launch_bounds__(WIDE_T) void k_nfd_min(int64_t *ctr, const int64_t *nnear, const int32_t *far0,
+                                                    const int32_t *far1, const uint64_t *key) {
+    __shared__ BlockScratch sc;
     const bool adv = *nnear == 0 && ctr[R_NF] > 0;
     if (blockIdx.x == 0 && threadIdx.x == 0) ctr[R_ADV] = adv ? 1 : 0;
     if (!adv) return;
@@ -763,14 +779,14 @@ __global__ void k_nfd_min(int64_t *ctr, const int64_t *nnear, const int32_t *far
         const int32_t d = sssp_dist(key[far[i]]);
         if (d >= T && d < INF) best = max(best, (int64_t)(INF - d));
     }
-    best = wave_max_i32((int32_t)best);
-    if (lane_id() == 0 && best > 0) atomicMax((unsigned long long *)(ctr + R_BEST), (unsigned long long)best);
+    block_raise<WIDE_T>(ctr + R_BEST, best, sc);
 }
 
 // Next bucket: pile entries in [T, T1) go near, entries >= T1 stay (other buffer),
 // the rest are stale; entries leaving the pile clear their membership stamp.
-__global__ void k_nfd_refill(int64_t *ctr, int32_t *far0, int32_t *far1, const uint64_t *key, int32_t delta,
-                             int32_t *near, int64_t *nnear, int32_t *farflag) {
+__global__ __launch_bounds__(WIDE_T) void k_nfd_refill(int64_t *ctr, int32_t *far0, int32_t *far1,
+                                                       const uint64_t *key, int32_t delta, int32_t *near,
+                                                       int64_t *nnear, int32_t *farflag) {
     __shared__ BlockScratch sc;
     if (ctr[R_ADV] == 0) return;
     const int64_t nf = ctr[R_NF];
@@ -788,9 +804,9 @@ __global__ void k_nfd_refill(int64_t *ctr, int32_t *far0, int32_t *far1, const u
             pn = !pk && d >= T0;
             if (!pk) farflag[v] = 0;
         }
-        const int64_t sn = block_append(nnear, pn, sc);
+        const int64_t sn = block_append<WIDE_T>(nnear, pn, sc);
         if (pn) near[sn] = v;
-        const int64_t sk = block_append(ctr + R_NF2, pk, sc);
+        const int64_t sk = block_append<WIDE_T>(ctr + R_NF2, pk, sc);
         if (pk) far2[sk] = v;
     }
 }
@@ -858,10 +874,10 @@ static int nf_round(dg_query *q, const int32_t *F, const int64_t *cf, int32_t *N
     hipLaunchKernelGGL(k_nfd_step, dim3(1), dim3(64), 0, s, ctr, delta, cf, cn, ws.dcnt + C_HEAVY);
     RelaxOpD op{q->key.p, q->gstamp.p, ctr + R_STAMP, ws.nfout.p, ctr + R_NB};
     DG_TRY(launch_expand(s, with_tally(dev_args(g, g->fwd, F, cf), ctr + R_EDGES), op, 1024));
-    hipLaunchKernelGGL(k_nfd_split, dim3(256), dim3(256), 0, s, ws.nfout.p, q->key.p, ctr, N, cn, ws.far0.p,
+    hipLaunchKernelGGL(k_nfd_split, dim3(64), dim3(WIDE_T), 0, s, ws.nfout.p, q->key.p, ctr, N, cn, ws.far0.p,
                        ws.far1.p, q->gfar.p);
-    hipLaunchKernelGGL(k_nfd_min, dim3(64), dim3(256), 0, s, ctr, cn, ws.far0.p, ws.far1.p, q->key.p);
-    hipLaunchKernelGGL(k_nfd_refill, dim3(64), dim3(256), 0, s, ctr, ws.far0.p, ws.far1.p, q->key.p, delta, N, cn,
+    hipLaunchKernelGGL(k_nfd_min, dim3(16), dim3(WIDE_T), 0, s, ctr, cn, ws.far0.p, ws.far1.p, q->key.p);
+    hipLaunchKernelGGL(k_nfd_refill, dim3(16), dim3(WIDE_T), 0, s, ctr, ws.far0.p, ws.far1.p, q->key.p, delta, N, cn,
                        q->gfar.p);
     return DG_OK;
 }
@@ -882,13 +898,13 @@ static int rounds_push_enqueue(dg_query *q, bool first) {
                              PullOp{q->key.p}, 1024));
         // seeds: pulled cut vertices and improved heads of inserted arcs
         hipLaunchKernelGGL(k_round_prep, dim3(1), dim3(64), 0, s, ctr + R_PA, ws.dcnt + C_HEAVY, ctr, nullptr);
-        hipLaunchKernelGGL(k_sssp_pulled_d, dim3(1024), dim3(256), 0, s, ctr + R_LIST, q->inval.p, q->key.p,
+        hipLaunchKernelGGL(k_sssp_pulled_d, dim3(256), dim3(WIDE_T), 0, s, ctr + R_LIST, q->inval.p, q->key.p,
                            q->gstamp.p, ctr + R_STAMP, ws.f0.p, ctr + R_PA);
-        hipLaunchKernelGGL(k_sssp_on_add_d, dim3(1024), dim3(256), 0, s, ctr + 1, ws.aiu.p, ws.aiv.p, ws.aiw.p,
+        hipLaunchKernelGGL(k_sssp_on_add_d, dim3(256), dim3(WIDE_T), 0, s, ctr + 1, ws.aiu.p, ws.aiv.p, ws.aiw.p,
                            q->key.p, q->gstamp.p, ctr + R_STAMP, ws.f0.p, ctr + R_PA);
         if (nf) {
             hipLaunchKernelGGL(k_nfd_reset, dim3(1), dim3(64), 0, s, ctr);
-            hipLaunchKernelGGL(k_nfd_seed_min, dim3(1024), dim3(256), 0, s, ctr + R_PA, ws.f0.p, q->key.p,
+            hipLaunchKernelGGL(k_nfd_seed_min, dim3(256), dim3(WIDE_T), 0, s, ctr + R_PA, ws.f0.p, q->key.p,
                                ctr + R_BEST);
             hipLaunchKernelGGL(k_nfd_start, dim3(1), dim3(64), 0, s, ctr, g->cfg.sssp_delta);
         }
@@ -1065,10 +1081,10 @@ int sssp_post_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
     int32_t stv;
     DG_TRY(next_stamp(g, &stv));
     if (ncut > 0)
-        hipLaunchKernelGGL(k_sssp_pulled, dim3(grid_for(ncut)), dim3(256), 0, s, ncut, q->inval.p,
+        hipLaunchKernelGGL(k_sssp_pulled, dim3(grid_wide(ncut)), dim3(WIDE_T), 0, s, ncut, q->inval.p,
                            q->key.p, ws.stamp.p, stv, ws.f0.p, ws.dcnt + C_F0);
     if (ains > 0)
-        hipLaunchKernelGGL(k_sssp_on_add, dim3(grid_for(ains)), dim3(256), 0, s, ains, ws.aiu.p,
+        hipLaunchKernelGGL(k_sssp_on_add, dim3(grid_wide(ains)), dim3(WIDE_T), 0, s, ains, ws.aiu.p,
                            ws.aiv.p, ws.aiw.p, q->key.p, ws.stamp.p, stv, ws.f0.p, ws.dcnt + C_F0);
     DG_HIP(hipGetLastError());
     DG_TRY(counters_read(g));

@@ -310,6 +310,7 @@ __global__ __launch_bounds__(256) void k_tc_orient(int32_t n, const int64_t *__r
 // when N+(y) is much longer, take the elements of N+(x) and binary-search N+(y)
 // in memory.
 constexpr int TCF_CAP = 1024;  // forward-list entries of a row staged in LDS, per wave
+constexpr int TCF_BLOCKS = 8192;  // four or more grids of resident blocks, few enough adds to the total
 
 __device__ __forceinline__ bool lds_has(const int32_t *a, int len, int32_t v) {
     int lo = 0, hi = len;
@@ -370,8 +371,16 @@ __global__ __launch_bounds__(256) void k_tc_forward(int32_t n, const int64_t *__
         }
         if (staged) wave_sync();  // the next row overwrites the staging
     }
+    // one add per block: a wave's add to the one total costs about 12 ns of a serial
+    // chain (262k rows, 131k waves: 2.19 ms with an add per wave)
+    __shared__ uint64_t s_acc[256 / WAVE];
     acc = wave_sum(acc);
-    if (l == 0 && acc) atomicAdd(total, (unsigned long long)acc);
+    if (l == 0) s_acc[threadIdx.x / WAVE] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int q = 1; q < 256 / WAVE; ++q) acc += s_acc[q];
+        if (acc) atomicAdd(total, (unsigned long long)acc);
+    }
 }
 
 int tc_count_static(dg_graph *g, uint64_t *count) {
@@ -394,7 +403,7 @@ int tc_count_static(dg_graph *g, uint64_t *count) {
                        ooff, ocol);
     DG_TRY(counters_clear(g));
     unsigned long long *acc = reinterpret_cast<unsigned long long *>(g->ws.dcnt + C_TC1);
-    hipLaunchKernelGGL(k_tc_forward, dim3(blocks), dim3(256), 0, s, n, ooff, ocol, acc);
+    hipLaunchKernelGGL(k_tc_forward, dim3(std::min(blocks, TCF_BLOCKS)), dim3(256), 0, s, n, ooff, ocol, acc);
     DG_HIP(hipGetLastError());
     DG_TRY(counters_read(g));
     *count = (uint64_t)g->ws.hcnt[C_TC1];
