@@ -198,8 +198,16 @@ enum Counter {
     C_MAXROW = 38,
     // set by a sort or scan whose look-back hit its spin limit; counters_clear
     // leaves it alone, counters_read reports it
-    C_SORT_ERR = 39, C_COUNT = 40
+    C_SORT_ERR = 39, C_COUNT = 40,
+    // slots of the traversal tally, summed into the host copy's C_EDGES by
+    // counters_read; then, host copy only, 16 slots of PageRank step state
+    C_TALLY = 64
 };
+// The tally's adds go to TALLY_SLOTS slots, a cache line each: same-line atomics of
+// different blocks run one after the other.
+constexpr int TALLY_SLOTS = 16, TALLY_STRIDE = 16;
+constexpr int C_ALL = C_TALLY + TALLY_SLOTS * TALLY_STRIDE;
+constexpr int H_PR = C_ALL, H_ALL = C_ALL + 16;
 
 }  // namespace dg
 

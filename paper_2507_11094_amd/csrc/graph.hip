@@ -82,27 +82,38 @@ int scan_excl(dg_graph *g, const int64_t *in, int64_t *out, int64_t n) {
 
 // ---------------------------------------------------------------- counters
 
-int counters_clear(dg_graph *g) { return fill_i64(g->ws.dcnt, 0, C_MAXROW, g->stream); }
+// Every counter and tally slot but C_MAXROW and C_SORT_ERR.
+__global__ __launch_bounds__(C_ALL) void k_counters_clear(int64_t *cnt) {
+    const int i = threadIdx.x;
+    if (i != C_MAXROW && i != C_SORT_ERR) cnt[i] = 0;
+}
+
+int counters_clear(dg_graph *g) {
+    hipLaunchKernelGGL(k_counters_clear, dim3(1), dim3(C_ALL), 0, g->stream, g->ws.dcnt);
+    DG_HIP(hipGetLastError());
+    return DG_OK;
+}
 
 int counters_read(dg_graph *g) {
-    DG_HIP(hipMemcpyAsync(g->ws.hcnt, g->ws.dcnt, sizeof(int64_t) * C_COUNT, hipMemcpyDeviceToHost,
+    DG_HIP(hipMemcpyAsync(g->ws.hcnt, g->ws.dcnt, sizeof(int64_t) * C_ALL, hipMemcpyDeviceToHost,
                           g->stream));
     DG_HIP(wait_stream(g, g->stream));
+    g->ws.hcnt[C_EDGES] = 0;
+    for (int j = 0; j < TALLY_SLOTS; ++j) g->ws.hcnt[C_EDGES] += g->ws.hcnt[C_TALLY + j * TALLY_STRIDE];
     if (g->ws.hcnt[C_SORT_ERR]) return set_error(DG_EDEVICE, "sort or scan look-back did not finish (internal error)");
     return DG_OK;
 }
 
 int ws_init(dg_graph *g) {
-    g->ws.dcnt = static_cast<int64_t *>(dmalloc(sizeof(int64_t) * C_COUNT));
+    g->ws.dcnt = static_cast<int64_t *>(dmalloc(sizeof(int64_t) * C_ALL));
     if (!g->ws.dcnt) return set_error(DG_ENOMEM, "counter allocation failed");
-    // C_COUNT counter slots, then 8 slots of PageRank step state
-    DG_HIP(hipHostMalloc((void **)&g->ws.hcnt, sizeof(int64_t) * (C_COUNT + 16), hipHostMallocDefault));
+    DG_HIP(hipHostMalloc((void **)&g->ws.hcnt, sizeof(int64_t) * H_ALL, hipHostMallocDefault));
     g->ws.dcnt_m = static_cast<int64_t *>(dmalloc(sizeof(int64_t) * C_COUNT));
     if (!g->ws.dcnt_m) return set_error(DG_ENOMEM, "counter allocation failed");
     DG_HIP(hipHostMalloc((void **)&g->ws.hcnt_m, sizeof(int64_t) * C_COUNT, hipHostMallocDefault));
     for (auto &e : g->ws.ev) DG_HIP(hipEventCreate(&e));
     DG_TRY(fill_i64(g->ws.dcnt_m, 0, C_COUNT, g->stream));
-    return fill_i64(g->ws.dcnt, 0, C_COUNT, g->stream);
+    return fill_i64(g->ws.dcnt, 0, C_ALL, g->stream);
 }
 
 void dir_free(Dir &d) {

@@ -510,15 +510,18 @@ __global__ void k_scale(const double *x, const int32_t *perm, int64_t n, const d
 
 // Reach closure and seeds.
 struct ReachOp {
+    static constexpr bool W = false, REDUCE = false, SPLIT = false;
     int32_t *stamp;
     int32_t st;
     int32_t *next;
     int64_t *ncount;
     __device__ bool vtx(int32_t, int32_t &pay) const { pay = 0; return true; }
-    __device__ bool edge(bool valid, int32_t, int32_t, int32_t x, int32_t) const {
-        // plain load first: most edges reach vertices that are already marked
-        return valid && stamp[x] != st && atomicExch(&stamp[x], st) != st;
+    // plain load first: most edges reach vertices that are already marked
+    __device__ int32_t peek(int32_t x) const { return stamp[x]; }
+    __device__ int attempt(bool valid, int32_t, int32_t, int32_t x, int32_t, int32_t p) const {
+        return valid && p != st && atomicExch(&stamp[x], st) != st;
     }
+    __device__ int select(bool, int32_t, int32_t, int32_t, int32_t, int a) const { return a; }
     __device__ SinkTarget sink() const { return SinkTarget{next, ncount}; }
 };
 
@@ -997,9 +1000,9 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
         launched += grp;
         double hp[11];
         // the host slots after the counters: a counter read of a side stream leaves them alone
-        DG_HIP(hipMemcpyAsync(ws.hcnt + C_COUNT, prs, sizeof(hp), hipMemcpyDeviceToHost, s));
+        DG_HIP(hipMemcpyAsync(ws.hcnt + H_PR, prs, sizeof(hp), hipMemcpyDeviceToHost, s));
         DG_HIP(hipStreamSynchronize(s));
-        std::memcpy(hp, ws.hcnt + C_COUNT, sizeof(hp));
+        std::memcpy(hp, ws.hcnt + H_PR, sizeof(hp));
         const int32_t total = (int32_t)hp[4];
         ws.pr_moves = (int32_t)hp[10];
         // launches after convergence did no work: keep them out of the timings
@@ -1129,6 +1132,7 @@ __global__ void k_push_take(const int32_t *F, int64_t nf, double *res, double *x
 // not needed); every neighbour joins the next round's candidates (once, stamp
 // st), where the take decides whether its residual is worth pushing.
 struct PushOp {
+    static constexpr bool W = false, REDUCE = false, SPLIT = false;
     double *res;
     const double *share;
     int32_t *stamp;
@@ -1139,12 +1143,14 @@ struct PushOp {
         pay = 0;
         return share[v] != 0.0;
     }
-    __device__ bool edge(bool valid, int32_t v, int32_t, int32_t x, int32_t) const {
-        if (!valid) return false;
+    // plain load first: most neighbours are already candidates
+    __device__ int32_t peek(int32_t x) const { return stamp[x]; }
+    __device__ int attempt(bool valid, int32_t v, int32_t, int32_t x, int32_t, int32_t p) const {
+        if (!valid) return 0;
         unsafeAtomicAdd(&res[x], share[v]);
-        // plain load first: most neighbours are already candidates
-        return stamp[x] != st && atomicExch(&stamp[x], st) != st;
+        return p != st && atomicExch(&stamp[x], st) != st;
     }
+    __device__ int select(bool, int32_t, int32_t, int32_t, int32_t, int a) const { return a; }
     __device__ SinkTarget sink() const { return SinkTarget{next, ncount}; }
 };
 
@@ -1228,7 +1234,7 @@ static int pr_push_run(dg_query *q, const int32_t *L, int64_t nl, dg_batch_stats
             a.F = F;
             a.nf = nf;
             PushOp op{q->res.p, share, ws.stamp.p, stamp, N, ws.dcnt + C_F1};
-            DG_TRY(launch_expand(s, a, op, 8192));
+            DG_TRY(launch_expand(s, a, op));
             DG_TRY(counters_read(g));
             // per pushed vertex: F entry 4, residual 8 read + 8 written, x 8 + 8, contrib 8, share 8,
             // degree 4 and offsets 16; per arc: col 4, residual atomic 8 + 8
@@ -1299,9 +1305,9 @@ static int pr_mass(dg_query *q, double *S) {
                        1.0, 0.0, 1, 0, ws.prs.p, ws.prs.p + 5);
     DG_HIP(hipGetLastError());
     // prs[0] here holds the plain sum (first partial of each pair)
-    DG_HIP(hipMemcpyAsync(ws.hcnt + C_COUNT, ws.prs.p, sizeof(double), hipMemcpyDeviceToHost, s));
+    DG_HIP(hipMemcpyAsync(ws.hcnt + H_PR, ws.prs.p, sizeof(double), hipMemcpyDeviceToHost, s));
     DG_HIP(hipStreamSynchronize(s));
-    std::memcpy(S, ws.hcnt + C_COUNT, sizeof(double));
+    std::memcpy(S, ws.hcnt + H_PR, sizeof(double));
     return DG_OK;
 }
 
@@ -1381,7 +1387,7 @@ static int pr_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
         a.F = S;
         a.nf = ns;
         ReachOp op{ws.stamp.p, st_a, Alist + na, ws.dcnt + C_F1};
-        DG_TRY(launch_expand(s, a, op, 8192));
+        DG_TRY(launch_expand(s, a, op));
         DG_TRY(counters_read(g));
         na += ws.hcnt[C_F1];
         if (mode == 3) {
@@ -1401,7 +1407,7 @@ static int pr_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
         a.F = Alist + lo;
         a.nf = hi - lo;
         ReachOp op{ws.stamp.p, st_a, Alist + hi, ws.dcnt + C_F1};
-        DG_TRY(launch_expand(s, a, op, 8192));
+        DG_TRY(launch_expand(s, a, op));
         DG_TRY(counters_read(g));
         lo = hi;
         hi += ws.hcnt[C_F1];

@@ -39,6 +39,7 @@ namespace dg {
 
 // Push relaxation: payload = dist of the frontier vertex.
 struct RelaxOp {
+    static constexpr bool W = true, REDUCE = false, SPLIT = false;
     uint64_t *key;
     int32_t *stamp;
     int32_t st;
@@ -49,54 +50,54 @@ struct RelaxOp {
         pay = d;
         return d < INF;
     }
-    __device__ bool edge(bool valid, int32_t v, int32_t d, int32_t x, int32_t w) const {
-        bool push = false;
-        if (valid) {
-            uint64_t cand = sssp_pack(d + w, v);
-            // keys only decrease, so a stale plain load can only make us skip a
-            // candidate that would not have won the atomicMin either
-            if (cand < __atomic_load_n(&key[x], __ATOMIC_RELAXED)) {
-                uint64_t old = atomicMin((unsigned long long *)&key[x], (unsigned long long)cand);
-                if (cand < old && sssp_dist(cand) < sssp_dist(old))
-                    push = atomicExch(&stamp[x], st) != st;
-            }
-        }
-        return push;
+    __device__ uint64_t peek(int32_t x) const { return __atomic_load_n(&key[x], __ATOMIC_RELAXED); }
+    // The key x had before, or 0 (smaller than any candidate) where there was no try.
+    __device__ uint64_t attempt(bool valid, int32_t v, int32_t d, int32_t x, int32_t w, uint64_t p) const {
+        const uint64_t cand = sssp_pack(d + w, v);
+        // keys only decrease, so a stale plain load can only make us skip a
+        // candidate that would not have won the atomicMin either
+        uint64_t old = 0;
+        if (valid && cand < p) old = atomicMin((unsigned long long *)&key[x], (unsigned long long)cand);
+        return old;
+    }
+    __device__ int select(bool, int32_t, int32_t d, int32_t x, int32_t w, uint64_t old) const {
+        // a strictly smaller distance (a tie only changed the parent)
+        return d + w < sssp_dist(old) && atomicExch(&stamp[x], st) != st;
     }
     __device__ SinkTarget sink() const { return SinkTarget{next, ncount}; }
 };
 
 // Decremental phase 1: cut children whose tree parent is the frontier vertex.
 struct CutOp {
+    static constexpr bool W = false, REDUCE = false, SPLIT = false;
     uint64_t *key;
     int32_t *next;
     int64_t *ncount;
     __device__ bool vtx(int32_t, int32_t &pay) const { pay = 0; return true; }
-    __device__ bool edge(bool valid, int32_t v, int32_t, int32_t x, int32_t) const {
-        bool cut = false;
-        if (valid) {
-            uint64_t k = key[x];
-            if (sssp_parent(k) == v) {
-                key[x] = sssp_pack(INF, -1);
-                cut = true;
-            }
-        }
-        return cut;
+    __device__ uint64_t peek(int32_t x) const { return key[x]; }
+    __device__ int attempt(bool valid, int32_t v, int32_t, int32_t x, int32_t, uint64_t p) const {
+        if (!valid || sssp_parent(p) != v) return 0;
+        key[x] = sssp_pack(INF, -1);
+        return 1;
     }
+    __device__ int select(bool, int32_t, int32_t, int32_t, int32_t, int a) const { return a; }
     __device__ SinkTarget sink() const { return SinkTarget{next, ncount}; }
 };
 
 // Decremental phase 2: pull over in-edges (reverse store); the frontier holds the
-// cut vertices, an edge (v <- x) offers dist[x] + w to v.
+// cut vertices, an edge (v <- x) offers dist[x] + w to v.  The offers of a row are
+// reduced in the wave: one atomic per row and 64 edges, where an atomic per edge
+// ran a row's edges one after the other.
 struct PullOp {
+    static constexpr bool W = true, REDUCE = true, SPLIT = false;
     uint64_t *key;
     __device__ bool vtx(int32_t, int32_t &pay) const { pay = 0; return true; }
-    __device__ bool edge(bool valid, int32_t v, int32_t, int32_t x, int32_t w) const {
-        if (!valid) return false;
-        int32_t dx = sssp_dist(__atomic_load_n(&key[x], __ATOMIC_RELAXED));
-        if (dx >= INF) return false;
-        atomicMin((unsigned long long *)&key[v], (unsigned long long)sssp_pack(dx + w, x));
-        return false;
+    __device__ uint64_t peek(int32_t x) const { return __atomic_load_n(&key[x], __ATOMIC_RELAXED); }
+    __device__ uint64_t cand(bool valid, int32_t, int32_t x, int32_t w, uint64_t p) const {
+        return valid && sssp_dist(p) < INF ? sssp_pack(sssp_dist(p) + w, x) : ~0ull;
+    }
+    __device__ void commit(int32_t v, uint64_t c) const {
+        atomicMin((unsigned long long *)&key[v], (unsigned long long)c);
     }
     __device__ SinkTarget sink() const { return SinkTarget{}; }
 };
@@ -342,7 +343,7 @@ static int sssp_push_nearfar(dg_graph *g, uint64_t *key, int64_t nf, int32_t del
             DG_TRY(next_stamp(g, &stv));
             DG_TRY(counters_clear(g));
             RelaxOp op{key, ws.stamp.p, stv, B, ws.dcnt + C_F1};
-            DG_TRY(launch_expand(s, with_tally(make_args(g, g->fwd, A, nnear), ws.dcnt + C_EDGES), op, 8192));
+            DG_TRY(launch_expand(s, with_tally(make_args(g, g->fwd, A, nnear), ws.dcnt + C_TALLY), op));
             hipLaunchKernelGGL(k_nf_split, dim3(512), dim3(WIDE_T), 0, s, ws.dcnt + C_F1, B, key, T, A,
                                ws.dcnt + C_F0, far + nfar, ws.dcnt + C_AUX1, ws.farflag.p, fst);
             DG_HIP(hipGetLastError());
@@ -392,7 +393,7 @@ static int sssp_push(dg_graph *g, uint64_t *key, int64_t nf, dg_batch_stats *st)
         DG_TRY(next_stamp(g, &stv));
         DG_TRY(counters_clear(g));
         RelaxOp op{key, ws.stamp.p, stv, N, ws.dcnt + C_F1};
-        DG_TRY(launch_expand(s, with_tally(make_args(g, g->fwd, F, nf), ws.dcnt + C_EDGES), op, 8192));
+        DG_TRY(launch_expand(s, with_tally(make_args(g, g->fwd, F, nf), ws.dcnt + C_TALLY), op));
         DG_TRY(counters_read(g));
         relaxed += nf;
         edges += ws.hcnt[C_EDGES];
@@ -423,14 +424,17 @@ __global__ void k_sssp_set_sources(const int32_t *src, int64_t ns, uint64_t *key
 constexpr int WL_MAX_DEPTH = 64;
 
 struct DepthOp {
+    static constexpr bool W = false, REDUCE = false, SPLIT = false;
     int32_t *stamp;
     int32_t st;
     int32_t *next;
     int64_t *ncount;
     __device__ bool vtx(int32_t, int32_t &pay) const { pay = 0; return true; }
-    __device__ bool edge(bool valid, int32_t, int32_t, int32_t x, int32_t) const {
-        return valid && stamp[x] != st && atomicExch(&stamp[x], st) != st;
+    __device__ int32_t peek(int32_t x) const { return stamp[x]; }
+    __device__ int attempt(bool valid, int32_t, int32_t, int32_t x, int32_t, int32_t p) const {
+        return valid && p != st && atomicExch(&stamp[x], st) != st;
     }
+    __device__ int select(bool, int32_t, int32_t, int32_t, int32_t, int a) const { return a; }
     __device__ SinkTarget sink() const { return SinkTarget{next, ncount}; }
 };
 
@@ -459,7 +463,7 @@ static int hop_depth_exceeds(dg_graph *g, const int32_t *srcs, int64_t ns, int l
     while (nf > 0 && level < limit) {
         DG_TRY(counters_clear(g));
         DepthOp op{ws.stamp.p, st, N, ws.dcnt + C_F1};
-        DG_TRY(launch_expand(s, make_args(g, g->fwd, F, nf), op, 8192));
+        DG_TRY(launch_expand(s, make_args(g, g->fwd, F, nf), op));
         DG_TRY(counters_read(g));
         nf = ws.hcnt[C_F1];
         std::swap(F, N);
@@ -544,14 +548,15 @@ enum {
     // count, which far buffer holds the pile, threshold T, smallest pile distance
     // (as INF - d), advance flag of the round, membership stamp of this batch
     R_NB, R_NF, R_NF2, R_FPAR, R_T, R_BEST, R_ADV, R_FST,
-    R_EDGES,  // adjacency entries the steps examined (the traversal tally)
-    R_END
+    R_EDGES,  // adjacency entries the steps examined (host copy: the sum of the tally slots)
+    R_END,
+    R_TALLY = 32, R_ALL = R_TALLY + TALLY_SLOTS * TALLY_STRIDE
 };  // slots of q->qcnt
 constexpr int CUT_LEVELS = 8, PUSH_ROUNDS = 16, NF_ROUNDS = 16;
-static_assert(R_END <= 32, "round counters must fit the pinned staging block");
+static_assert(R_END <= R_TALLY, "round counters end before the tally slots");
 static_assert((CUT_LEVELS % 2) == 0 && (PUSH_ROUNDS % 2) == 0 && (NF_ROUNDS % 2) == 0,
               "a continuation graph must end in the buffer it starts from");
-constexpr int HPIN_SLOTS = 32;
+constexpr int HPIN_SLOTS = R_ALL;
 
 // Next step: zero the output count and the heavy-chunk count, advance the stamp,
 // count the step if its input frontier is non-empty.
@@ -568,34 +573,32 @@ __global__ void k_rounds_init(int64_t *ctr) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         ctr[R_LIST] = ctr[0];  // the cut list starts with the pre-hook's seeds
         ctr[R_STEPS] = 0;
-        ctr[R_EDGES] = 0;
     }
+    if (blockIdx.x == 0 && threadIdx.x < TALLY_SLOTS) ctr[R_TALLY + threadIdx.x * TALLY_STRIDE] = 0;
 }
 
 // Cut walk that also appends every cut vertex to the cut list.
 struct CutListOp {
+    static constexpr bool W = false, REDUCE = false, SPLIT = false;
     uint64_t *key;
     int32_t *next;
     int64_t *ncount;
     int32_t *list;
     int64_t *lcount;
     __device__ bool vtx(int32_t, int32_t &pay) const { pay = 0; return true; }
-    __device__ bool edge(bool valid, int32_t v, int32_t, int32_t x, int32_t) const {
-        bool cut = false;
-        if (valid) {
-            uint64_t k = key[x];
-            if (sssp_parent(k) == v) {
-                key[x] = sssp_pack(INF, -1);
-                cut = true;
-            }
-        }
-        return cut;
+    __device__ uint64_t peek(int32_t x) const { return key[x]; }
+    __device__ int attempt(bool valid, int32_t v, int32_t, int32_t x, int32_t, uint64_t p) const {
+        if (!valid || sssp_parent(p) != v) return 0;
+        key[x] = sssp_pack(INF, -1);
+        return 1;
     }
+    __device__ int select(bool, int32_t, int32_t, int32_t, int32_t, int a) const { return a; }
     __device__ SinkTarget sink() const { return SinkTarget{next, ncount, list, lcount}; }
 };
 
 // RelaxOp with the round's stamp read from device memory.
 struct RelaxOpD {
+    static constexpr bool W = true, REDUCE = false, SPLIT = false;
     uint64_t *key;
     int32_t *stamp;
     const int64_t *stp;
@@ -606,19 +609,17 @@ struct RelaxOpD {
         pay = d;
         return d < INF;
     }
-    __device__ bool edge(bool valid, int32_t v, int32_t d, int32_t x, int32_t w) const {
-        bool push = false;
-        if (valid) {
-            uint64_t cand = sssp_pack(d + w, v);
-            if (cand < __atomic_load_n(&key[x], __ATOMIC_RELAXED)) {
-                uint64_t old = atomicMin((unsigned long long *)&key[x], (unsigned long long)cand);
-                if (cand < old && sssp_dist(cand) < sssp_dist(old)) {
-                    const int32_t st = (int32_t)*stp;
-                    push = atomicExch(&stamp[x], st) != st;
-                }
-            }
-        }
-        return push;
+    __device__ uint64_t peek(int32_t x) const { return __atomic_load_n(&key[x], __ATOMIC_RELAXED); }
+    __device__ uint64_t attempt(bool valid, int32_t v, int32_t d, int32_t x, int32_t w, uint64_t p) const {
+        const uint64_t cand = sssp_pack(d + w, v);
+        uint64_t old = 0;
+        if (valid && cand < p) old = atomicMin((unsigned long long *)&key[x], (unsigned long long)cand);
+        return old;
+    }
+    __device__ int select(bool, int32_t, int32_t d, int32_t x, int32_t w, uint64_t old) const {
+        if (d + w >= sssp_dist(old)) return 0;
+        const int32_t st = (int32_t)*stp;
+        return atomicExch(&stamp[x], st) != st;
     }
     __device__ SinkTarget sink() const { return SinkTarget{next, ncount}; }
 };
@@ -826,7 +827,7 @@ static int cut_level(dg_query *q, const int32_t *F, const int64_t *cf, int32_t *
     int64_t *ctr = q->qcnt.p;
     hipLaunchKernelGGL(k_round_prep, dim3(1), dim3(64), 0, g->stream, cn, g->ws.dcnt + C_HEAVY, ctr, nullptr);
     CutListOp op{q->key.p, N, cn, q->inval.p, ctr + R_LIST};
-    DG_TRY(launch_expand(g->stream, with_tally(dev_args(g, g->fwd, F, cf), ctr + R_EDGES), op, 1024));
+    DG_TRY(launch_expand(g->stream, with_tally(dev_args(g, g->fwd, F, cf), ctr + R_TALLY), op));
     return DG_OK;
 }
 
@@ -836,7 +837,7 @@ static int push_round(dg_query *q, const int32_t *F, const int64_t *cf, int32_t 
     int64_t *ctr = q->qcnt.p;
     hipLaunchKernelGGL(k_round_prep, dim3(1), dim3(64), 0, g->stream, cn, g->ws.dcnt + C_HEAVY, ctr, cf);
     RelaxOpD op{q->key.p, q->gstamp.p, ctr + R_STAMP, N, cn};
-    DG_TRY(launch_expand(g->stream, with_tally(dev_args(g, g->fwd, F, cf), ctr + R_EDGES), op, 1024));
+    DG_TRY(launch_expand(g->stream, with_tally(dev_args(g, g->fwd, F, cf), ctr + R_TALLY), op));
     return DG_OK;
 }
 
@@ -873,7 +874,7 @@ static int nf_round(dg_query *q, const int32_t *F, const int64_t *cf, int32_t *N
     const int32_t delta = g->cfg.sssp_delta;
     hipLaunchKernelGGL(k_nfd_step, dim3(1), dim3(64), 0, s, ctr, delta, cf, cn, ws.dcnt + C_HEAVY);
     RelaxOpD op{q->key.p, q->gstamp.p, ctr + R_STAMP, ws.nfout.p, ctr + R_NB};
-    DG_TRY(launch_expand(s, with_tally(dev_args(g, g->fwd, F, cf), ctr + R_EDGES), op, 1024));
+    DG_TRY(launch_expand(s, with_tally(dev_args(g, g->fwd, F, cf), ctr + R_TALLY), op));
     hipLaunchKernelGGL(k_nfd_split, dim3(64), dim3(WIDE_T), 0, s, ws.nfout.p, q->key.p, ctr, N, cn, ws.far0.p,
                        ws.far1.p, q->gfar.p);
     hipLaunchKernelGGL(k_nfd_min, dim3(16), dim3(WIDE_T), 0, s, ctr, cn, ws.far0.p, ws.far1.p, q->key.p);
@@ -894,8 +895,8 @@ static int rounds_push_enqueue(dg_query *q, bool first) {
     if (first) {
         // pull once at every cut vertex
         hipLaunchKernelGGL(k_round_prep, dim3(1), dim3(64), 0, s, nullptr, ws.dcnt + C_HEAVY, ctr, nullptr);
-        DG_TRY(launch_expand(s, with_tally(dev_args(g, *g->rev, q->inval.p, ctr + R_LIST), ctr + R_EDGES),
-                             PullOp{q->key.p}, 1024));
+        DG_TRY(launch_expand(s, with_tally(dev_args(g, *g->rev, q->inval.p, ctr + R_LIST), ctr + R_TALLY),
+                             PullOp{q->key.p}));
         // seeds: pulled cut vertices and improved heads of inserted arcs
         hipLaunchKernelGGL(k_round_prep, dim3(1), dim3(64), 0, s, ctr + R_PA, ws.dcnt + C_HEAVY, ctr, nullptr);
         hipLaunchKernelGGL(k_sssp_pulled_d, dim3(256), dim3(WIDE_T), 0, s, ctr + R_LIST, q->inval.p, q->key.p,
@@ -929,9 +930,11 @@ static int rounds_push_enqueue(dg_query *q, bool first) {
 
 static int rounds_read(dg_query *q, int64_t *h) {
     dg_graph *g = q->g;
-    DG_HIP(hipMemcpyAsync(q->hpin, q->qcnt.p, R_END * sizeof(int64_t), hipMemcpyDeviceToHost, g->stream));
+    DG_HIP(hipMemcpyAsync(q->hpin, q->qcnt.p, R_ALL * sizeof(int64_t), hipMemcpyDeviceToHost, g->stream));
     DG_HIP(wait_stream(g, g->stream));
     std::memcpy(h, q->hpin, R_END * sizeof(int64_t));
+    h[R_EDGES] = 0;
+    for (int j = 0; j < TALLY_SLOTS; ++j) h[R_EDGES] += q->hpin[R_TALLY + j * TALLY_STRIDE];
     return DG_OK;
 }
 
@@ -941,12 +944,12 @@ static int sssp_post_rounds(dg_query *q, int64_t ains, dg_batch_stats *st) {
     const bool nf = g->cfg.sssp_delta > 0;
     DG_TRY(ensure_frontiers(g));
     if (!q->hpin) DG_HIP(hipHostMalloc((void **)&q->hpin, HPIN_SLOTS * sizeof(int64_t), hipHostMallocDefault));
-    if (!q->gstamp.p || q->gstamp.cap < (size_t)g->n + 1 || q->qcnt.cap < (size_t)R_END) {
+    if (!q->gstamp.p || q->gstamp.cap < (size_t)g->n + 1 || q->qcnt.cap < (size_t)R_ALL) {
         // stamps and their counters start together (a stamp is never reused)
-        DG_TRY(q->qcnt.ensure(R_END, true, g->stream));
+        DG_TRY(q->qcnt.ensure(R_ALL, true, g->stream));
         DG_TRY(q->gstamp.ensure((size_t)g->n + 1));
         DG_TRY(fill_i32(q->gstamp.p, 0, g->n + 1, g->stream));
-        DG_TRY(fill_i64(q->qcnt.p, 0, R_END, g->stream));
+        DG_TRY(fill_i64(q->qcnt.p, 0, R_ALL, g->stream));
     }
     if (nf) {
         const size_t cap = (size_t)g->n + 1;
@@ -1062,8 +1065,7 @@ int sssp_post_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
     while (hi > lo) {
         DG_TRY(counters_clear(g));
         CutOp op{q->key.p, q->inval.p + hi, ws.dcnt + C_F1};
-        DG_TRY(launch_expand(s, with_tally(make_args(g, g->fwd, q->inval.p + lo, hi - lo), ws.dcnt + C_EDGES), op,
-                             8192));
+        DG_TRY(launch_expand(s, with_tally(make_args(g, g->fwd, q->inval.p + lo, hi - lo), ws.dcnt + C_TALLY), op));
         DG_TRY(counters_read(g));
         edges += ws.hcnt[C_EDGES];
         lo = hi;
@@ -1075,7 +1077,7 @@ int sssp_post_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
     DG_TRY(counters_clear(g));
     if (ncut > 0) {
         PullOp op{q->key.p};
-        DG_TRY(launch_expand(s, with_tally(make_args(g, *g->rev, q->inval.p, ncut), ws.dcnt + C_EDGES), op, 8192));
+        DG_TRY(launch_expand(s, with_tally(make_args(g, *g->rev, q->inval.p, ncut), ws.dcnt + C_TALLY), op));
     }
     // 3. inserted arcs relax their heads; 2+3 seed the push frontier
     int32_t stv;

@@ -384,14 +384,15 @@ __global__ void k_wl_seed_sources(WorkQ wq, const int32_t *src, int64_t ns, int3
 
 // PullOp of sssp.hip, reproduced here so both drivers can use it.
 struct WlPullOp {
+    static constexpr bool W = true, REDUCE = true, SPLIT = false;
     uint64_t *key;
     __device__ bool vtx(int32_t, int32_t &pay) const { pay = 0; return true; }
-    __device__ bool edge(bool valid, int32_t v, int32_t, int32_t x, int32_t w) const {
-        if (!valid) return false;
-        int32_t dx = sssp_dist(__atomic_load_n(&key[x], __ATOMIC_RELAXED));
-        if (dx >= INF) return false;
-        atomicMin((unsigned long long *)&key[v], (unsigned long long)sssp_pack(dx + w, x));
-        return false;
+    __device__ uint64_t peek(int32_t x) const { return __atomic_load_n(&key[x], __ATOMIC_RELAXED); }
+    __device__ uint64_t cand(bool valid, int32_t, int32_t x, int32_t w, uint64_t p) const {
+        return valid && sssp_dist(p) < INF ? sssp_pack(sssp_dist(p) + w, x) : ~0ull;
+    }
+    __device__ void commit(int32_t v, uint64_t c) const {
+        atomicMin((unsigned long long *)&key[v], (unsigned long long)c);
     }
     __device__ SinkTarget sink() const { return SinkTarget{}; }
 };
@@ -537,7 +538,7 @@ static int sssp_post_enqueue(dg_graph *g, uint64_t *key, const int32_t *seeds, c
         a.chunk = H;
         DG_TRY(counters_clear(g));
         WlPullOp op{key};
-        DG_TRY(launch_expand(s, a, op, 4096));
+        DG_TRY(launch_expand(s, a, op));
     }
     // 3. push from the pulled cut vertices and the improved heads of inserted arcs
     unsigned long long *listc = wq.ctr + WT_LIST;  // keep the cut count across the reset
