@@ -67,6 +67,32 @@ struct RelaxOp {
     __device__ SinkTarget sink() const { return SinkTarget{next, ncount}; }
 };
 
+// The same relaxation for the near-far schedule: an improved vertex goes to the next
+// near frontier when its new distance is below T (once per round, stamp st), else to
+// the far pile (once while it is there, stamp fst).  A vertex that first lands in
+// the pile and then drops below T joins both; its pile entry is stale by the time
+// the pile is split.
+struct RelaxNfOp {
+    static constexpr bool W = true, REDUCE = false, SPLIT = true;
+    RelaxOp r;
+    int32_t T;
+    int32_t *far;
+    int64_t *nfar;
+    int32_t *farflag;
+    int32_t fst;
+    __device__ bool vtx(int32_t v, int32_t &pay) const { return r.vtx(v, pay); }
+    __device__ uint64_t peek(int32_t x) const { return r.peek(x); }
+    __device__ uint64_t attempt(bool valid, int32_t v, int32_t d, int32_t x, int32_t w, uint64_t p) const {
+        return r.attempt(valid, v, d, x, w, p);
+    }
+    __device__ int select(bool, int32_t, int32_t d, int32_t x, int32_t w, uint64_t old) const {
+        if (d + w >= sssp_dist(old)) return 0;
+        if (d + w < T) return atomicExch(&r.stamp[x], r.st) != r.st ? 1 : 0;
+        return atomicExch(&farflag[x], fst) != fst ? 2 : 0;
+    }
+    __device__ SinkTarget sink() const { return SinkTarget{r.next, r.ncount, far, nfar}; }
+};
+
 // Decremental phase 1: cut children whose tree parent is the frontier vertex.
 struct CutOp {
     static constexpr bool W = false, REDUCE = false, SPLIT = false;
@@ -246,28 +272,6 @@ static ExpandArgs with_tally(ExpandArgs a, int64_t *tally) {
 // they are stale and leave the pile.  Only the order of relaxations changes; the
 // fixed point is the same.
 
-// Improved vertices (count on the device) -> near (dist < T) or the far pile.
-__global__ __launch_bounds__(WIDE_T) void k_nf_split(const int64_t *nn_p, const int32_t *N, const uint64_t *key,
-                                                     int32_t T, int32_t *near, int64_t *nnear, int32_t *far,
-                                                     int64_t *nfar, int32_t *farflag, int32_t fst) {
-    __shared__ BlockScratch sc;
-    const int64_t nn = *nn_p;
-    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < nn; base += gstride()) {
-        const int64_t i = base + threadIdx.x;
-        bool pn = false, pf = false;
-        int32_t v = 0;
-        if (i < nn) {
-            v = N[i];
-            pn = sssp_dist(key[v]) < T;
-            pf = !pn && atomicExch(&farflag[v], fst) != fst;
-        }
-        const int64_t sn = block_append<WIDE_T>(nnear, pn, sc);
-        if (pn) near[sn] = v;
-        const int64_t sf = block_append<WIDE_T>(nfar, pf, sc);
-        if (pf) far[sf] = v;
-    }
-}
-
 // Smallest distance >= T in the far pile, as INF - d through a max (0: none).
 __global__ __launch_bounds__(WIDE_T) void k_nf_min(int64_t nf, const int32_t *far, const uint64_t *key, int32_t T,
                                                    int64_t *out) {
@@ -342,16 +346,14 @@ static int sssp_push_nearfar(dg_graph *g, uint64_t *key, int64_t nf, int32_t del
             int32_t stv;
             DG_TRY(next_stamp(g, &stv));
             DG_TRY(counters_clear(g));
-            RelaxOp op{key, ws.stamp.p, stv, B, ws.dcnt + C_F1};
+            RelaxNfOp op{{key, ws.stamp.p, stv, B, ws.dcnt + C_F1}, T, far + nfar, ws.dcnt + C_AUX1, ws.farflag.p, fst};
             DG_TRY(launch_expand(s, with_tally(make_args(g, g->fwd, A, nnear), ws.dcnt + C_TALLY), op));
-            hipLaunchKernelGGL(k_nf_split, dim3(512), dim3(WIDE_T), 0, s, ws.dcnt + C_F1, B, key, T, A,
-                               ws.dcnt + C_F0, far + nfar, ws.dcnt + C_AUX1, ws.farflag.p, fst);
-            DG_HIP(hipGetLastError());
             DG_TRY(counters_read(g));
             relaxed += nnear;
             edges += ws.hcnt[C_EDGES];
-            nnear = ws.hcnt[C_F0];
+            nnear = ws.hcnt[C_F1];
             nfar += ws.hcnt[C_AUX1];
+            std::swap(A, B);
             ++steps;
         }
         if (nfar == 0) break;

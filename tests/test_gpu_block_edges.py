@@ -38,9 +38,9 @@ def test_batch_counts_and_distances(dg, k):
 
 
 # frontiers and rows around a wave's slots, the heavy degree and the wave-count rule
-@pytest.mark.parametrize("heavy", [0, 64])
+@pytest.mark.parametrize("heavy,delta", [(0, 0), (64, 0), (0, 30)])
 @pytest.mark.parametrize("k", [1, 7, 8, 9, 63, 65, 255, 257, 511, 513, 16383, 16385])
-def test_frontier_shapes(dg, k, heavy):
+def test_frontier_shapes(dg, k, heavy, delta):
     rng = np.random.default_rng(k)
     # 0 -> k middle vertices -> three of seven sinks each, and one sink back to all
     mid = np.arange(1, k + 1)
@@ -51,6 +51,7 @@ def test_frontier_shapes(dg, k, heavy):
     s, d, w = s.astype(np.int32), d.astype(np.int32), w.astype(np.int32)
     c = dg.Config()
     c.heavy_degree = heavy
+    c.sssp_delta = delta  # 30: near frontier and far pile
     G = dg.Graph(n, s, d, w, config=c)
     q = G.sssp_attach(0)
     assert np.array_equal(q.read()[0], oracle.sssp(n, s, d, w, 0))
