@@ -169,11 +169,12 @@ struct Work {
     // counters: device block + pinned host mirror
     int64_t *dcnt = nullptr;
     int64_t *hcnt = nullptr;
+    int64_t seq = 0;                      // blocks published so far (host copy of hcnt[H_SEQ])
     // a merge on the second stream keeps its own error counter and scan scratch
     int64_t *dcnt_m = nullptr;
     int64_t *hcnt_m = nullptr;
     SortWork sw_m;
-    hipEvent_t ev[16] = {};
+    std::vector<hipEvent_t> ev;  // phase timing marks of a batch, created as needed
     hipEvent_t step_ev[8] = {};  // completion of the last PageRank steps queued (ring)
 };
 
@@ -207,7 +208,8 @@ enum Counter {
 // different blocks run one after the other.
 constexpr int TALLY_SLOTS = 16, TALLY_STRIDE = 16;
 constexpr int C_ALL = C_TALLY + TALLY_SLOTS * TALLY_STRIDE;
-constexpr int H_PR = C_ALL, H_ALL = C_ALL + 16;
+// H_SEQ: the number of the last block the device wrote to host memory (publish).
+constexpr int H_PR = C_ALL, H_SEQ = H_PR + 16, H_ALL = H_SEQ + 16;
 
 }  // namespace dg
 
@@ -279,8 +281,15 @@ int graph_merge(dg_graph *g);
 // expect_op >= 0: every op must equal it (partially dynamic modes), else DG_EINVAL.
 int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, const int32_t *w,
                 const uint8_t *op, bool dev, dg_batch_stats *st, int expect_op = -1);
+// The host copy of the counters, once the work queued on g->stream is done; the
+// device's are zero after it (but C_MAXROW and C_SORT_ERR).  Every step that counts
+// starts from zero, so counters_clear is only needed at entries that cannot know
+// whether an earlier call ended in an error.
 int counters_read(dg_graph *g);
 int counters_clear(dg_graph *g);
+// n <= 512 words of device memory to dst (pinned host memory), in stream order, and
+// the wait for them.
+int publish(dg_graph *g, const void *src, int n, void *dst);
 int ws_init(dg_graph *g);
 void ws_free(dg_graph *g);
 void dir_free(Dir &d);

@@ -88,6 +88,68 @@ __global__ __launch_bounds__(C_ALL) void k_counters_clear(int64_t *cnt) {
     if (i != C_MAXROW && i != C_SORT_ERR) cnt[i] = 0;
 }
 
+// ---- results of a step on the host -----------------------------------------------------
+// A step's counts reach the host by a one-wave kernel that stores them into pinned,
+// coherent host memory and then a sequence number the host polls.  A blit copy and a
+// stream synchronisation in its place cost about 25 us a step (and the next step a
+// launch to clear the counters), against about 10 us; a 4096^2 grid batch has 250 steps.
+
+__device__ __forceinline__ void publish_seq(int64_t *host_seq, int64_t seq) {
+    __threadfence_system();  // the wave's stores before the number
+    if (lane_id() == 0) __hip_atomic_store(host_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Counters and the sum of the tally slots to the host, then zero for the next step.
+__global__ __launch_bounds__(WAVE) void k_counters_publish(int64_t *cnt, int64_t *host, int64_t *host_seq, int64_t seq) {
+    static_assert(C_COUNT <= WAVE && TALLY_SLOTS <= WAVE, "one wave");
+    const int l = lane_id();
+    int64_t tally = l < TALLY_SLOTS ? cnt[C_TALLY + l * TALLY_STRIDE] : 0;
+    if (l < TALLY_SLOTS) cnt[C_TALLY + l * TALLY_STRIDE] = 0;
+    tally = wave_sum(tally);
+    if (l < C_COUNT) {
+        host[l] = l == C_EDGES ? tally : cnt[l];
+        if (l != C_MAXROW && l != C_SORT_ERR) cnt[l] = 0;
+    }
+    publish_seq(host_seq, seq);
+}
+
+__global__ __launch_bounds__(WAVE) void k_publish(const int64_t *src, int n, int64_t *host, int64_t *host_seq,
+                                                  int64_t seq) {
+    for (int i = lane_id(); i < n; i += WAVE) host[i] = src[i];
+    publish_seq(host_seq, seq);
+}
+
+// Until block g->ws.seq has arrived.  Polls for about 0.1 ms (queuing PageRank steps
+// between polls while SSSP runs beside them), then blocks; a stream that ends
+// without the number has failed.
+static int publish_wait(dg_graph *g) {
+    const int64_t *f = g->ws.hcnt + H_SEQ;
+    constexpr int SPINS = 4096, QUERY = 1024;
+    for (int spin = 1;; ++spin) {
+        if (__atomic_load_n(f, __ATOMIC_ACQUIRE) == g->ws.seq) return DG_OK;
+        hipError_t e = hipErrorNotReady;
+        if (g->pump) {
+            (*g->pump)();
+            if (spin % QUERY == 0) e = hipStreamQuery(g->stream);
+        } else if (spin < SPINS) {
+            __builtin_ia32_pause();
+        } else {
+            e = hipStreamSynchronize(g->stream);
+        }
+        if (e == hipErrorNotReady) continue;
+        DG_HIP(e);
+        if (__atomic_load_n(f, __ATOMIC_ACQUIRE) == g->ws.seq) return DG_OK;
+        return set_error(DG_EDEVICE, "a step's counts did not reach the host");
+    }
+}
+
+int publish(dg_graph *g, const void *src, int n, void *dst) {
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(WAVE), 0, g->stream, static_cast<const int64_t *>(src), n,
+                       static_cast<int64_t *>(dst), g->ws.hcnt + H_SEQ, ++g->ws.seq);
+    DG_HIP(hipGetLastError());
+    return publish_wait(g);
+}
+
 int counters_clear(dg_graph *g) {
     hipLaunchKernelGGL(k_counters_clear, dim3(1), dim3(C_ALL), 0, g->stream, g->ws.dcnt);
     DG_HIP(hipGetLastError());
@@ -95,11 +157,10 @@ int counters_clear(dg_graph *g) {
 }
 
 int counters_read(dg_graph *g) {
-    DG_HIP(hipMemcpyAsync(g->ws.hcnt, g->ws.dcnt, sizeof(int64_t) * C_ALL, hipMemcpyDeviceToHost,
-                          g->stream));
-    DG_HIP(wait_stream(g, g->stream));
-    g->ws.hcnt[C_EDGES] = 0;
-    for (int j = 0; j < TALLY_SLOTS; ++j) g->ws.hcnt[C_EDGES] += g->ws.hcnt[C_TALLY + j * TALLY_STRIDE];
+    hipLaunchKernelGGL(k_counters_publish, dim3(1), dim3(WAVE), 0, g->stream, g->ws.dcnt, g->ws.hcnt,
+                       g->ws.hcnt + H_SEQ, ++g->ws.seq);
+    DG_HIP(hipGetLastError());
+    DG_TRY(publish_wait(g));
     if (g->ws.hcnt[C_SORT_ERR]) return set_error(DG_EDEVICE, "sort or scan look-back did not finish (internal error)");
     return DG_OK;
 }
@@ -107,11 +168,11 @@ int counters_read(dg_graph *g) {
 int ws_init(dg_graph *g) {
     g->ws.dcnt = static_cast<int64_t *>(dmalloc(sizeof(int64_t) * C_ALL));
     if (!g->ws.dcnt) return set_error(DG_ENOMEM, "counter allocation failed");
-    DG_HIP(hipHostMalloc((void **)&g->ws.hcnt, sizeof(int64_t) * H_ALL, hipHostMallocDefault));
+    DG_HIP(hipHostMalloc((void **)&g->ws.hcnt, sizeof(int64_t) * H_ALL, hipHostMallocMapped | hipHostMallocCoherent));
+    std::memset(g->ws.hcnt, 0, sizeof(int64_t) * H_ALL);
     g->ws.dcnt_m = static_cast<int64_t *>(dmalloc(sizeof(int64_t) * C_COUNT));
     if (!g->ws.dcnt_m) return set_error(DG_ENOMEM, "counter allocation failed");
     DG_HIP(hipHostMalloc((void **)&g->ws.hcnt_m, sizeof(int64_t) * C_COUNT, hipHostMallocDefault));
-    for (auto &e : g->ws.ev) DG_HIP(hipEventCreate(&e));
     DG_TRY(fill_i64(g->ws.dcnt_m, 0, C_COUNT, g->stream));
     return fill_i64(g->ws.dcnt, 0, C_ALL, g->stream);
 }
@@ -153,8 +214,8 @@ void ws_free(dg_graph *g) {
     if (g->ev_join) (void)hipEventDestroy(g->ev_join);
     g->aux = nullptr;
     g->ev_fork = g->ev_join = nullptr;
-    for (auto &e : w.ev)
-        if (e) (void)hipEventDestroy(e);
+    for (auto &e : w.ev) (void)hipEventDestroy(e);
+    w.ev.clear();
     for (auto &e : w.step_ev)
         if (e) (void)hipEventDestroy(e);
     w.dcnt = nullptr;
@@ -1380,7 +1441,6 @@ static int fill_vacancies(dg_graph *g, Dir &d, const uint64_t *nkey, const int32
     DG_TRY(ws.vw.ensure((size_t)nk + 1));
     int64_t *slot = ws.vslot.p, *todiff = ws.vslot.p + (nk + 1);
     DG_TRY(ws.vpos.ensure((size_t)nk + 1));
-    DG_TRY(counters_clear(g));
     hipLaunchKernelGGL(k_vacancy_claim, dim3(grid_for(nk + 1)), dim3(256), 0, s, nk, nkey, d.keybits, d.off.p,
                        d.col.p, slot, todiff);
     hipLaunchKernelGGL(k_vacancy_fill, dim3(grid_wide(nk)), dim3(WIDE_T), 0, s, nk, nkey, nw, d.keybits, slot,
@@ -1399,21 +1459,46 @@ static int fill_vacancies(dg_graph *g, Dir &d, const uint64_t *nkey, const int32
     return DG_OK;
 }
 
-// Wrappers that time a phase with HIP events on the graph's stream.
-struct PhaseTimer {
+// Phase times of a batch from HIP events on the stream a phase runs on.  The marks
+// are only recorded during the batch and read once its last one is done.
+struct PhaseLog {
     dg_graph *g;
-    int a, b;
+    size_t used = 0;
+    struct Span {
+        size_t a, b;
+        float *acc;
+    };
+    std::vector<Span> spans;
+    size_t mark(hipStream_t s) {
+        std::vector<hipEvent_t> &ev = g->ws.ev;
+        if (used == ev.size()) {
+            hipEvent_t e = nullptr;
+            if (hipEventCreate(&e) != hipSuccess) return SIZE_MAX;
+            ev.push_back(e);
+        }
+        (void)hipEventRecord(ev[used], s);
+        return used++;
+    }
+    // The batch ends: wait for the last mark and add up the spans.
+    int finish() {
+        if (spans.empty()) return DG_OK;
+        const size_t last = spans.back().b;
+        DG_HIP(last == SIZE_MAX ? hipStreamSynchronize(g->stream) : hipEventSynchronize(g->ws.ev[last]));
+        for (const Span &p : spans) {
+            float ms = 0.f;
+            if (p.a != SIZE_MAX && p.b != SIZE_MAX &&
+                hipEventElapsedTime(&ms, g->ws.ev[p.a], g->ws.ev[p.b]) == hipSuccess)
+                *p.acc += ms;
+        }
+        return DG_OK;
+    }
+};
+struct PhaseTimer {
+    PhaseLog &log;
     float *acc;
-    PhaseTimer(dg_graph *g_, int slot, float *acc_) : g(g_), a(2 * slot), b(2 * slot + 1), acc(acc_) {
-        (void)hipEventRecord(g->ws.ev[a], g->stream);
-    }
-    void stop() {
-        (void)hipEventRecord(g->ws.ev[b], g->stream);
-        (void)hipEventSynchronize(g->ws.ev[b]);
-        float ms = 0.f;
-        (void)hipEventElapsedTime(&ms, g->ws.ev[a], g->ws.ev[b]);
-        if (acc) *acc += ms;
-    }
+    size_t a;
+    PhaseTimer(PhaseLog &l, float *acc_) : log(l), acc(acc_), a(l.mark(l.g->stream)) {}
+    void stop() { log.spans.push_back({a, log.mark(log.g->stream), acc}); }
 };
 
 int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, const int32_t *w,
@@ -1426,8 +1511,9 @@ int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, 
     const int B = F.keybits;
     dg_batch_stats dummy{};
     if (!st) st = &dummy;
-    PhaseTimer t_all(g, 7, &st->t_total_ms);
-    PhaseTimer t_val(g, 0, &st->t_validate_ms);
+    PhaseLog plog{g};
+    PhaseTimer t_all(plog, &st->t_total_ms);
+    PhaseTimer t_val(plog, &st->t_validate_ms);
 
     // ---- stage the chunk on the device
     const int32_t *ds = src, *dd = dst, *dw = w;
@@ -1457,6 +1543,7 @@ int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, 
     if (ws.hcnt[C_ERR]) {
         t_val.stop();
         t_all.stop();
+        DG_TRY(plog.finish());
         return set_error(DG_EINVAL, "batch holds a self-loop, an id outside [0,n), an op other than 0/1 (or "
                                     "other than the partially dynamic mode's) or a weight outside [1,2^30)");
     }
@@ -1503,11 +1590,11 @@ int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, 
     // ---- pre-hooks on the old graph (deleted arcs still present, MARKed)
     for (dg_query *q : g->queries) {
         if (q->kind == Q_SSSP) {
-            PhaseTimer t(g, 2, &st->t_sssp_ms);
+            PhaseTimer t(plog, &st->t_sssp_ms);
             DG_TRY(sssp_pre_delete(q, adel));
             t.stop();
         } else if (q->kind == Q_TC && tcdel > 0) {
-            PhaseTimer t(g, 4, &st->t_tc_ms);
+            PhaseTimer t(plog, &st->t_tc_ms);
             uint64_t sum6 = 0;
             int64_t walked = 0;
             DG_TRY(tc_delta(g, ws.tcu.p, ws.tcv.p, tcdel, &sum6, &walked));
@@ -1521,10 +1608,9 @@ int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, 
     // ---- commit deletions, revive slots, rebuild the diff (both directions)
     // The commits count into slots of their own (KILL_F, KILL_R: C_AUX2 and C_AUX3
     // relative to them), so one read after the revivals serves both passes.
-    PhaseTimer t_upd(g, 1, &st->t_update_ms);
+    PhaseTimer t_upd(plog, &st->t_update_ms);
     constexpr int KILL_F = 16, KILL_R = 18;  // counts at 32..35, clear of every other use
     static_assert(C_AUX3 + KILL_R < C_SORT_ERR && C_AUX2 + KILL_F > C_EDGES, "kill counts have free slots");
-    DG_TRY(counters_clear(g));
     if (adel > 0) {
         hipLaunchKernelGGL(k_commit_deletes, dim3(grid_wide(adel)), dim3(WIDE_T), 0, s, adel, ws.adu.p,
                            ws.adpos.p, F.col.p, F.dcol.p, F.deg.p, F.ttomb.p, ws.dcnt + KILL_F);
@@ -1607,13 +1693,13 @@ int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, 
                 merge_r = !und && merge_needed(g->rev_own);
                 DG_HIP(hipEventRecord(g->ev_fork, s));
                 DG_HIP(hipStreamWaitEvent(g->aux, g->ev_fork, 0));
-                DG_HIP(hipEventRecord(ws.ev[6], g->aux));
+                const size_t m0 = plog.mark(g->aux);
                 if (merge_f) DG_TRY(merge_dir_start(g, F, g->m_live, true));
                 if (merge_r) DG_TRY(merge_dir_start(g, g->rev_own, g->m_live, true));
-                DG_HIP(hipEventRecord(ws.ev[7], g->aux));
+                plog.spans.push_back({m0, plog.mark(g->aux), &st->t_merge_ms});
                 merge_pending = true;
             } else {
-                PhaseTimer t(g, 3, &st->t_merge_ms);
+                PhaseTimer t(plog, &st->t_merge_ms);
                 DG_TRY(merge_dir(g, F, g->m_live));
                 if (!und) DG_TRY(merge_dir(g, g->rev_own, g->m_live));
                 t.stop();
@@ -1648,7 +1734,7 @@ int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, 
             int rc = DG_OK;
             for (dg_query *q : g->queries) {
                 if (q->kind != Q_SSSP) continue;
-                PhaseTimer t(g, 2, &st->t_sssp_ms);
+                PhaseTimer t(plog, &st->t_sssp_ms);
                 rc = sssp_post_update(q, adel, ains, st);
                 t.stop();
                 if (rc != DG_OK) break;
@@ -1659,22 +1745,22 @@ int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, 
             if (rc == DG_OK) DG_HIP(hipStreamWaitEvent(s, g->ev_join, 0));
             return rc;
         };
-        PhaseTimer t(g, 5, &st->t_pr_ms);
+        PhaseTimer t(plog, &st->t_pr_ms);
         DG_TRY(pr_post_update(prq, adel, ains, st, &side));
         t.stop();
     }
     for (dg_query *q : g->queries) {
         if (prq && has_sssp && g->cfg.sssp_persistent != 1 && (q == prq || q->kind == Q_SSSP)) continue;
         if (q->kind == Q_SSSP) {
-            PhaseTimer t(g, 2, &st->t_sssp_ms);
+            PhaseTimer t(plog, &st->t_sssp_ms);
             DG_TRY(sssp_post_update(q, adel, ains, st));
             t.stop();
         } else if (q->kind == Q_PR) {
-            PhaseTimer t(g, 5, &st->t_pr_ms);
+            PhaseTimer t(plog, &st->t_pr_ms);
             DG_TRY(pr_post_update(q, adel, ains, st));
             t.stop();
         } else if (q->kind == Q_TC && tcins > 0) {
-            PhaseTimer t(g, 4, &st->t_tc_ms);
+            PhaseTimer t(plog, &st->t_tc_ms);
             uint64_t sum6 = 0;
             int64_t walked = 0;
             DG_TRY(tc_delta(g, ws.tcu.p + tcdel, ws.tcv.p + tcdel, tcins, &sum6, &walked));
@@ -1687,8 +1773,6 @@ int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, 
     // ---- a merge beside the SSSP updates: check it, then swap in the merged arrays
     if (merge_pending) {
         DG_TRY(merge_side_check(g));
-        float ms = 0.f;
-        if (hipEventElapsedTime(&ms, ws.ev[6], ws.ev[7]) == hipSuccess) st->t_merge_ms += ms;
         if (merge_f) DG_TRY(merge_dir_commit(g, F, g->m_live));
         if (merge_r) DG_TRY(merge_dir_commit(g, g->rev_own, g->m_live));
     }
@@ -1704,6 +1788,7 @@ int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, 
         DG_HIP(hipGetLastError());
     }
     t_all.stop();
+    DG_TRY(plog.finish());
     const int64_t div = und ? 2 : 1;
     st->updates += k;
     st->deleted += adel / div;

@@ -999,9 +999,7 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
         for (; queued < grp; ++queued) DG_TRY(launch_step());
         launched += grp;
         double hp[11];
-        // the host slots after the counters: a counter read of a side stream leaves them alone
-        DG_HIP(hipMemcpyAsync(ws.hcnt + H_PR, prs, sizeof(hp), hipMemcpyDeviceToHost, s));
-        DG_HIP(hipStreamSynchronize(s));
+        DG_TRY(publish(g, prs, 11, ws.hcnt + H_PR));
         std::memcpy(hp, ws.hcnt + H_PR, sizeof(hp));
         const int32_t total = (int32_t)hp[4];
         ws.pr_moves = (int32_t)hp[10];
@@ -1018,6 +1016,7 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
     }
     if (na == 0) *conv = 1;
     *iters = it;
+    if (!tiles) DG_TRY(counters_clear(g));  // the last step's queue counters
     // whole-graph steps alternate the buffers: step k wrote xn if k is odd
     x = x_home;
     xn = xn_home;
@@ -1305,8 +1304,7 @@ static int pr_mass(dg_query *q, double *S) {
                        1.0, 0.0, 1, 0, ws.prs.p, ws.prs.p + 5);
     DG_HIP(hipGetLastError());
     // prs[0] here holds the plain sum (first partial of each pair)
-    DG_HIP(hipMemcpyAsync(ws.hcnt + H_PR, ws.prs.p, sizeof(double), hipMemcpyDeviceToHost, s));
-    DG_HIP(hipStreamSynchronize(s));
+    DG_TRY(publish(g, ws.prs.p, 1, ws.hcnt + H_PR));
     std::memcpy(S, ws.hcnt + H_PR, sizeof(double));
     return DG_OK;
 }
@@ -1373,7 +1371,6 @@ static int pr_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
     if (!global) {
         // seeds: heads of changed arcs, then all out-neighbours of the tails
         DG_TRY(next_stamp(g, &st_a));
-        DG_TRY(counters_clear(g));
         if (adel > 0)
             hipLaunchKernelGGL(k_mark_list, dim3(grid_wide(adel)), dim3(WIDE_T), 0, s, adel, ws.adv.p,
                                ws.stamp.p, st_a, Alist, ws.dcnt + C_F0);
@@ -1383,7 +1380,6 @@ static int pr_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
         DG_HIP(hipGetLastError());
         DG_TRY(counters_read(g));
         na = ws.hcnt[C_F0];
-        DG_TRY(counters_clear(g));
         a.F = S;
         a.nf = ns;
         ReachOp op{ws.stamp.p, st_a, Alist + na, ws.dcnt + C_F1};
@@ -1403,7 +1399,6 @@ static int pr_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
     // global form then runs over every vertex anyway.
     int64_t lo = 0, hi = na;
     while (!global && hi > lo) {
-        DG_TRY(counters_clear(g));
         a.F = Alist + lo;
         a.nf = hi - lo;
         ReachOp op{ws.stamp.p, st_a, Alist + hi, ws.dcnt + C_F1};
@@ -1423,7 +1418,6 @@ static int pr_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
                            flags);
         DG_TRY(scan_excl(g, flags, pos, g->n + 1));
         hipLaunchKernelGGL(k_compact_flags, dim3(grid_for(g->n)), dim3(256), 0, s, g->n, flags, pos, Alist);
-        DG_TRY(counters_clear(g));
         hipLaunchKernelGGL(k_sum_degrees, dim3(grid_wide(na)), dim3(WIDE_T), 0, s, Alist, na, (const int64_t *)nullptr,
                            g->rev->off.p, g->rev->doff.p, ws.dcnt + C_AUX0);
         DG_HIP(hipGetLastError());

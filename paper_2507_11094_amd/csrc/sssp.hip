@@ -332,7 +332,6 @@ static int sssp_push_nearfar(dg_graph *g, uint64_t *key, int64_t nf, int32_t del
     const int32_t fst = ++ws.far_ctr;
     int32_t *A = ws.f0.p, *B = ws.f1.p, *far = ws.far0.p, *far2 = ws.far1.p;
     // first threshold: nearest seed + delta (every seed is relaxed in the first round)
-    DG_TRY(counters_clear(g));
     hipLaunchKernelGGL(k_nf_seed_min, dim3(grid_wide(nf)), dim3(WIDE_T), 0, s, nf, A, key, ws.dcnt + C_AUX2);
     DG_HIP(hipGetLastError());
     DG_TRY(counters_read(g));
@@ -345,7 +344,6 @@ static int sssp_push_nearfar(dg_graph *g, uint64_t *key, int64_t nf, int32_t del
         while (nnear > 0) {
             int32_t stv;
             DG_TRY(next_stamp(g, &stv));
-            DG_TRY(counters_clear(g));
             RelaxNfOp op{{key, ws.stamp.p, stv, B, ws.dcnt + C_F1}, T, far + nfar, ws.dcnt + C_AUX1, ws.farflag.p, fst};
             DG_TRY(launch_expand(s, with_tally(make_args(g, g->fwd, A, nnear), ws.dcnt + C_TALLY), op));
             DG_TRY(counters_read(g));
@@ -357,13 +355,11 @@ static int sssp_push_nearfar(dg_graph *g, uint64_t *key, int64_t nf, int32_t del
             ++steps;
         }
         if (nfar == 0) break;
-        DG_TRY(counters_clear(g));
         hipLaunchKernelGGL(k_nf_min, dim3(grid_wide(nfar)), dim3(WIDE_T), 0, s, nfar, far, key, T, ws.dcnt + C_AUX2);
         DG_HIP(hipGetLastError());
         DG_TRY(counters_read(g));
         const int64_t best = ws.hcnt[C_AUX2];
         const int32_t T1 = best == 0 ? INF : (int32_t)std::min<int64_t>((int64_t)(INF - best) + delta, INF);
-        DG_TRY(counters_clear(g));
         hipLaunchKernelGGL(k_nf_refill, dim3(grid_wide(nfar)), dim3(WIDE_T), 0, s, nfar, far, key, T, T1, A,
                            ws.dcnt + C_F0, far2, ws.dcnt + C_AUX1, ws.farflag.p);
         DG_HIP(hipGetLastError());
@@ -393,7 +389,6 @@ static int sssp_push(dg_graph *g, uint64_t *key, int64_t nf, dg_batch_stats *st)
     while (nf > 0) {
         int32_t stv;
         DG_TRY(next_stamp(g, &stv));
-        DG_TRY(counters_clear(g));
         RelaxOp op{key, ws.stamp.p, stv, N, ws.dcnt + C_F1};
         DG_TRY(launch_expand(s, with_tally(make_args(g, g->fwd, F, nf), ws.dcnt + C_TALLY), op));
         DG_TRY(counters_read(g));
@@ -463,7 +458,6 @@ static int hop_depth_exceeds(dg_graph *g, const int32_t *srcs, int64_t ns, int l
     int64_t nf = ns;
     int level = 0;
     while (nf > 0 && level < limit) {
-        DG_TRY(counters_clear(g));
         DepthOp op{ws.stamp.p, st, N, ws.dcnt + C_F1};
         DG_TRY(launch_expand(s, make_args(g, g->fwd, F, nf), op));
         DG_TRY(counters_read(g));
@@ -480,6 +474,7 @@ static int hop_depth_exceeds(dg_graph *g, const int32_t *srcs, int64_t ns, int l
 int sssp_static_multi(dg_graph *g, uint64_t *key, const int32_t *srcs, int64_t ns, dg_batch_stats *st) {
     hipStream_t s = g->stream;
     DG_TRY(ensure_frontiers(g));
+    DG_TRY(counters_clear(g));
     hipLaunchKernelGGL(k_sssp_init, dim3(grid_for(g->n)), dim3(256), 0, s, g->n, key, -1);
     hipLaunchKernelGGL(k_sssp_set_sources, dim3(grid_for(ns)), dim3(256), 0, s, srcs, ns, key);
     DG_HIP(hipGetLastError());
@@ -522,7 +517,6 @@ int sssp_pre_delete(dg_query *q, int64_t adel) {
     dg_graph *g = q->g;
     q->nseeds = 0;
     if (adel <= 0) return DG_OK;
-    DG_TRY(counters_clear(g));
     hipLaunchKernelGGL(k_sssp_on_delete, dim3(grid_wide(adel)), dim3(WIDE_T), 0, g->stream, adel,
                        g->ws.adu.p, g->ws.adv.p, q->key.p, q->inval.p, g->ws.dcnt + C_AUX0);
     DG_HIP(hipGetLastError());
@@ -932,8 +926,7 @@ static int rounds_push_enqueue(dg_query *q, bool first) {
 
 static int rounds_read(dg_query *q, int64_t *h) {
     dg_graph *g = q->g;
-    DG_HIP(hipMemcpyAsync(q->hpin, q->qcnt.p, R_ALL * sizeof(int64_t), hipMemcpyDeviceToHost, g->stream));
-    DG_HIP(wait_stream(g, g->stream));
+    DG_TRY(publish(g, q->qcnt.p, R_ALL, q->hpin));
     std::memcpy(h, q->hpin, R_END * sizeof(int64_t));
     h[R_EDGES] = 0;
     for (int j = 0; j < TALLY_SLOTS; ++j) h[R_EDGES] += q->hpin[R_TALLY + j * TALLY_STRIDE];
@@ -945,7 +938,7 @@ static int sssp_post_rounds(dg_query *q, int64_t ains, dg_batch_stats *st) {
     Work &ws = g->ws;
     const bool nf = g->cfg.sssp_delta > 0;
     DG_TRY(ensure_frontiers(g));
-    if (!q->hpin) DG_HIP(hipHostMalloc((void **)&q->hpin, HPIN_SLOTS * sizeof(int64_t), hipHostMallocDefault));
+    if (!q->hpin) DG_HIP(hipHostMalloc((void **)&q->hpin, HPIN_SLOTS * sizeof(int64_t), hipHostMallocMapped | hipHostMallocCoherent));
     if (!q->gstamp.p || q->gstamp.cap < (size_t)g->n + 1 || q->qcnt.cap < (size_t)R_ALL) {
         // stamps and their counters start together (a stamp is never reused)
         DG_TRY(q->qcnt.ensure(R_ALL, true, g->stream));
@@ -1023,7 +1016,7 @@ static int sssp_post_rounds(dg_query *q, int64_t ains, dg_batch_stats *st) {
         st->sssp_steps += (int32_t)h[R_STEPS];
         st->edges_traversed += h[R_EDGES];
     }
-    return DG_OK;
+    return counters_clear(g);  // the rounds leave the heavy-chunk count set
 }
 
 int sssp_post_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st) {
@@ -1043,7 +1036,7 @@ int sssp_post_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
     if (g->cfg.sssp_persistent == 1) {
         // the same four steps on device work queues, without host round trips
         DG_TRY(q->qcnt.ensure(4));
-        if (!q->hpin) DG_HIP(hipHostMalloc((void **)&q->hpin, HPIN_SLOTS * sizeof(int64_t), hipHostMallocDefault));
+        if (!q->hpin) DG_HIP(hipHostMalloc((void **)&q->hpin, HPIN_SLOTS * sizeof(int64_t), hipHostMallocMapped | hipHostMallocCoherent));
         q->hpin[0] = q->nseeds;
         q->hpin[1] = ains;
         DG_HIP(hipMemcpyAsync(q->qcnt.p, q->hpin, 2 * sizeof(int64_t), hipMemcpyHostToDevice, s));
@@ -1059,13 +1052,12 @@ int sssp_post_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
             st->sssp_steps += 1;
             st->edges_traversed += edges;
         }
-        return DG_OK;
+        return counters_clear(g);  // the pull leaves the heavy-chunk count set
     }
     // 1. cut the subtrees below the seeds; q->inval collects every cut vertex
     int64_t ncut = q->nseeds;
     int64_t lo = 0, hi = ncut, edges = 0;
     while (hi > lo) {
-        DG_TRY(counters_clear(g));
         CutOp op{q->key.p, q->inval.p + hi, ws.dcnt + C_F1};
         DG_TRY(launch_expand(s, with_tally(make_args(g, g->fwd, q->inval.p + lo, hi - lo), ws.dcnt + C_TALLY), op));
         DG_TRY(counters_read(g));
@@ -1076,7 +1068,6 @@ int sssp_post_update(dg_query *q, int64_t adel, int64_t ains, dg_batch_stats *st
     ncut = hi;
     if (st) st->sssp_invalidated += ncut;
     // 2. one pull per cut vertex over its live in-edges
-    DG_TRY(counters_clear(g));
     if (ncut > 0) {
         PullOp op{q->key.p};
         DG_TRY(launch_expand(s, with_tally(make_args(g, *g->rev, q->inval.p, ncut), ws.dcnt + C_TALLY), op));

@@ -237,7 +237,6 @@ int tc_delta(dg_graph *g, const int32_t *eu, const int32_t *ev, int64_t ne, uint
     if (ne <= 0) return DG_OK;
     hipStream_t s = g->stream;
     Dir &F = g->fwd;
-    DG_TRY(counters_clear(g));
     // four waves per block; 16,384 blocks measured faster than a resident-size grid
     int64_t blocks = std::min<int64_t>((ne + 3) / 4, 16384);
     DG_TRY(g->ws.bpart.ensure(3 * (size_t)blocks + 8));
