@@ -5,7 +5,10 @@
 #include <atomic>
 #include <cstdarg>
 #include <cstring>
+#include <map>
 #include <mutex>
+#include <unordered_map>
+#include <vector>
 
 #include "dg_internal.h"
 
@@ -25,21 +28,162 @@ int set_error(int code, const char *fmt, ...) {
     return code;
 }
 
+// ---- device memory kept between objects ------------------------------------------------
+// hipMalloc and hipFree map and unmap pages and hipFree waits for the device: a graph of
+// 1M vertices and 16M arcs spent 6 of 14.5 ms per load in them, one of 262k vertices and 4M
+// edges 9 of 13.  So memory that a destroyed graph or query, or a finished build, gives
+// up goes to a pool, from which dmalloc serves blocks of about the same size.  Only
+// memory that no queued work uses enters it (IdleFrees: the owner has waited for its
+// streams); every other free still is a hipFree.  The pool holds at most POOL_MAX bytes
+// per process (oldest blocks leave first) and is emptied when an allocation fails and
+// by dg_set_allocator; a caller's allocator bypasses it.  It knows blocks by their
+// address only while they are in use, and serves any thread and stream.
+constexpr size_t POOL_MAX = (size_t)4 << 30;
+
+namespace {
+struct Pool {
+    struct Block {
+        void *p;
+        size_t bytes;
+        int dev;
+        uint64_t age;
+    };
+    std::mutex mu;
+    std::multimap<size_t, Block> idle;                             // by size
+    std::unordered_map<void *, std::pair<size_t, int>> allocated;  // of blocks in use
+    size_t held = 0;
+    uint64_t clock = 0;
+
+    // Sizes step by an eighth of their power of two, so that blocks of about the same
+    // size are of the same size.
+    static size_t round(size_t n) {
+        size_t g = 256;
+        while (g * 16 <= n) g *= 2;
+        return (n + g - 1) / g * g;
+    }
+    void *take(size_t bytes, int dev) {
+        std::lock_guard<std::mutex> l(mu);
+        for (auto it = idle.lower_bound(bytes); it != idle.end() && it->first <= bytes + bytes / 4; ++it) {
+            if (it->second.dev != dev) continue;
+            void *p = it->second.p;
+            allocated[p] = {it->first, dev};
+            held -= it->first;
+            idle.erase(it);
+            return p;
+        }
+        return nullptr;
+    }
+    void note(void *p, size_t bytes, int dev) {
+        std::lock_guard<std::mutex> l(mu);
+        allocated[p] = {bytes, dev};
+    }
+    // False: the caller frees p itself.
+    bool give(void *p, bool keep) {
+        std::vector<void *> out;
+        bool kept = false;
+        {
+            std::lock_guard<std::mutex> l(mu);
+            auto it = allocated.find(p);
+            if (it == allocated.end()) return false;
+            const size_t bytes = it->second.first;
+            const int dev = it->second.second;
+            allocated.erase(it);
+            if (keep && bytes <= POOL_MAX) {
+                while (held + bytes > POOL_MAX) {
+                    auto old = idle.begin();
+                    for (auto i = idle.begin(); i != idle.end(); ++i)
+                        if (i->second.age < old->second.age) old = i;
+                    held -= old->first;
+                    out.push_back(old->second.p);
+                    idle.erase(old);
+                }
+                idle.emplace(bytes, Block{p, bytes, dev, ++clock});
+                held += bytes;
+                kept = true;
+            }
+        }
+        for (void *q : out) (void)hipFree(q);
+        return kept;
+    }
+    void trim() {
+        std::multimap<size_t, Block> out;
+        {
+            std::lock_guard<std::mutex> l(mu);
+            out.swap(idle);
+            held = 0;
+        }
+        for (auto &b : out) (void)hipFree(b.second.p);
+    }
+};
+// (never destroyed: graphs may outlive the statics of other files, and the memory goes
+// with the process)
+Pool &pool() {
+    static Pool *p = new Pool();
+    return *p;
+}
+thread_local bool t_idle_frees = false;
+std::mutex g_blocks_mu;
+std::vector<int64_t *> g_blocks;  // counter blocks given up (pinned host memory, 3 KB each)
+constexpr size_t BLOCKS_MAX = 64;
+}  // namespace
+
+IdleFrees::IdleFrees() : before(t_idle_frees) { t_idle_frees = true; }
+IdleFrees::~IdleFrees() { t_idle_frees = before; }
+
 void *dmalloc(size_t bytes) {
     if (bytes == 0) bytes = 8;
     if (g_alloc) return g_alloc(bytes, g_ctx);
-    void *p = nullptr;
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    bytes = Pool::round(bytes);
+    void *p = pool().take(bytes, dev);
+    if (p) return p;
     if (hipMalloc(&p, bytes) != hipSuccess) {
         (void)hipGetLastError();
-        return nullptr;
+        pool().trim();
+        if (hipMalloc(&p, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
     }
+    pool().note(p, bytes, dev);
     return p;
 }
 
 void dfree(void *p) {
     if (!p) return;
     if (g_free) g_free(p, g_ctx);
-    else (void)hipFree(p);
+    else if (!pool().give(p, t_idle_frees)) (void)hipFree(p);
+}
+
+int64_t *counter_block_alloc() {
+    constexpr size_t bytes = sizeof(int64_t) * (H_ALL + C_COUNT);
+    int64_t *p = nullptr;
+    {
+        std::lock_guard<std::mutex> l(g_blocks_mu);
+        if (!g_blocks.empty()) {
+            p = g_blocks.back();
+            g_blocks.pop_back();
+        }
+    }
+    if (!p && hipHostMalloc((void **)&p, bytes, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) !=
+                  hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    std::memset(p, 0, bytes);
+    return p;
+}
+
+void counter_block_free(int64_t *p) {
+    {
+        std::lock_guard<std::mutex> l(g_blocks_mu);
+        if (t_idle_frees && g_blocks.size() < BLOCKS_MAX) {
+            g_blocks.push_back(p);
+            return;
+        }
+    }
+    (void)hipHostFree(p);
 }
 
 static dg_config defaults(const dg_config *c) {
@@ -142,6 +286,7 @@ const char *dg_last_error(void) { return dg::g_err; }
 int dg_set_allocator(void *(*alloc)(size_t, void *), void (*free_fn)(void *, void *), void *ctx) {
     if (g_live_graphs.load() > 0) return set_error(DG_ESTATE, "allocator must be set before any graph exists");
     if ((alloc == nullptr) != (free_fn == nullptr)) return set_error(DG_EINVAL, "alloc and free come together");
+    pool().trim();
     g_alloc = alloc;
     g_free = free_fn;
     g_ctx = ctx;
@@ -169,6 +314,12 @@ int dg_graph_create(int32_t n, int64_t m, const int32_t *src, const int32_t *dst
     if (rc == DG_OK) rc = stage(dst, m, dev, g->stream, bd, &dd);
     if (rc == DG_OK) rc = stage(w, m, dev, g->stream, bw, &dw);
     if (rc == DG_OK) rc = graph_build(g, m, ds, dd, dw);
+    if (rc == DG_OK) {  // the build has waited for its stream
+        IdleFrees idle;
+        bs.release();
+        bd.release();
+        bw.release();
+    }
     bs.release();
     bd.release();
     bw.release();
@@ -202,11 +353,15 @@ static void query_free(dg_query *q) {
 
 int dg_graph_destroy(dg_graph *g) {
     if (!g) return set_error(DG_EINVAL, "null graph");
+    // the graph's work ends before its memory may serve another graph
+    const bool ended = hipStreamSynchronize(g->stream) == hipSuccess &&
+                       (!g->aux || hipStreamSynchronize(g->aux) == hipSuccess) && !g->broken;
+    IdleFrees idle;
+    if (!ended) t_idle_frees = false;
     for (dg_query *q : g->queries) {
         query_free(q);
     }
     g->queries.clear();
-    (void)hipStreamSynchronize(g->stream);
     dir_free(g->fwd);
     dir_free(g->rev_own);
     ws_free(g);
@@ -391,7 +546,9 @@ int dg_query_detach(dg_query *q) {
     auto it = std::find(g->queries.begin(), g->queries.end(), q);
     if (it == g->queries.end()) return set_error(DG_EINVAL, "query not attached");
     g->queries.erase(it);
-    (void)hipStreamSynchronize(g->stream);
+    const bool ended = hipStreamSynchronize(g->stream) == hipSuccess && !g->broken;
+    IdleFrees idle;
+    if (!ended) t_idle_frees = false;
     query_free(q);
     return DG_OK;
 }

@@ -47,6 +47,16 @@ int set_error(int code, const char *fmt, ...);
 // ---- device memory -------------------------------------------------------------------
 void *dmalloc(size_t bytes);
 void dfree(void *p);
+// While one is in scope, the calling thread's dfree calls may keep the memory for a
+// later dmalloc: nothing queued on any stream uses what it frees.
+struct IdleFrees {
+    IdleFrees();
+    ~IdleFrees();
+    bool before;
+};
+// The pinned, device-visible block of a graph's counters (H_ALL + C_COUNT words, zero).
+int64_t *counter_block_alloc();
+void counter_block_free(int64_t *p);
 
 // Growable device buffer.  ensure() keeps contents only when asked.
 template <class T>

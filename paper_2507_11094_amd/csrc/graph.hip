@@ -166,11 +166,11 @@ int counters_read(dg_graph *g) {
 int ws_init(dg_graph *g) {
     g->ws.dcnt = static_cast<int64_t *>(dmalloc(sizeof(int64_t) * C_ALL));
     if (!g->ws.dcnt) return set_error(DG_ENOMEM, "counter allocation failed");
-    DG_HIP(hipHostMalloc((void **)&g->ws.hcnt, sizeof(int64_t) * H_ALL, hipHostMallocMapped | hipHostMallocCoherent));
-    std::memset(g->ws.hcnt, 0, sizeof(int64_t) * H_ALL);
+    g->ws.hcnt = counter_block_alloc();
+    if (!g->ws.hcnt) return set_error(DG_ENOMEM, "counter allocation failed");
+    g->ws.hcnt_m = g->ws.hcnt + H_ALL;
     g->ws.dcnt_m = static_cast<int64_t *>(dmalloc(sizeof(int64_t) * C_COUNT));
     if (!g->ws.dcnt_m) return set_error(DG_ENOMEM, "counter allocation failed");
-    DG_HIP(hipHostMalloc((void **)&g->ws.hcnt_m, sizeof(int64_t) * C_COUNT, hipHostMallocDefault));
     DG_TRY(fill_i64(g->ws.dcnt_m, 0, C_COUNT, g->stream));
     return fill_i64(g->ws.dcnt, 0, C_ALL, g->stream);
 }
@@ -201,9 +201,8 @@ void ws_free(dg_graph *g) {
     w.wq.release(); w.wseq.release(); w.wctr.release(); w.inq.release();
     g->perm.release(); g->iperm.release();
     if (w.dcnt) dfree(w.dcnt);
-    if (w.hcnt) (void)hipHostFree(w.hcnt);
+    if (w.hcnt) counter_block_free(w.hcnt);
     if (w.dcnt_m) dfree(w.dcnt_m);
-    if (w.hcnt_m) (void)hipHostFree(w.hcnt_m);
     w.sw_m.release();
     w.dcnt_m = nullptr;
     w.hcnt_m = nullptr;
@@ -433,9 +432,11 @@ int graph_build(dg_graph *g, int64_t m, const int32_t *src, const int32_t *dst, 
     }
     g->rev = g->undirected ? &g->fwd : &g->rev_own;
     g->m_live = arcs;
+    DG_TRY(counters_read(g));  // also brings the longest-row bound to the host
     // the build-sized scratch is not needed again
+    IdleFrees idle;
     ws.ikey.release(); ws.ikey_s.release(); ws.iw.release(); ws.iw_s.release(); ws.sw.release();
-    return counters_read(g);  // also brings the longest-row bound to the host
+    return DG_OK;
 }
 
 // ---------------------------------------------------------------- merge (Section 3.5)
