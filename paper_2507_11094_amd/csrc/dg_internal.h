@@ -308,12 +308,12 @@ int fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 int fill_i64(int64_t *p, int64_t v, int64_t n, hipStream_t s);
 int scan_excl(dg_graph *g, const int64_t *in, int64_t *out, int64_t n);  // exclusive prefix sum
 
-// sort.hip: stable LSD radix sort of (key, value) pairs on the low `bits` bits of
-// the keys (kin/vin are not modified; kout/vout must not alias them), and an
+// sort.hip: stable LSD radix sort of (key, value) pairs on the `bits` bits of the keys
+// from bit `shift0` up (kin/vin are not modified; kout/vout must not alias them), and an
 // exclusive scan of non-negative int64 values (total below 2^48).  On a look-back
 // spin-limit exit they OR a bit into *err (device memory).
 int radix_sort_pairs(hipStream_t s, SortWork &w, const uint64_t *kin, uint64_t *kout, const int32_t *vin,
-                     int32_t *vout, int64_t n, int bits, int64_t *err);
+                     int32_t *vout, int64_t n, int bits, int64_t *err, int shift0 = 0);
 int scan_excl_i64(hipStream_t s, SortWork &w, const int64_t *in, int64_t *out, int64_t n, int64_t *err);
 int fill_u64_on(uint64_t *p, uint64_t v, int64_t n, hipStream_t s);
 

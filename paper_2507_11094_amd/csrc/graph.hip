@@ -243,15 +243,14 @@ __global__ void k_validate_edges(int64_t m, const int32_t *s, const int32_t *d, 
     }
 }
 
-__global__ void k_make_keys(int64_t m, const int32_t *s, const int32_t *d, const int32_t *w, int B,
-                            int reverse, int both, const int32_t *perm, uint64_t *keys, int32_t *vals) {
+__global__ void k_make_keys(int64_t m, const int32_t *s, const int32_t *d, const int32_t *w, int B, int both,
+                            const int32_t *perm, uint64_t *keys, int32_t *vals) {
     for (int64_t i = gtid(); i < m; i += gstride()) {
         uint32_t u = (uint32_t)s[i], v = (uint32_t)d[i];
         if (perm) {
             u = (uint32_t)perm[u];
             v = (uint32_t)perm[v];
         }
-        if (reverse) { uint32_t t = u; u = v; v = t; }
         int32_t wt = w ? w[i] : 1;
         keys[i] = ((uint64_t)u << B) | v;
         vals[i] = wt;
@@ -267,11 +266,13 @@ __global__ void k_check_dup(int64_t m, const uint64_t *k, int64_t *cnt) {
         if (k[i] == k[i - 1]) atomicOr((unsigned long long *)&cnt[C_ERR], 2ull);
 }
 
-__global__ void k_split_keys(int64_t m, const uint64_t *k, const int32_t *vals, int B, int32_t *col,
+// Entries of sorted keys (row << B | col), or, swapped, of keys (col << B | row)
+// sorted by row and then column.
+__global__ void k_split_keys(int64_t m, const uint64_t *k, const int32_t *vals, int B, int swapped, int32_t *col,
                              int32_t *w) {
     const uint64_t mask = (1ull << B) - 1;
     for (int64_t i = gtid(); i < m; i += gstride()) {
-        col[i] = (int32_t)(k[i] & mask);
+        col[i] = (int32_t)(swapped ? k[i] >> B : k[i] & mask);
         w[i] = vals[i];
     }
 }
@@ -279,6 +280,18 @@ __global__ void k_split_keys(int64_t m, const uint64_t *k, const int32_t *vals, 
 // off[r] = first position whose row is >= r, for r in [0, n]
 __global__ void k_row_offsets(int32_t n, const uint64_t *k, int64_t m, int B, int64_t *off) {
     for (int64_t r = gtid(); r <= n; r += gstride()) off[r] = lower_key(k, 0, m, (uint64_t)r << B);
+}
+__global__ void k_row_offsets_swapped(int32_t n, const uint64_t *k, int64_t m, int B, int64_t *off) {
+    const uint64_t mask = (1ull << B) - 1;
+    for (int64_t r = gtid(); r <= n; r += gstride()) {
+        int64_t lo = 0, hi = m;
+        while (lo < hi) {
+            const int64_t mid = (lo + hi) >> 1;
+            if ((k[mid] & mask) < (uint64_t)r) lo = mid + 1;
+            else hi = mid;
+        }
+        off[r] = lo;
+    }
 }
 
 // Row lengths, and their maximum raised into *maxrow.
@@ -309,7 +322,7 @@ __global__ __launch_bounds__(WIDE_T) void k_diff_row_max(int64_t nk, const uint6
 static int64_t ntiles_for(int64_t m) { return (m + TILE - 1) / TILE; }
 
 static int dir_from_sorted(dg_graph *g, Dir &d, const uint64_t *keys, const int32_t *vals, int64_t m,
-                           int B) {
+                           int B, bool swapped) {
     hipStream_t s = g->stream;
     d.n = g->n;
     d.keybits = B;
@@ -324,10 +337,10 @@ static int dir_from_sorted(dg_graph *g, Dir &d, const uint64_t *keys, const int3
     DG_TRY(d.ttomb.ensure(ntiles_for(m) + 2));
     DG_TRY(d.doff.ensure(g->n + 1));
     if (m > 0)
-        hipLaunchKernelGGL(k_split_keys, dim3(grid_for(m)), dim3(256), 0, s, m, keys, vals, B,
+        hipLaunchKernelGGL(k_split_keys, dim3(grid_for(m)), dim3(256), 0, s, m, keys, vals, B, (int)swapped,
                            d.col.p, d.w.p);
-    hipLaunchKernelGGL(k_row_offsets, dim3(grid_for(g->n + 1)), dim3(256), 0, s, g->n, keys, m, B,
-                       d.off.p);
+    hipLaunchKernelGGL(swapped ? k_row_offsets_swapped : k_row_offsets, dim3(grid_for(g->n + 1)), dim3(256), 0, s,
+                       g->n, keys, m, B, d.off.p);
     hipLaunchKernelGGL(k_degrees, dim3(grid_wide(g->n)), dim3(WIDE_T), 0, s, g->n, d.off.p, d.deg.p,
                        g->ws.dcnt + C_MAXROW);
     DG_HIP(hipGetLastError());
@@ -336,12 +349,59 @@ static int dir_from_sorted(dg_graph *g, Dir &d, const uint64_t *keys, const int3
     return DG_OK;
 }
 
-// Vertex order by degree: key = (INT32_MAX - degree) above the id, so that an
-// ascending sort puts the highest degree first and breaks ties by id.
-__global__ void k_order_keys(int32_t n, const int64_t *off, int B, uint64_t *keys, int32_t *vals) {
+// Degrees of an edge list.  One add in memory per arc would run at 14 G/s (1.2 ms for
+// 16.7M arcs), so the ids are first parted by their top bits (one pass of the radix
+// sort) and each part is counted in LDS by DEG_COPIES blocks, one share of the part
+// and one copy of the counts each.
+constexpr int DEG_PARTS_BITS = 8, DEG_PARTS = 1 << DEG_PARTS_BITS;
+constexpr int DEG_COPIES = 8;
+constexpr int DEG_RANGE = 8192;  // ids counted at a time (32 KB)
+
+__global__ void k_degree_keys(int64_t m, const int32_t *a, const int32_t *b, uint64_t *keys) {
+    for (int64_t i = gtid(); i < m; i += gstride()) {
+        keys[i] = (uint64_t)a[i];
+        if (b) keys[m + i] = (uint64_t)b[i];
+    }
+}
+
+// cnt[copy * n + v] = keys equal to v in this copy's share of v's part.  Parts hold the
+// ids p << shift .. (p + 1) << shift and are the ranges start[p] .. start[p + 1] of keys.
+// (A skewed part may be a tenth of the arcs: four keys per thread in flight.)
+__global__ __launch_bounds__(WIDE_T) void k_degree_count(const uint64_t *keys, const int64_t *start, int shift,
+                                                         int32_t n, int32_t *cnt) {
+    __shared__ int32_t h[DEG_RANGE];
+    const int p = blockIdx.x / DEG_COPIES, copy = blockIdx.x % DEG_COPIES;
+    const int64_t s = start[p], len = start[p + 1] - s;
+    const int64_t e0 = s + len * copy / DEG_COPIES, e1 = s + len * (copy + 1) / DEG_COPIES;
+    const int64_t v1 = min((int64_t)(p + 1) << shift, (int64_t)n);
+    for (int64_t v0 = (int64_t)p << shift; v0 < v1; v0 += DEG_RANGE) {
+        const int r = (int)min((int64_t)DEG_RANGE, v1 - v0);
+        for (int i = threadIdx.x; i < r; i += WIDE_T) h[i] = 0;
+        __syncthreads();
+        constexpr int U = 4;
+        for (int64_t e = e0 + threadIdx.x; e < e1; e += U * WIDE_T) {
+            uint64_t k[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) k[u] = keys[min(e + u * WIDE_T, e1 - 1)];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t at = (int64_t)k[u] - v0;
+                if (e + u * WIDE_T < e1 && at >= 0 && at < r) atomicAdd(&h[at], 1);
+            }
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < r; i += WIDE_T) cnt[(int64_t)copy * n + v0 + i] = h[i];
+        __syncthreads();
+    }
+}
+
+// Vertex order by degree: key = n - 1 - degree, so that a stable ascending sort of the
+// ids puts the highest degree first and keeps ties in id order.
+__global__ void k_order_keys(int32_t n, int copies, const int32_t *cnt, uint64_t *keys, int32_t *vals) {
     for (int64_t v = gtid(); v < n; v += gstride()) {
-        const int64_t deg = off[v + 1] - off[v];
-        keys[v] = ((uint64_t)(INT32_MAX - (int32_t)min(deg, (int64_t)INT32_MAX)) << B) | (uint64_t)v;
+        int64_t deg = 0;
+        for (int c = 0; c < copies; ++c) deg += cnt[(int64_t)c * n + v];
+        keys[v] = (uint64_t)(n - 1 - min(deg, (int64_t)n - 1));
         vals[v] = (int32_t)v;
     }
 }
@@ -355,7 +415,8 @@ __global__ void k_perm_from_order(int32_t n, const int32_t *order, int32_t *perm
 }
 
 // perm / iperm of the degree order of a validated edge list: the out-degree (the
-// degree, undirected) of every given id, then a sort of (degree, id).
+// degree, undirected) of every given id, then a sort by it.  Counting takes the place
+// of a whole sort of the arcs, which only served to find the row lengths.
 static int vertex_order_build(dg_graph *g, int64_t m, const int32_t *src, const int32_t *dst, int B) {
     hipStream_t s = g->stream;
     Work &ws = g->ws;
@@ -366,22 +427,32 @@ static int vertex_order_build(dg_graph *g, int64_t m, const int32_t *src, const 
     DG_TRY(ws.ikey_s.ensure(cap));
     DG_TRY(ws.iw.ensure(cap));
     DG_TRY(ws.iw_s.ensure(cap));
-    DG_TRY(ws.scan64.ensure((size_t)n + 1));
     DG_TRY(g->perm.ensure((size_t)n + 1));
     DG_TRY(g->iperm.ensure((size_t)n + 1));
+    DBuf<int32_t> cnt;
+    DG_TRY(cnt.ensure((size_t)DEG_COPIES * n));
+    DG_TRY(ws.scan64.ensure(DEG_PARTS + 1));
+    const int shift = std::max(0, B - DEG_PARTS_BITS);
     if (m > 0)
-        hipLaunchKernelGGL(k_make_keys, dim3(grid_for(m)), dim3(256), 0, s, m, src, dst, (const int32_t *)nullptr,
-                           B, 0, (int)g->undirected, (const int32_t *)nullptr, ws.ikey.p, ws.iw.p);
+        hipLaunchKernelGGL(k_degree_keys, dim3(grid_for(m)), dim3(256), 0, s, m, src,
+                           g->undirected ? dst : (const int32_t *)nullptr, ws.ikey.p);
     DG_HIP(hipGetLastError());
-    DG_TRY(sort_pairs(g, ws.ikey.p, ws.ikey_s.p, ws.iw.p, ws.iw_s.p, arcs, 2 * B));
-    hipLaunchKernelGGL(k_row_offsets, dim3(grid_for(n + 1)), dim3(256), 0, s, n, ws.ikey_s.p, arcs, B,
-                       ws.scan64.p);
-    hipLaunchKernelGGL(k_order_keys, dim3(grid_for(n)), dim3(256), 0, s, n, ws.scan64.p, B, ws.ikey.p, ws.iw.p);
+    // (the values the sort carries along mean nothing here)
+    DG_TRY(radix_sort_pairs(s, ws.sw, ws.ikey.p, ws.ikey_s.p, ws.iw.p, ws.iw_s.p, arcs, B - shift,
+                            ws.dcnt + C_SORT_ERR, shift));
+    hipLaunchKernelGGL(k_row_offsets, dim3(grid_for(DEG_PARTS + 1)), dim3(256), 0, s, DEG_PARTS, ws.ikey_s.p, arcs,
+                       shift, ws.scan64.p);
+    hipLaunchKernelGGL(k_degree_count, dim3(DEG_PARTS * DEG_COPIES), dim3(WIDE_T), 0, s, ws.ikey_s.p, ws.scan64.p, shift,
+                       n, cnt.p);
+    hipLaunchKernelGGL(k_order_keys, dim3(grid_for(n)), dim3(256), 0, s, n, DEG_COPIES, cnt.p, ws.ikey.p, ws.iw.p);
     DG_HIP(hipGetLastError());
-    DG_TRY(sort_pairs(g, ws.ikey.p, ws.ikey_s.p, ws.iw.p, ws.iw_s.p, n, B + 31));
+    DG_TRY(sort_pairs(g, ws.ikey.p, ws.ikey_s.p, ws.iw.p, ws.iw_s.p, n, B));
     hipLaunchKernelGGL(k_perm_from_order, dim3(grid_for(n)), dim3(256), 0, s, n, ws.iw_s.p, g->perm.p,
                        g->iperm.p);
     DG_HIP(hipGetLastError());
+    DG_HIP(hipStreamSynchronize(s));
+    IdleFrees idle;
+    cnt.release();
     return DG_OK;
 }
 
@@ -414,21 +485,21 @@ int graph_build(dg_graph *g, int64_t m, const int32_t *src, const int32_t *dst, 
     DG_TRY(ws.ikey_s.ensure(arcs + 1));
     DG_TRY(ws.iw.ensure(arcs + 1));
     DG_TRY(ws.iw_s.ensure(arcs + 1));
-    for (int dir = 0; dir < (g->undirected ? 1 : 2); ++dir) {
-        if (m > 0)
-            hipLaunchKernelGGL(k_make_keys, dim3(grid_for(m)), dim3(256), 0, s, m, src, dst, w, B, dir,
-                               (int)g->undirected, perm, ws.ikey.p, ws.iw.p);
-        DG_HIP(hipGetLastError());
-        DG_TRY(sort_pairs(g, ws.ikey.p, ws.ikey_s.p, ws.iw.p, ws.iw_s.p, arcs, 2 * B));
-        if (dir == 0) {
-            if (arcs > 1)
-                hipLaunchKernelGGL(k_check_dup, dim3(grid_for(arcs)), dim3(256), 0, s, arcs, ws.ikey_s.p,
-                                   ws.dcnt);
-            DG_TRY(counters_read(g));
-            if (ws.hcnt[C_ERR]) return set_error(DG_EINVAL, "edge list holds a repeated edge");
-        }
-        Dir &d = dir == 0 ? g->fwd : g->rev_own;
-        DG_TRY(dir_from_sorted(g, d, ws.ikey_s.p, ws.iw_s.p, arcs, B));
+    if (m > 0)
+        hipLaunchKernelGGL(k_make_keys, dim3(grid_for(m)), dim3(256), 0, s, m, src, dst, w, B, (int)g->undirected,
+                           perm, ws.ikey.p, ws.iw.p);
+    DG_HIP(hipGetLastError());
+    DG_TRY(sort_pairs(g, ws.ikey.p, ws.ikey_s.p, ws.iw.p, ws.iw_s.p, arcs, 2 * B));
+    if (arcs > 1)
+        hipLaunchKernelGGL(k_check_dup, dim3(grid_for(arcs)), dim3(256), 0, s, arcs, ws.ikey_s.p, ws.dcnt);
+    DG_TRY(counters_read(g));
+    if (ws.hcnt[C_ERR]) return set_error(DG_EINVAL, "edge list holds a repeated edge");
+    DG_TRY(dir_from_sorted(g, g->fwd, ws.ikey_s.p, ws.iw_s.p, arcs, B, false));
+    if (!g->undirected) {
+        // the reverse rows: the sorted arcs (u, v) in the order of v, by a stable sort of
+        // the low half of their keys
+        DG_TRY(sort_pairs(g, ws.ikey_s.p, ws.ikey.p, ws.iw_s.p, ws.iw.p, arcs, B));
+        DG_TRY(dir_from_sorted(g, g->rev_own, ws.ikey.p, ws.iw.p, arcs, B, true));
     }
     g->rev = g->undirected ? &g->fwd : &g->rev_own;
     g->m_live = arcs;

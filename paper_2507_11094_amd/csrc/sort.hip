@@ -164,7 +164,8 @@ __host__ __device__ __forceinline__ uint32_t digit_mask(int bits, int shift) {
 // `ghist` (cleared by the previous call) and clears `gnext` for the next call
 // (its last reader, the previous call's passes, has finished on this stream).
 __global__ __launch_bounds__(RS_THREADS) void k_rs_hist(const uint64_t *__restrict__ keys, int64_t n,
-                                                        int passes, int bits, uint32_t *ghist, uint32_t *gnext) {
+                                                        int passes, int shift0, int bits, uint32_t *ghist,
+                                                        uint32_t *gnext) {
     __shared__ uint32_t h[RS_WAVES][RS_MAX_PASSES][RS_RADIX];
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < RS_MAX_PASSES * RS_RADIX; i += RS_THREADS) gnext[i] = 0;
@@ -175,7 +176,8 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_hist(const uint64_t *__restri
     const int64_t stride = gstride();
     for (int64_t i = gtid(); i < n; i += stride) {
         const uint64_t k = keys[i];
-        for (int p = 0; p < passes; ++p) atomicAdd(&h[wv][p][digit_of(k, RS_BITS * p, digit_mask(bits, RS_BITS * p))], 1u);
+        for (int p = 0; p < passes; ++p)
+            atomicAdd(&h[wv][p][digit_of(k, shift0 + RS_BITS * p, digit_mask(bits, RS_BITS * p))], 1u);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < passes * RS_RADIX; i += RS_THREADS) {
@@ -434,7 +436,7 @@ int scan_excl_i64(hipStream_t s, SortWork &w, const int64_t *in, int64_t *out, i
 }
 
 int radix_sort_pairs(hipStream_t s, SortWork &w, const uint64_t *kin, uint64_t *kout, const int32_t *vin,
-                     int32_t *vout, int64_t n, int bits, int64_t *err) {
+                     int32_t *vout, int64_t n, int bits, int64_t *err, int shift0) {
     if (n <= 0) return DG_OK;
     if (n > INT32_MAX) return set_error(DG_EINVAL, "sort of more than 2^31 keys");
     bits = std::max(1, std::min(bits, 64));
@@ -457,7 +459,7 @@ int radix_sort_pairs(hipStream_t s, SortWork &w, const uint64_t *kin, uint64_t *
     uint32_t *gcur = (w.calls & 1) ? gbase : ghist, *gnext = (w.calls & 1) ? ghist : gbase;
     ++w.calls;
     hipLaunchKernelGGL(k_rs_hist, dim3(blocks_for(n, RS_THREADS * 4, 2048)), dim3(RS_THREADS), 0, s, kin, n,
-                       passes, bits, gcur, gnext);
+                       passes, shift0, bits, gcur, gnext);
     DG_HIP(hipGetLastError());
     // ping-pong so that the last pass writes kout/vout: odd pass counts start there
     const uint64_t *ki = kin;
@@ -468,7 +470,7 @@ int radix_sort_pairs(hipStream_t s, SortWork &w, const uint64_t *kin, uint64_t *
         int32_t *vo = to_out ? vout : tv;
         uint64_t ep = 0;
         DG_TRY(next_epoch(w, status, words, s, &ep));
-        hipLaunchKernelGGL(big ? k_rs_pass<16> : k_rs_pass<RS_ITEMS>, dim3((unsigned)tiles), dim3(RS_THREADS), 0, s, ki, vi, ko, vo, n, RS_BITS * p,
+        hipLaunchKernelGGL(big ? k_rs_pass<16> : k_rs_pass<RS_ITEMS>, dim3((unsigned)tiles), dim3(RS_THREADS), 0, s, ki, vi, ko, vo, n, shift0 + RS_BITS * p,
                            digit_mask(bits, RS_BITS * p), gcur + p * RS_RADIX, status, hdr + H_TILE_SORT + p, ep, err);
         DG_HIP(hipGetLastError());
         ki = ko;

@@ -70,3 +70,30 @@ def test_frontier_shapes(dg, k, heavy, delta):
     G.apply(bs, bd, back, 1 - bo)
     assert np.array_equal(q.read()[0], oracle.sssp(n, s, d, w, 0))
     G.close()
+
+
+# the degree order and both directions of a build: id ranges around the parts of the
+# degree count, a vertex with most of the arcs, no arcs, one arc, undirected
+@pytest.mark.parametrize("n,m,und", [(2, 1, False), (1, 0, False), (257, 4000, False), (8193, 40000, True),
+                                     (262145, 1500000, False), (2097151, 1200000, False), (2097153, 500000, True)])
+def test_build_order_and_directions(dg, n, m, und):
+    rng = np.random.default_rng(n)
+    u = np.where(rng.random(2 * m + 8) < 0.4, n // 3, rng.integers(0, n, 2 * m + 8))
+    v = rng.integers(0, n, 2 * m + 8)
+    if n == 2:
+        u, v = np.array([1]), np.array([0])
+    if und:
+        u, v = np.minimum(u, v), np.maximum(u, v)
+    key = np.unique((u.astype(np.int64) << 32 | v)[u != v])
+    key = rng.permutation(key)[:m]
+    s, d = (key >> 32).astype(np.int32), (key & 0xFFFFFFFF).astype(np.int32)
+    w = rng.integers(1, 100, s.size).astype(np.int32)
+    G = dg.Graph(n, s, d, w, undirected=und)
+    es, ed, ew = G.export()
+    o = np.argsort(key)
+    assert np.array_equal(es, s[o]) and np.array_equal(ed, d[o]) and np.array_equal(ew, w[o])
+    # ranks read the reverse rows, the export the forward ones
+    as_, ad = (np.concatenate([s, d]), np.concatenate([d, s])) if und else (s, d)
+    want, _, _ = oracle.pagerank(n, as_, ad, 0.85, 1e-9, 1000)
+    assert np.max(np.abs(G.pr_static(0.85, 1e-9, 1000)[0] - want)) <= 1e-10
+    G.close()
