@@ -239,6 +239,13 @@ __device__ __forceinline__ uint64_t sssp_pack(int32_t dist, int32_t parent) {
 __device__ __forceinline__ int32_t sssp_dist(uint64_t k) { return (int32_t)(k >> 32); }
 __device__ __forceinline__ int32_t sssp_parent(uint64_t k) { return (int32_t)(uint32_t)(k & 0xffffffffu); }
 
+// The end of a kernel whose results the host polls for (publish_wait): one wave, after
+// the results are stored (by other waves: and a block barrier passed).
+__device__ __forceinline__ void publish_seq(int64_t *host_seq, int64_t seq) {
+    __threadfence_system();  // the wave's stores before the number
+    if (lane_id() == 0) __hip_atomic_store(host_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Grid-stride helpers
 __device__ __forceinline__ int64_t gtid() { return (int64_t)blockIdx.x * blockDim.x + threadIdx.x; }
 __device__ __forceinline__ int64_t gstride() { return (int64_t)gridDim.x * blockDim.x; }

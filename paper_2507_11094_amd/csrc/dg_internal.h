@@ -300,6 +300,9 @@ int counters_clear(dg_graph *g);
 // n <= 512 words of device memory to dst (pinned host memory), in stream order, and
 // the wait for them.
 int publish(dg_graph *g, const void *src, int n, void *dst);
+// The wait for the block that ++g->ws.seq numbers, whose kernel on g->stream stores the
+// number to g->ws.hcnt[H_SEQ] last.
+int publish_wait(dg_graph *g);
 int ws_init(dg_graph *g);
 void ws_free(dg_graph *g);
 void dir_free(Dir &d);

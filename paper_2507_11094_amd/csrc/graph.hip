@@ -91,11 +91,6 @@ __global__ __launch_bounds__(C_ALL) void k_counters_clear(int64_t *cnt) {
 // stream synchronisation in its place cost about 25 us a step (and the next step a
 // launch to clear the counters), against about 10 us; a 4096^2 grid batch has 250 steps.
 
-__device__ __forceinline__ void publish_seq(int64_t *host_seq, int64_t seq) {
-    __threadfence_system();  // the wave's stores before the number
-    if (lane_id() == 0) __hip_atomic_store(host_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 // Counters and the sum of the tally slots to the host, then zero for the next step.
 __global__ __launch_bounds__(WAVE) void k_counters_publish(int64_t *cnt, int64_t *host, int64_t *host_seq,
                                                            int64_t seq) {
@@ -120,7 +115,7 @@ __global__ __launch_bounds__(WAVE) void k_publish(const int64_t *src, int n, int
 // Until block g->ws.seq has arrived.  Polls for about 0.1 ms (queuing PageRank steps
 // between polls while SSSP runs beside them), then blocks; a stream that ends
 // without the number has failed.
-static int publish_wait(dg_graph *g) {
+int publish_wait(dg_graph *g) {
     const int64_t *f = g->ws.hcnt + H_SEQ;
     constexpr int SPINS = 4096, QUERY = 1024;
     for (int spin = 1;; ++spin) {

@@ -78,6 +78,34 @@ __global__ void k_set_unpack(int64_t nl, const uint64_t *key, int64_t base, int3
     }
 }
 
+// The same by one workgroup, which tells the host itself when its stores are done: a
+// read of one member is short (at most 16k vertices in one pass of 16 loads per
+// thread), and a set is read member by member, so the wait is what it costs.
+constexpr int UNPACK_T = 1024, UNPACK_U = 8;
+constexpr int64_t UNPACK_ONE = 2 * UNPACK_T * UNPACK_U;
+__global__ __launch_bounds__(UNPACK_T) void k_set_unpack_one(int64_t nl, const uint64_t *key, int64_t base,
+                                                             int32_t *dist, int32_t *parent, int64_t *host_seq,
+                                                             int64_t seq) {
+    for (int64_t v0 = threadIdx.x; v0 < nl; v0 += UNPACK_U * UNPACK_T) {
+        uint64_t k[UNPACK_U];
+#pragma unroll
+        for (int u = 0; u < UNPACK_U; ++u) k[u] = key[base + min(v0 + u * UNPACK_T, nl - 1)];
+#pragma unroll
+        for (int u = 0; u < UNPACK_U; ++u) {
+            const int64_t v = v0 + u * UNPACK_T;
+            if (v >= nl) continue;
+            const int32_t d = sssp_dist(k[u]);
+            dist[v] = d >= INF ? INF : d;
+            if (parent) {
+                const int32_t p = d >= INF ? -1 : sssp_parent(k[u]);
+                parent[v] = p < 0 ? -1 : (int32_t)(p - base);
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < WAVE) publish_seq(host_seq, seq);
+}
+
 template <class T>
 static int stage_into(const T *p, int64_t n, bool dev, hipStream_t s, DBuf<T> &buf, const T **out) {
     if (!p || dev) {
@@ -313,6 +341,13 @@ int dg_set_sssp_read(dg_set *S, int32_t member, int32_t *dist, int32_t *parent, 
     const int64_t base = S->vbase[member], nl = S->vbase[member + 1] - base;
     hipStream_t s = S->stream;
     if (flags & DG_DEVICE_PTRS) {
+        dg_graph *g = S->g;
+        if (nl <= UNPACK_ONE && g->stream == s) {
+            hipLaunchKernelGGL(k_set_unpack_one, dim3(1), dim3(UNPACK_T), 0, s, nl, S->q->key.p, base, dist, parent,
+                               g->ws.hcnt + H_SEQ, ++g->ws.seq);
+            DG_HIP(hipGetLastError());
+            return publish_wait(g);
+        }
         hipLaunchKernelGGL(k_set_unpack, dim3(grid_for(nl)), dim3(256), 0, s, nl, S->q->key.p, base, dist, parent);
         DG_HIP(hipGetLastError());
         DG_HIP(hipStreamSynchronize(s));
