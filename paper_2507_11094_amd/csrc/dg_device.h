@@ -92,6 +92,18 @@ __device__ __forceinline__ T dpp_move(T x) {
     }
 }
 
+// Lanes of the wave whose d (8 bits) equals this lane's, among `active`.
+__device__ __forceinline__ uint64_t match8(uint32_t d, uint64_t active) {
+    uint64_t m = active;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        const bool bit = (d >> b) & 1u;
+        const uint64_t bb = ballot(bit);
+        m &= bit ? bb : ~bb;
+    }
+    return m;
+}
+
 // Wave-wide inclusive scan of integers: Hillis-Steele inside each 16-lane row by
 // DPP row shifts, then the row totals carried across rows by the two DPP row
 // broadcasts.  Six DPP moves per 32 bits, no LDS traffic.  All lanes must be active.

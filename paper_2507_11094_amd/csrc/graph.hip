@@ -92,8 +92,8 @@ __global__ __launch_bounds__(C_ALL) void k_counters_clear(int64_t *cnt) {
 // launch to clear the counters), against about 10 us; a 4096^2 grid batch has 250 steps.
 
 // Counters and the sum of the tally slots to the host, then zero for the next step.
-__global__ __launch_bounds__(WAVE) void k_counters_publish(int64_t *cnt, int64_t *host, int64_t *host_seq,
-                                                           int64_t seq) {
+// (one wave)
+__device__ __forceinline__ void counters_publish_body(int64_t *cnt, int64_t *host, int64_t *host_seq, int64_t seq) {
     static_assert(C_COUNT <= WAVE && TALLY_SLOTS <= WAVE, "one wave");
     const int l = lane_id();
     int64_t tally = l < TALLY_SLOTS ? cnt[C_TALLY + l * TALLY_STRIDE] : 0;
@@ -104,6 +104,10 @@ __global__ __launch_bounds__(WAVE) void k_counters_publish(int64_t *cnt, int64_t
         if (l != C_MAXROW && l != C_SORT_ERR) cnt[l] = 0;
     }
     publish_seq(host_seq, seq);
+}
+__global__ __launch_bounds__(WAVE) void k_counters_publish(int64_t *cnt, int64_t *host, int64_t *host_seq,
+                                                           int64_t seq) {
+    counters_publish_body(cnt, host, host_seq, seq);
 }
 
 __global__ __launch_bounds__(WAVE) void k_publish(const int64_t *src, int n, int64_t *host, int64_t *host_seq,
@@ -149,10 +153,15 @@ int counters_clear(dg_graph *g) {
     return DG_OK;
 }
 
+static int counters_wait(dg_graph *g);
 int counters_read(dg_graph *g) {
     hipLaunchKernelGGL(k_counters_publish, dim3(1), dim3(WAVE), 0, g->stream, g->ws.dcnt, g->ws.hcnt,
                        g->ws.hcnt + H_SEQ, ++g->ws.seq);
     DG_HIP(hipGetLastError());
+    return counters_wait(g);
+}
+
+static int counters_wait(dg_graph *g) {
     DG_TRY(publish_wait(g));
     if (g->ws.hcnt[C_SORT_ERR]) return set_error(DG_EDEVICE, "sort or scan look-back did not finish (internal error)");
     return DG_OK;
@@ -929,8 +938,18 @@ int graph_export(dg_graph *g, int64_t *m, int32_t *src, int32_t *dst, int32_t *w
 
 // ---------------------------------------------------------------- batch application
 
-// Validation of a whole chunk before any change (rejects self-loops, ids outside
-// [0, n), ops other than 0/1 and insert weights outside [1, 2^30)).
+// One update: 1 (a deletion), 1 << 20 (an insertion) or 1 << 40 (self-loop, id outside
+// [0, n), op other than 0/1 or than expected, insert weight outside [1, 2^30)).
+__device__ __forceinline__ int64_t check_update(int64_t i, const int32_t *s, const int32_t *d, const int32_t *w,
+                                                const uint8_t *op, int32_t n, int expect) {
+    const int32_t u = s[i], v = d[i];
+    const uint8_t o = op[i];
+    bool bad = u < 0 || u >= n || v < 0 || v >= n || u == v || o > 1 || (expect >= 0 && o != expect);
+    if (o == 1 && w) bad |= (w[i] < 1 || w[i] >= (1 << 30));
+    return bad ? 1ll << 40 : (o == 0 ? 1 : 1ll << 20);
+}
+
+// Validation of a whole chunk before any change.
 // (One million updates: 98 us with one 256-thread block per 256 updates, whose 7,812
 // adds to the two counts ran one after the other.)
 __global__ __launch_bounds__(WIDE_T) void k_validate_batch(int64_t k, const int32_t *s, const int32_t *d,
@@ -940,13 +959,10 @@ __global__ __launch_bounds__(WIDE_T) void k_validate_batch(int64_t k, const int3
     int64_t nd = 0, ni = 0;
     bool anybad = false;
     for (int64_t i = gtid(); i < k; i += gstride()) {
-        int32_t u = s[i], v = d[i];
-        uint8_t o = op[i];
-        bool bad = u < 0 || u >= n || v < 0 || v >= n || u == v || o > 1 || (expect >= 0 && o != expect);
-        if (o == 1 && w) bad |= (w[i] < 1 || w[i] >= (1 << 30));
-        anybad |= bad;
-        nd += !bad && o == 0;
-        ni += !bad && o == 1;
+        const int64_t c = check_update(i, s, d, w, op, n, expect);
+        nd += c == 1;
+        ni += c == 1ll << 20;
+        anybad |= c == 1ll << 40;
     }
     if (anybad) atomicOr((unsigned long long *)&cnt[C_ERR], 1ull);
     block_count<WIDE_T>(&cnt[C_NDEL], nd, sc);
@@ -964,10 +980,10 @@ __global__ __launch_bounds__(WIDE_T) void k_validate_batch(int64_t k, const int3
 // both arcs).  The outputs of one workgroup are one contiguous range (the order of
 // arcs and keys is free: the keys are sorted next, and repeated deletions are told
 // apart by the MARK bit).
-__global__ __launch_bounds__(WIDE_T) void k_expand_batch(int64_t k, const int32_t *s, const int32_t *d,
-                                                         const int32_t *w, const uint8_t *op, int B, int undirected,
-                                                         const int32_t *perm, int32_t *ddu, int32_t *ddv,
-                                                         uint64_t *ikey, int32_t *iw, int64_t *cnt) {
+__device__ __forceinline__ void expand_batch_body(int64_t k, const int32_t *s, const int32_t *d,
+                                                  const int32_t *w, const uint8_t *op, int B, int undirected,
+                                                  const int32_t *perm, int32_t *ddu, int32_t *ddv,
+                                                  uint64_t *ikey, int32_t *iw, int64_t *cnt) {
     __shared__ BlockScratch sc;
     const int rep = undirected ? 2 : 1;
     for (int64_t c0 = (int64_t)blockIdx.x * WIDE_T; c0 < k; c0 += gstride()) {
@@ -996,6 +1012,12 @@ __global__ __launch_bounds__(WIDE_T) void k_expand_batch(int64_t k, const int32_
         }
     }
 }
+__global__ __launch_bounds__(WIDE_T) void k_expand_batch(int64_t k, const int32_t *s, const int32_t *d,
+                                                         const int32_t *w, const uint8_t *op, int B,
+                                                         int undirected, const int32_t *perm, int32_t *ddu,
+                                                         int32_t *ddv, uint64_t *ikey, int32_t *iw, int64_t *cnt) {
+    expand_batch_body(k, s, d, w, op, B, undirected, perm, ddu, ddv, ikey, iw, cnt);
+}
 
 // Place of arc (row, v): its base position, or -2 - its diff position, or -1 when
 // neither level holds it (tombstones count as held; the caller checks flags).
@@ -1013,11 +1035,11 @@ __device__ __forceinline__ int64_t find_arc(const int64_t *__restrict__ off, con
 // still intact for the pre-hooks).  The atomic MARK also dedups repeated
 // deletions of one arc.  Applied arcs are listed with their slot
 // (>= 0: base position, <= -2: diff position -2-p).
-__global__ __launch_bounds__(WIDE_T) void k_mark_deletes(int64_t na, const int32_t *ddu, const int32_t *ddv,
-                                                         const int64_t *__restrict__ off, int32_t *col,
-                                                         const int64_t *__restrict__ doff, int32_t *dcol,
-                                                         int undirected, int32_t *adu, int32_t *adv, int64_t *adpos,
-                                                         int32_t *tcu, int32_t *tcv, int64_t *cnt) {
+__device__ __forceinline__ void mark_deletes_body(int64_t na, const int32_t *ddu, const int32_t *ddv,
+                                                  const int64_t *__restrict__ off, int32_t *col,
+                                                  const int64_t *__restrict__ doff, int32_t *dcol,
+                                                  int undirected, int32_t *adu, int32_t *adv, int64_t *adpos,
+                                                  int32_t *tcu, int32_t *tcv, int64_t *cnt) {
     __shared__ BlockScratch sc;
     for (int64_t c0 = (int64_t)blockIdx.x * WIDE_T; c0 < na; c0 += gstride()) {
         const int64_t i = c0 + threadIdx.x;
@@ -1049,18 +1071,25 @@ __global__ __launch_bounds__(WIDE_T) void k_mark_deletes(int64_t na, const int32
         }
     }
 }
+__global__ __launch_bounds__(WIDE_T) void k_mark_deletes(int64_t na, const int32_t *ddu, const int32_t *ddv,
+                                                         const int64_t *__restrict__ off, int32_t *col,
+                                                         const int64_t *__restrict__ doff, int32_t *dcol,
+                                                         int undirected, int32_t *adu, int32_t *adv,
+                                                         int64_t *adpos, int32_t *tcu, int32_t *tcv, int64_t *cnt) {
+    mark_deletes_body(na, ddu, ddv, off, col, doff, dcol, undirected, adu, adv, adpos, tcu, tcv, cnt);
+}
 
 // Classify the sorted insertion keys: the first key of each run takes the
 // smallest weight of the run; it is IGNORED if the edge is live and not being
 // deleted, REVIVED in place if its slot is a tombstone or is being deleted in this
 // chunk (delete + insert ends present with the new weight), otherwise NEW.
-__global__ __launch_bounds__(WIDE_T) void k_classify_inserts(int64_t ni, const uint64_t *key, int32_t *iw, int B,
-                                                             const int64_t *__restrict__ off,
-                                                             const int32_t *__restrict__ col,
-                                                             const int64_t *__restrict__ doff,
-                                                             const int32_t *__restrict__ dcol, int64_t *isnew,
-                                                             int32_t *aiu, int32_t *aiv, int32_t *aiw,
-                                                             int64_t *aipos, int64_t *cnt) {
+__device__ __forceinline__ void classify_inserts_body(int64_t ni, const uint64_t *key, int32_t *iw, int B,
+                                                      const int64_t *__restrict__ off,
+                                                      const int32_t *__restrict__ col,
+                                                      const int64_t *__restrict__ doff,
+                                                      const int32_t *__restrict__ dcol, int64_t *isnew,
+                                                      int32_t *aiu, int32_t *aiv, int32_t *aiw, int64_t *aipos,
+                                                      int64_t *cnt) {
     __shared__ BlockScratch sc;
     const uint64_t mask = (1ull << B) - 1;
     int64_t nnew = 0, nign = 0, ndist = 0;
@@ -1100,6 +1129,12 @@ __global__ __launch_bounds__(WIDE_T) void k_classify_inserts(int64_t ni, const u
     block_count<WIDE_T>(&cnt[C_IGNINS], nign, sc);
     block_count<WIDE_T>(&cnt[C_DISTINCT], ndist, sc);
 }
+__global__ __launch_bounds__(WIDE_T) void k_classify_inserts(int64_t ni, const uint64_t *key, int32_t *iw, int B,
+    const int64_t *__restrict__ off, const int32_t *__restrict__ col, const int64_t *__restrict__ doff,
+    const int32_t *__restrict__ dcol, int64_t *isnew, int32_t *aiu, int32_t *aiv, int32_t *aiw, int64_t *aipos,
+    int64_t *cnt) {
+    classify_inserts_body(ni, key, iw, B, off, col, doff, dcol, isnew, aiu, aiv, aiw, aipos, cnt);
+}
 
 __global__ void k_compact_new(int64_t ni, const uint64_t *key, const int32_t *iw, const int64_t *isnew,
                               const int64_t *pos, uint64_t *nkey, int32_t *nw) {
@@ -1108,8 +1143,8 @@ __global__ void k_compact_new(int64_t ni, const uint64_t *key, const int32_t *iw
 }
 
 // TC needs the inserted undirected edges once each.
-__global__ __launch_bounds__(WIDE_T) void k_list_tc_inserts(int64_t na, const int32_t *aiu, const int32_t *aiv,
-                                                            int32_t *tcu, int32_t *tcv, int64_t *cnt) {
+__device__ __forceinline__ void list_tc_inserts_body(int64_t na, const int32_t *aiu, const int32_t *aiv,
+                                                     int32_t *tcu, int32_t *tcv, int64_t *cnt) {
     __shared__ BlockScratch sc;
     for (int64_t c0 = (int64_t)blockIdx.x * WIDE_T; c0 < na; c0 += gstride()) {
         const int64_t i = c0 + threadIdx.x;
@@ -1121,11 +1156,21 @@ __global__ __launch_bounds__(WIDE_T) void k_list_tc_inserts(int64_t na, const in
         }
     }
 }
+__global__ __launch_bounds__(WIDE_T) void k_list_tc_inserts(int64_t na, const int32_t *aiu, const int32_t *aiv,
+                                                            int32_t *tcu, int32_t *tcv, int64_t *cnt) {
+    list_tc_inserts_body(na, aiu, aiv, tcu, tcv, cnt);
+}
+
+// The commits count into slots of their own (KILL_F, KILL_R: C_AUX2 and C_AUX3 relative
+// to them), so that one read after the revivals serves both directions; FILL_F and
+// FILL_R count the hole reuse of a small batch.
+constexpr int KILL_F = 16, KILL_R = 18, FILL_F = 36, FILL_R = 37;
+static_assert(C_AUX3 + KILL_R < FILL_F && C_AUX2 + KILL_F > C_EDGES && FILL_R < C_MAXROW, "slots of their own");
 
 // updateCSRDel, second half: turn the MARKs of applied deletions into tombstones.
-__global__ __launch_bounds__(WIDE_T) void k_commit_deletes(int64_t na, const int32_t *adu, const int64_t *adpos,
-                                                           int32_t *col, int32_t *dcol, int32_t *deg, int32_t *ttomb,
-                                                           int64_t *cnt) {
+__device__ __forceinline__ void commit_deletes_body(int64_t na, const int32_t *adu, const int64_t *adpos,
+                                                    int32_t *col, int32_t *dcol, int32_t *deg, int32_t *ttomb,
+                                                    int64_t *cnt) {
     __shared__ BlockScratch sc;
     int64_t nbase = 0, ndiff = 0;
     for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < na; base += gstride()) {
@@ -1151,12 +1196,17 @@ __global__ __launch_bounds__(WIDE_T) void k_commit_deletes(int64_t na, const int
     block_count<WIDE_T>(&cnt[C_AUX2], nbase, sc);
     block_count<WIDE_T>(&cnt[C_AUX3], ndiff, sc);
 }
+__global__ __launch_bounds__(WIDE_T) void k_commit_deletes(int64_t na, const int32_t *adu, const int64_t *adpos,
+                                                           int32_t *col, int32_t *dcol, int32_t *deg,
+                                                           int32_t *ttomb, int64_t *cnt) {
+    commit_deletes_body(na, adu, adpos, col, dcol, deg, ttomb, cnt);
+}
 
 // Reverse direction of a directed graph: find (v, u) in row v and tombstone it.
-__global__ __launch_bounds__(WIDE_T) void k_commit_deletes_rev(int64_t na, const int32_t *adu, const int32_t *adv,
-                                                               const int64_t *__restrict__ off, int32_t *col,
-                                                               const int64_t *__restrict__ doff, int32_t *dcol,
-                                                               int32_t *deg, int32_t *ttomb, int64_t *cnt) {
+__device__ __forceinline__ void commit_deletes_rev_body(int64_t na, const int32_t *adu, const int32_t *adv,
+                                                        const int64_t *__restrict__ off, int32_t *col,
+                                                        const int64_t *__restrict__ doff, int32_t *dcol,
+                                                        int32_t *deg, int32_t *ttomb, int64_t *cnt) {
     __shared__ BlockScratch sc;
     int64_t nbase = 0, ndiff = 0;
     for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < na; base += gstride()) {
@@ -1184,16 +1234,21 @@ __global__ __launch_bounds__(WIDE_T) void k_commit_deletes_rev(int64_t na, const
     block_count<WIDE_T>(&cnt[C_AUX2], nbase, sc);
     block_count<WIDE_T>(&cnt[C_AUX3], ndiff, sc);
 }
+__global__ __launch_bounds__(WIDE_T) void k_commit_deletes_rev(int64_t na, const int32_t *adu,
+    const int32_t *adv, const int64_t *__restrict__ off, int32_t *col, const int64_t *__restrict__ doff,
+    int32_t *dcol, int32_t *deg, int32_t *ttomb, int64_t *cnt) {
+    commit_deletes_rev_body(na, adu, adv, off, col, doff, dcol, deg, ttomb, cnt);
+}
 
 // updateCSRAdd for slots that already exist: revive a tombstone in place
 // (sorted hole reuse) with the new weight; NEW arcs only bump the degree here.
 // Inserted entries carry MARK until the post-hooks have run.
-__global__ __launch_bounds__(WIDE_T) void k_revive(int64_t na, const int32_t *aiu, const int32_t *aiv,
-                                                   const int32_t *aiw, const int64_t *aipos, int reverse,
-                                                   const int64_t *__restrict__ off, int32_t *col, int32_t *w,
-                                                   const int64_t *__restrict__ doff, int32_t *dcol, int32_t *dw,
-                                                   int32_t *deg, int32_t *ttomb, int B, uint64_t *rkey, int32_t *rw,
-                                                   int64_t *cnt) {
+__device__ __forceinline__ void revive_body(int64_t na, const int32_t *aiu, const int32_t *aiv,
+                                            const int32_t *aiw, const int64_t *aipos, int reverse,
+                                            const int64_t *__restrict__ off, int32_t *col, int32_t *w,
+                                            const int64_t *__restrict__ doff, int32_t *dcol, int32_t *dw,
+                                            int32_t *deg, int32_t *ttomb, int B, uint64_t *rkey, int32_t *rw,
+                                            int64_t *cnt) {
     __shared__ BlockScratch sc;
     int64_t nrev = 0;
     for (int64_t c0 = (int64_t)blockIdx.x * WIDE_T; c0 < na; c0 += gstride()) {
@@ -1236,6 +1291,14 @@ __global__ __launch_bounds__(WIDE_T) void k_revive(int64_t na, const int32_t *ai
     }
     block_count<WIDE_T>(&cnt[C_AUX2], nrev, sc);
 }
+__global__ __launch_bounds__(WIDE_T) void k_revive(int64_t na, const int32_t *aiu, const int32_t *aiv,
+                                                   const int32_t *aiw, const int64_t *aipos, int reverse,
+                                                   const int64_t *__restrict__ off, int32_t *col, int32_t *w,
+                                                   const int64_t *__restrict__ doff, int32_t *dcol, int32_t *dw,
+                                                   int32_t *deg, int32_t *ttomb, int B, uint64_t *rkey,
+                                                   int32_t *rw, int64_t *cnt) {
+    revive_body(na, aiu, aiv, aiw, aipos, reverse, off, col, w, doff, dcol, dw, deg, ttomb, B, rkey, rw, cnt);
+}
 
 // Sorted hole reuse (Section "Modified Graph Representation: diff-CSR": a new edge
 // takes a vacant, tombstoned slot of its row when one is available, and goes to
@@ -1261,8 +1324,9 @@ __device__ __forceinline__ int64_t vacancy_of(const int64_t *__restrict__ off, c
 
 // slot[j] = the base slot NEW key j takes, or -1 (it goes to the diff level);
 // todiff[j] = 1 for the latter (the compaction's flags, with todiff[nk] = 0).
-__global__ void k_vacancy_claim(int64_t nk, const uint64_t *nkey, int B, const int64_t *__restrict__ off,
-                                const int32_t *__restrict__ col, int64_t *slot, int64_t *todiff) {
+__device__ __forceinline__ void vacancy_claim_body(int64_t nk, const uint64_t *nkey, int B,
+                                                   const int64_t *__restrict__ off,
+                                                   const int32_t *__restrict__ col, int64_t *slot, int64_t *todiff) {
     const uint64_t mask = (1ull << B) - 1;
     for (int64_t j = gtid(); j <= nk; j += gstride()) {
         if (j == nk) {
@@ -1279,11 +1343,15 @@ __global__ void k_vacancy_claim(int64_t nk, const uint64_t *nkey, int B, const i
         todiff[j] = c < 0;
     }
 }
+__global__ void k_vacancy_claim(int64_t nk, const uint64_t *nkey, int B, const int64_t *__restrict__ off,
+                                const int32_t *__restrict__ col, int64_t *slot, int64_t *todiff) {
+    vacancy_claim_body(nk, nkey, B, off, col, slot, todiff);
+}
 
 // Write the taken slots (MARKed like every fresh insert until the post-hooks end).
-__global__ __launch_bounds__(WIDE_T) void k_vacancy_fill(int64_t nk, const uint64_t *nkey, const int32_t *nw, int B,
-                                                         const int64_t *slot, int32_t *col, int32_t *w, int32_t *ttomb,
-                                                         int64_t *cnt) {
+__device__ __forceinline__ void vacancy_fill_body(int64_t nk, const uint64_t *nkey, const int32_t *nw, int B,
+                                                  const int64_t *slot, int32_t *col, int32_t *w, int32_t *ttomb,
+                                                  int64_t *cnt) {
     __shared__ BlockScratch sc;
     const uint64_t mask = (1ull << B) - 1;
     int64_t filled = 0;
@@ -1299,6 +1367,11 @@ __global__ __launch_bounds__(WIDE_T) void k_vacancy_fill(int64_t nk, const uint6
     }
     block_count<WIDE_T>(&cnt[C_AUX1], filled, sc);
 }
+__global__ __launch_bounds__(WIDE_T) void k_vacancy_fill(int64_t nk, const uint64_t *nkey, const int32_t *nw,
+                                                         int B, const int64_t *slot, int32_t *col, int32_t *w,
+                                                         int32_t *ttomb, int64_t *cnt) {
+    vacancy_fill_body(nk, nkey, nw, B, slot, col, w, ttomb, cnt);
+}
 
 __global__ void k_vacancy_rest(int64_t nk, const uint64_t *nkey, const int32_t *nw, const int64_t *todiff,
                                const int64_t *pos, uint64_t *okey, int32_t *ow) {
@@ -1307,6 +1380,222 @@ __global__ void k_vacancy_rest(int64_t nk, const uint64_t *nkey, const int32_t *
             okey[pos[j]] = nkey[j];
             ow[pos[j]] = nw[j];
         }
+}
+
+// ---- small batches -----------------------------------------------------------------------
+// A batch of up to SMALL_MAX arcs leaves every kernel above on a few blocks, and its time
+// is the launches: about 30 of them, 5 us each with their gaps, and four host waits.  Such
+// a batch runs the same steps in two launches of one workgroup, one before the
+// pre-hooks and one after them, with its sorts in LDS.  Between steps the workgroup
+// passes a barrier and drops what its L1 holds, as a kernel boundary would.
+constexpr int SMALL_MAX = 4096;
+constexpr int SMALL_ITEMS = SMALL_MAX / WIDE_T;
+constexpr int SMALL_WAVES = WIDE_T / WAVE;
+
+__device__ __forceinline__ void small_step() {
+    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+}
+
+// Stable radix sort of n <= SMALL_MAX pairs by the low `bits` bits, in LDS, eight bits
+// a pass.  Wave w holds keys [w * 64 * items, (w + 1) * 64 * items), item i of lane l
+// being the i * 64 + l th, so ranks taken in item and lane order are stable.
+__device__ void small_sort(int n, int bits, const uint64_t *kin, const int32_t *vin, uint64_t *kout, int32_t *vout) {
+    __shared__ uint64_t s_key[SMALL_MAX];
+    __shared__ int32_t s_val[SMALL_MAX];
+    __shared__ uint16_t s_cnt[SMALL_WAVES][256];
+    __shared__ uint32_t s_start[256], s_tot[4];
+    if (n <= 0) return;  // uniform
+    const int t = threadIdx.x, wv = t / WAVE, l = lane_id();
+    const int items = (n + WIDE_T - 1) / WIDE_T;
+    const int at = wv * items * WAVE + l;
+    uint64_t key[SMALL_ITEMS];
+    int32_t val[SMALL_ITEMS];
+#pragma unroll
+    for (int i = 0; i < SMALL_ITEMS; ++i) {
+        const bool ok = i < items && at + i * WAVE < n;
+        key[i] = ok ? kin[at + i * WAVE] : 0;
+        val[i] = ok ? vin[at + i * WAVE] : 0;
+    }
+    for (int shift = 0; shift < bits; shift += 8) {
+        const uint32_t mask = (1u << min(8, bits - shift)) - 1u;
+        for (int i = t; i < SMALL_WAVES * 256; i += WIDE_T) (&s_cnt[0][0])[i] = 0;
+        __syncthreads();
+        uint32_t rank[SMALL_ITEMS];
+#pragma unroll
+        for (int i = 0; i < SMALL_ITEMS; ++i) {
+            rank[i] = 0;
+            if (i >= items) continue;  // uniform
+            const bool ok = at + i * WAVE < n;
+            const uint32_t d = (uint32_t)(key[i] >> shift) & mask;
+            const uint64_t m = match8(d, ballot(ok));
+            const uint32_t before = (uint32_t)__popcll(m & lanemask_lt());
+            const uint32_t old = ok ? s_cnt[wv][d] : 0;
+            wave_sync();
+            if (ok && before == 0) s_cnt[wv][d] = (uint16_t)(old + (uint32_t)__popcll(m));
+            wave_sync();
+            rank[i] = old + before;
+        }
+        __syncthreads();
+        uint32_t cnt = 0, incl = 0;
+        if (t < 256) {  // thread d: starts of digit d in each wave, then its start
+            for (int w = 0; w < SMALL_WAVES; ++w) {
+                const uint32_t c = s_cnt[w][t];
+                s_cnt[w][t] = (uint16_t)cnt;
+                cnt += c;
+            }
+            incl = wave_incl_scan(cnt);
+            if (l == WAVE - 1) s_tot[wv] = incl;
+        }
+        __syncthreads();
+        if (t < 256) {
+            uint32_t b = incl - cnt;
+            for (int w = 0; w < wv; ++w) b += s_tot[w];
+            s_start[t] = b;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < SMALL_ITEMS; ++i)
+            if (i < items && at + i * WAVE < n) {
+                const uint32_t d = (uint32_t)(key[i] >> shift) & mask;
+                const uint32_t o = s_start[d] + s_cnt[wv][d] + rank[i];
+                s_key[o] = key[i];
+                s_val[o] = val[i];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < SMALL_ITEMS; ++i)
+            if (i < items && at + i * WAVE < n) {
+                key[i] = s_key[at + i * WAVE];
+                val[i] = s_val[at + i * WAVE];
+            }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < SMALL_ITEMS; ++i)
+        if (i < items && at + i * WAVE < n) {
+            kout[at + i * WAVE] = key[i];
+            vout[at + i * WAVE] = val[i];
+        }
+}
+
+// The pairs whose flag is set, in order, to okey / ow (one workgroup).
+__device__ void small_compact(int n, const int64_t *flag, const uint64_t *key, const int32_t *w, uint64_t *okey,
+                              int32_t *ow) {
+    __shared__ BlockScratch sc;
+    int64_t base = 0;
+    for (int c0 = 0; c0 < n; c0 += WIDE_T) {
+        const int i = c0 + (int)threadIdx.x;
+        const bool p = i < n && flag[i];
+        int64_t tot;
+        const int64_t o = base + block_scan_excl<WIDE_T>(p, &tot, sc);
+        if (p) {
+            okey[o] = key[i];
+            ow[o] = w[i];
+        }
+        base += tot;
+    }
+}
+
+struct SmallDir {
+    const int64_t *off, *doff;
+    int32_t *col, *w, *dcol, *dw, *deg, *ttomb;
+};
+struct SmallBatch {
+    int64_t k;
+    const int32_t *src, *dst, *w;
+    const uint8_t *op;
+    int32_t n;
+    int expect, B, und;
+    const int32_t *perm;
+    SmallDir F, R;
+    int32_t *ddu, *ddv, *adu, *adv;
+    int64_t *adpos;
+    uint64_t *ikey, *ikey_s, *rkey, *rkey_s, *nkey, *vkey;
+    int32_t *iw, *iw_s, *rw, *rw_s, *nw, *vw;
+    int32_t *aiu, *aiv, *aiw;
+    int64_t *aipos;
+    int32_t *tcu, *tcv;
+    int64_t *isnew, *slot;
+    int64_t *cnt, *host, *host_seq, seq;
+};
+
+// Validation, split, sort, deletion marks, insert classification and the list of NEW keys.
+__global__ __launch_bounds__(WIDE_T) void k_small_prepare(SmallBatch a) {
+    __shared__ BlockScratch sc;
+    for (int i = threadIdx.x; i < C_ALL; i += WIDE_T)
+        if (i != C_MAXROW && i != C_SORT_ERR) a.cnt[i] = 0;
+    small_step();
+    // counts of deletions, insertions and bad updates, 20 bits each
+    int64_t v = 0;
+    for (int64_t i = threadIdx.x; i < a.k; i += WIDE_T) v += check_update(i, a.src, a.dst, a.w, a.op, a.n, a.expect);
+    int64_t tot;
+    (void)block_scan_excl<WIDE_T>(v, &tot, sc);
+    const int rep = a.und ? 2 : 1;
+    const int nd = (int)(tot & 0xfffff) * rep, ni = (int)(tot >> 20 & 0xfffff) * rep;
+    const bool bad = tot >> 40 != 0;
+    if (threadIdx.x == 0) {
+        a.cnt[C_NDEL] = nd / rep;
+        a.cnt[C_NINS] = ni / rep;
+        if (bad) a.cnt[C_ERR] = 1;
+    }
+    small_step();
+    if (!bad) {  // uniform
+        expand_batch_body(a.k, a.src, a.dst, a.w, a.op, a.B, a.und, a.perm, a.ddu, a.ddv, a.ikey, a.iw, a.cnt);
+        small_step();
+        small_sort(ni, 2 * a.B, a.ikey, a.iw, a.ikey_s, a.iw_s);
+        mark_deletes_body(nd, a.ddu, a.ddv, a.F.off, a.F.col, a.F.doff, a.F.dcol, a.und, a.adu, a.adv, a.adpos, a.tcu,
+                          a.tcv, a.cnt);
+        small_step();
+        classify_inserts_body(ni, a.ikey_s, a.iw_s, a.B, a.F.off, a.F.col, a.F.doff, a.F.dcol, a.isnew, a.aiu, a.aiv,
+                              a.aiw, a.aipos, a.cnt);
+        small_step();
+        small_compact(ni, a.isnew, a.ikey_s, a.iw_s, a.nkey, a.nw);
+        small_step();
+    }
+    if (threadIdx.x < WAVE) counters_publish_body(a.cnt, a.host, a.host_seq, a.seq);
+}
+
+// Hole reuse of one direction (fill_vacancies): the keys left go to okey / ow, the
+// number that found a slot is added to *filled.
+__device__ void small_vacancies(const SmallBatch &a, const SmallDir &d, int nk, const uint64_t *key, const int32_t *w,
+                                uint64_t *okey, int32_t *ow, int64_t *filled) {
+    int64_t *slot = a.slot, *todiff = a.slot + SMALL_MAX + 1;
+    vacancy_claim_body(nk, key, a.B, d.off, d.col, slot, todiff);
+    small_step();
+    vacancy_fill_body(nk, key, w, a.B, slot, d.col, d.w, d.ttomb, filled - C_AUX1);
+    small_compact(nk, todiff, key, w, okey, ow);
+    small_step();
+}
+
+// Deletion commits, revivals, the reverse NEW keys in order and the hole reuse.
+// tomb_f, tomb_r: base tombstones before the batch.
+__global__ __launch_bounds__(WIDE_T) void k_small_update(SmallBatch a, int adel, int ains, int nnew, int tcdel,
+                                                         int64_t tomb_f, int64_t tomb_r, int diff_only) {
+    commit_deletes_body(adel, a.adu, a.adpos, a.F.col, a.F.dcol, a.F.deg, a.F.ttomb, a.cnt + KILL_F);
+    if (!a.und)
+        commit_deletes_rev_body(adel, a.adu, a.adv, a.R.off, a.R.col, a.R.doff, a.R.dcol, a.R.deg, a.R.ttomb,
+                                a.cnt + KILL_R);
+    small_step();
+    revive_body(ains, a.aiu, a.aiv, a.aiw, a.aipos, 0, a.F.off, a.F.col, a.F.w, a.F.doff, a.F.dcol, a.F.dw, a.F.deg,
+                a.F.ttomb, a.B, (uint64_t *)nullptr, (int32_t *)nullptr, a.cnt);
+    if (a.und)
+        list_tc_inserts_body(ains, a.aiu, a.aiv, a.tcu + tcdel, a.tcv + tcdel, a.cnt);
+    else
+        revive_body(ains, a.aiu, a.aiv, a.aiw, a.aipos, 1, a.R.off, a.R.col, a.R.w, a.R.doff, a.R.dcol, a.R.dw,
+                    a.R.deg, a.R.ttomb, a.B, a.rkey, a.rw, a.cnt + 8);
+    small_step();
+    if (nnew > 0 && !diff_only && tomb_f + a.cnt[C_AUX2 + KILL_F] - a.cnt[C_AUX2] > 0)
+        small_vacancies(a, a.F, nnew, a.nkey, a.nw, a.vkey, a.vw, &a.cnt[FILL_F]);
+    if (!a.und) {
+        const int nr = (int)a.cnt[C_AUX1 + 8];
+        small_sort(nr, 2 * a.B, a.rkey, a.rw, a.rkey_s, a.rw_s);
+        small_step();
+        if (nr > 0 && !diff_only && tomb_r + a.cnt[C_AUX2 + KILL_R] - a.cnt[C_AUX2 + 8] > 0)
+            small_vacancies(a, a.R, nr, a.rkey_s, a.rw_s, a.rkey, a.rw, &a.cnt[FILL_R]);
+    }
+    small_step();
+    if (threadIdx.x < WAVE) counters_publish_body(a.cnt, a.host, a.host_seq, a.seq);
 }
 
 // Drop MARK from the entries this chunk inserted.
@@ -1328,7 +1617,7 @@ __global__ void k_clear_marks(int64_t na, const int32_t *aiu, const int32_t *aiv
 
 // Diff rebuild: merge the live old diff entries with the sorted NEW keys (keys
 // are distinct, so each side's output slot is its rank plus the count of smaller
-// keys on the other side) and drop the tombstoned diff entries.
+// keys on the other side) and drop the tombstoned diff entries (rank null: none).
 __global__ void k_live_flags(int64_t dm, const int32_t *dcol, int64_t *flags) {
     for (int64_t i = gtid(); i <= dm; i += gstride())
         flags[i] = i < dm ? !((uint32_t)dcol[i] & DEAD) : 0;
@@ -1339,7 +1628,7 @@ __global__ void k_diff_old(int64_t dm, const uint64_t *dkey, const int32_t *dcol
                            int32_t *dcol2, int32_t *dw2, int64_t cap) {
     for (int64_t i = gtid(); i < dm; i += gstride()) {
         if ((uint32_t)dcol[i] & DEAD) continue;
-        int64_t p = rank[i] + lower_key(nkey, 0, nk, dkey[i]);
+        int64_t p = (rank ? rank[i] : i) + lower_key(nkey, 0, nk, dkey[i]);
         if (p >= cap) continue;
         dkey2[p] = dkey[i];
         dcol2[p] = dcol[i];
@@ -1352,7 +1641,8 @@ __global__ void k_diff_new(int64_t nk, const uint64_t *nkey, const int32_t *nw, 
                            int32_t *dw2, int64_t cap) {
     const uint64_t mask = (1ull << B) - 1;
     for (int64_t j = gtid(); j < nk; j += gstride()) {
-        int64_t p = j + rank[lower_key(dkey, 0, dm, nkey[j])];
+        const int64_t q = lower_key(dkey, 0, dm, nkey[j]);
+        int64_t p = j + (rank ? rank[q] : q);
         if (p >= cap) continue;
         dkey2[p] = nkey[j];
         dcol2[p] = (int32_t)((uint32_t)(nkey[j] & mask) | MARK);
@@ -1371,10 +1661,13 @@ static int diff_rebuild(dg_graph *g, Dir &d, const uint64_t *nkey, const int32_t
     // device) is rare
     if (2 * ((size_t)dm + 1) > ws.scan64.cap)
         DG_TRY(ws.scan64.ensure(std::max(2 * ((size_t)dm + 1), 2 * ws.scan64.cap)));
-    int64_t *flags = ws.scan64.p;
-    int64_t *rank = flags + (dm + 1);
-    hipLaunchKernelGGL(k_live_flags, dim3(grid_for(dm + 1)), dim3(256), 0, s, dm, d.dcol.p, flags);
-    DG_TRY(scan_excl(g, flags, rank, dm + 1));
+    int64_t *rank = nullptr;  // live entries before each one: its index, when all are live
+    if (killed > 0) {
+        int64_t *flags = ws.scan64.p;
+        rank = flags + (dm + 1);
+        hipLaunchKernelGGL(k_live_flags, dim3(grid_for(dm + 1)), dim3(256), 0, s, dm, d.dcol.p, flags);
+        DG_TRY(scan_excl(g, flags, rank, dm + 1));
+    }
     const int64_t live = dm - killed;
     const int64_t dm2 = live + nk;
     if ((size_t)dm2 + 1 > d.dkey2.cap) {
@@ -1522,55 +1815,87 @@ int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, 
             dw = ws.bw.p;
         }
     }
-    // ---- validate and count (no change to the graph before this passes)
-    DG_TRY(counters_clear(g));
-    hipLaunchKernelGGL(k_validate_batch, dim3(grid_wide(k)), dim3(WIDE_T), 0, s, k, ds, dd, dw, dop, g->n,
-                       expect_op, ws.dcnt);
-    DG_HIP(hipGetLastError());
-    DG_TRY(counters_read(g));
-    if (ws.hcnt[C_ERR]) {
+    const int rep = und ? 2 : 1;
+    const int32_t *perm = g->relabeled ? g->perm.p : nullptr;  // caller's ids to internal ids
+    const bool small = k * rep <= SMALL_MAX;
+    // work arrays for nd deletion and ni insertion arcs
+    auto reserve = [&](int64_t nd, int64_t ni) -> int {
+        DG_TRY(ws.ddu.ensure(nd + 1)); DG_TRY(ws.ddv.ensure(nd + 1));
+        DG_TRY(ws.adu.ensure(nd + 1)); DG_TRY(ws.adv.ensure(nd + 1)); DG_TRY(ws.adpos.ensure(nd + 1));
+        DG_TRY(ws.ikey.ensure(ni + 1)); DG_TRY(ws.ikey_s.ensure(ni + 1));
+        DG_TRY(ws.iw.ensure(ni + 1)); DG_TRY(ws.iw_s.ensure(ni + 1));
+        DG_TRY(ws.aiu.ensure(ni + 1)); DG_TRY(ws.aiv.ensure(ni + 1)); DG_TRY(ws.aiw.ensure(ni + 1));
+        DG_TRY(ws.aipos.ensure(ni + 1));
+        DG_TRY(ws.nkey.ensure(ni + 1)); DG_TRY(ws.nw.ensure(ni + 1));
+        DG_TRY(ws.rkey.ensure(ni + 1)); DG_TRY(ws.rkey_s.ensure(ni + 1));
+        DG_TRY(ws.rw.ensure(ni + 1)); DG_TRY(ws.rw_s.ensure(ni + 1));
+        DG_TRY(ws.tcu.ensure(nd + ni + 1)); DG_TRY(ws.tcv.ensure(nd + ni + 1));
+        DG_TRY(ws.scan64.ensure(2 * ((size_t)ni + 1)));
+        return DG_OK;
+    };
+    auto reject = [&]() -> int {
         t_val.stop();
         t_all.stop();
         DG_TRY(plog.finish());
         return set_error(DG_EINVAL, "batch holds a self-loop, an id outside [0,n), an op other than 0/1 (or "
                                     "other than the partially dynamic mode's) or a weight outside [1,2^30)");
-    }
-    const int rep = und ? 2 : 1;
-    const int64_t nda = ws.hcnt[C_NDEL] * rep, nia = ws.hcnt[C_NINS] * rep;
-    DG_TRY(ws.ddu.ensure(nda + 1)); DG_TRY(ws.ddv.ensure(nda + 1));
-    DG_TRY(ws.adu.ensure(nda + 1)); DG_TRY(ws.adv.ensure(nda + 1)); DG_TRY(ws.adpos.ensure(nda + 1));
-    DG_TRY(ws.ikey.ensure(nia + 1)); DG_TRY(ws.ikey_s.ensure(nia + 1));
-    DG_TRY(ws.iw.ensure(nia + 1)); DG_TRY(ws.iw_s.ensure(nia + 1));
-    DG_TRY(ws.aiu.ensure(nia + 1)); DG_TRY(ws.aiv.ensure(nia + 1)); DG_TRY(ws.aiw.ensure(nia + 1));
-    DG_TRY(ws.aipos.ensure(nia + 1));
-    DG_TRY(ws.nkey.ensure(nia + 1)); DG_TRY(ws.nw.ensure(nia + 1));
-    DG_TRY(ws.rkey.ensure(nia + 1)); DG_TRY(ws.rkey_s.ensure(nia + 1));
-    DG_TRY(ws.rw.ensure(nia + 1)); DG_TRY(ws.rw_s.ensure(nia + 1));
-    DG_TRY(ws.tcu.ensure(nda + nia + 1)); DG_TRY(ws.tcv.ensure(nda + nia + 1));
-    DG_TRY(ws.scan64.ensure(2 * ((size_t)nia + 1)));
-    const int32_t *perm = g->relabeled ? g->perm.p : nullptr;  // caller's ids to internal ids
-    hipLaunchKernelGGL(k_expand_batch, dim3(grid_wide(k)), dim3(WIDE_T), 0, s, k, ds, dd, dw, dop, B, (int)und, perm,
-                       ws.ddu.p, ws.ddv.p, ws.ikey.p, ws.iw.p, ws.dcnt);
-    DG_HIP(hipGetLastError());
-    DG_TRY(sort_pairs(g, ws.ikey.p, ws.ikey_s.p, ws.iw.p, ws.iw_s.p, nia, 2 * B));
-    // ---- updateCSRDel (mark) and insert classification against the old graph
-    if (nda > 0)
-        hipLaunchKernelGGL(k_mark_deletes, dim3(grid_wide(nda)), dim3(WIDE_T), 0, s, nda, ws.ddu.p, ws.ddv.p,
-                           F.off.p, F.col.p, F.doff.p, F.dcol.p, (int)und, ws.adu.p, ws.adv.p, ws.adpos.p,
-                           ws.tcu.p, ws.tcv.p, ws.dcnt);
-    int64_t *isnew = ws.scan64.p, *newpos = ws.scan64.p + (nia + 1);
-    if (nia > 0)
-        hipLaunchKernelGGL(k_classify_inserts, dim3(grid_wide(nia)), dim3(WIDE_T), 0, s, nia, ws.ikey_s.p,
-                           ws.iw_s.p, B, F.off.p, F.col.p, F.doff.p, F.dcol.p, isnew, ws.aiu.p,
-                           ws.aiv.p, ws.aiw.p, ws.aipos.p, ws.dcnt);
-    DG_HIP(hipGetLastError());
-    if (nia > 0) {
-        DG_TRY(scan_excl(g, isnew, newpos, nia));
-        hipLaunchKernelGGL(k_compact_new, dim3(grid_for(nia)), dim3(256), 0, s, nia, ws.ikey_s.p,
-                           ws.iw_s.p, isnew, newpos, ws.nkey.p, ws.nw.p);
+    };
+    int64_t nda, nia;  // deletion and insertion arcs given
+    SmallBatch sb{};
+    // ---- validate and count (no change to the graph before this passes), then
+    // updateCSRDel (mark) and insert classification against the old graph
+    if (small) {
+        DG_TRY(reserve(k * rep, k * rep));
+        DG_TRY(ws.vslot.ensure(2 * ((size_t)SMALL_MAX + 1)));
+        DG_TRY(ws.vkey.ensure(SMALL_MAX + 1));
+        DG_TRY(ws.vw.ensure(SMALL_MAX + 1));
+        auto dir = [](Dir &d) {
+            return SmallDir{d.off.p, d.doff.p, d.col.p, d.w.p, d.dcol.p, d.dw.p, d.deg.p, d.ttomb.p};
+        };
+        sb = SmallBatch{k, ds, dd, dw, dop, g->n, expect_op, B, (int)und, perm, dir(F), dir(R),
+                        ws.ddu.p, ws.ddv.p, ws.adu.p, ws.adv.p, ws.adpos.p,
+                        ws.ikey.p, ws.ikey_s.p, ws.rkey.p, ws.rkey_s.p, ws.nkey.p, ws.vkey.p,
+                        ws.iw.p, ws.iw_s.p, ws.rw.p, ws.rw_s.p, ws.nw.p, ws.vw.p,
+                        ws.aiu.p, ws.aiv.p, ws.aiw.p, ws.aipos.p, ws.tcu.p, ws.tcv.p,
+                        ws.scan64.p, ws.vslot.p, ws.dcnt, ws.hcnt, ws.hcnt + H_SEQ, ++ws.seq};
+        hipLaunchKernelGGL(k_small_prepare, dim3(1), dim3(WIDE_T), 0, s, sb);
         DG_HIP(hipGetLastError());
+        DG_TRY(counters_wait(g));
+        if (ws.hcnt[C_ERR]) return reject();
+        nda = ws.hcnt[C_NDEL] * rep;
+        nia = ws.hcnt[C_NINS] * rep;
+    } else {
+        DG_TRY(counters_clear(g));
+        hipLaunchKernelGGL(k_validate_batch, dim3(grid_wide(k)), dim3(WIDE_T), 0, s, k, ds, dd, dw, dop, g->n,
+                           expect_op, ws.dcnt);
+        DG_HIP(hipGetLastError());
+        DG_TRY(counters_read(g));
+        if (ws.hcnt[C_ERR]) return reject();
+        nda = ws.hcnt[C_NDEL] * rep;
+        nia = ws.hcnt[C_NINS] * rep;
+        DG_TRY(reserve(nda, nia));
+        hipLaunchKernelGGL(k_expand_batch, dim3(grid_wide(k)), dim3(WIDE_T), 0, s, k, ds, dd, dw, dop, B, (int)und,
+                           perm, ws.ddu.p, ws.ddv.p, ws.ikey.p, ws.iw.p, ws.dcnt);
+        DG_HIP(hipGetLastError());
+        DG_TRY(sort_pairs(g, ws.ikey.p, ws.ikey_s.p, ws.iw.p, ws.iw_s.p, nia, 2 * B));
+        if (nda > 0)
+            hipLaunchKernelGGL(k_mark_deletes, dim3(grid_wide(nda)), dim3(WIDE_T), 0, s, nda, ws.ddu.p, ws.ddv.p,
+                               F.off.p, F.col.p, F.doff.p, F.dcol.p, (int)und, ws.adu.p, ws.adv.p, ws.adpos.p,
+                               ws.tcu.p, ws.tcv.p, ws.dcnt);
+        int64_t *isnew = ws.scan64.p, *newpos = ws.scan64.p + (nia + 1);
+        if (nia > 0)
+            hipLaunchKernelGGL(k_classify_inserts, dim3(grid_wide(nia)), dim3(WIDE_T), 0, s, nia, ws.ikey_s.p,
+                               ws.iw_s.p, B, F.off.p, F.col.p, F.doff.p, F.dcol.p, isnew, ws.aiu.p, ws.aiv.p,
+                               ws.aiw.p, ws.aipos.p, ws.dcnt);
+        DG_HIP(hipGetLastError());
+        if (nia > 0) {
+            DG_TRY(scan_excl(g, isnew, newpos, nia));
+            hipLaunchKernelGGL(k_compact_new, dim3(grid_for(nia)), dim3(256), 0, s, nia, ws.ikey_s.p, ws.iw_s.p,
+                               isnew, newpos, ws.nkey.p, ws.nw.p);
+            DG_HIP(hipGetLastError());
+        }
+        DG_TRY(counters_read(g));
     }
-    DG_TRY(counters_read(g));
     const int64_t adel = ws.hcnt[C_ADEL], ains = ws.hcnt[C_AINS], nnew = ws.hcnt[C_NEW];
     const int64_t tcdel = ws.hcnt[C_TCDEL];
     t_val.stop();
@@ -1594,35 +1919,39 @@ int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, 
     }
 
     // ---- commit deletions, revive slots, rebuild the diff (both directions)
-    // The commits count into slots of their own (KILL_F, KILL_R: C_AUX2 and C_AUX3
-    // relative to them), so one read after the revivals serves both passes.
     PhaseTimer t_upd(plog, &st->t_update_ms);
-    constexpr int KILL_F = 16, KILL_R = 18;  // counts at 32..35, clear of every other use
-    static_assert(C_AUX3 + KILL_R < C_SORT_ERR && C_AUX2 + KILL_F > C_EDGES, "kill counts have free slots");
-    if (adel > 0) {
-        hipLaunchKernelGGL(k_commit_deletes, dim3(grid_wide(adel)), dim3(WIDE_T), 0, s, adel, ws.adu.p,
-                           ws.adpos.p, F.col.p, F.dcol.p, F.deg.p, F.ttomb.p, ws.dcnt + KILL_F);
-        if (!und)
-            hipLaunchKernelGGL(k_commit_deletes_rev, dim3(grid_wide(adel)), dim3(WIDE_T), 0, s, adel, ws.adu.p,
-                               ws.adv.p, R.off.p, R.col.p, R.doff.p, R.dcol.p, R.deg.p, R.ttomb.p,
-                               ws.dcnt + KILL_R);
-    }
-    if (ains > 0) {
-        hipLaunchKernelGGL(k_revive, dim3(grid_wide(ains)), dim3(WIDE_T), 0, s, ains, ws.aiu.p, ws.aiv.p,
-                           ws.aiw.p, ws.aipos.p, 0, F.off.p, F.col.p, F.w.p, F.doff.p, F.dcol.p, F.dw.p,
-                           F.deg.p, F.ttomb.p, B, (uint64_t *)nullptr, (int32_t *)nullptr,
-                           ws.dcnt);
-        if (!und)
+    if (small) {
+        sb.seq = ++ws.seq;
+        hipLaunchKernelGGL(k_small_update, dim3(1), dim3(WIDE_T), 0, s, sb, (int)adel, (int)ains, (int)nnew,
+                           (int)tcdel, F.tomb_base, R.tomb_base, (int)(g->cfg.diff_only != 0));
+        DG_HIP(hipGetLastError());
+        DG_TRY(counters_wait(g));
+    } else {
+        if (adel > 0) {
+            hipLaunchKernelGGL(k_commit_deletes, dim3(grid_wide(adel)), dim3(WIDE_T), 0, s, adel, ws.adu.p,
+                               ws.adpos.p, F.col.p, F.dcol.p, F.deg.p, F.ttomb.p, ws.dcnt + KILL_F);
+            if (!und)
+                hipLaunchKernelGGL(k_commit_deletes_rev, dim3(grid_wide(adel)), dim3(WIDE_T), 0, s, adel, ws.adu.p,
+                                   ws.adv.p, R.off.p, R.col.p, R.doff.p, R.dcol.p, R.deg.p, R.ttomb.p,
+                                   ws.dcnt + KILL_R);
+        }
+        if (ains > 0) {
             hipLaunchKernelGGL(k_revive, dim3(grid_wide(ains)), dim3(WIDE_T), 0, s, ains, ws.aiu.p, ws.aiv.p,
-                               ws.aiw.p, ws.aipos.p, 1, R.off.p, R.col.p, R.w.p, R.doff.p, R.dcol.p,
-                               R.dw.p, R.deg.p, R.ttomb.p, B, ws.rkey.p, ws.rw.p,
-                               ws.dcnt + 8);
-        if (und)
-            hipLaunchKernelGGL(k_list_tc_inserts, dim3(grid_wide(ains)), dim3(WIDE_T), 0, s, ains, ws.aiu.p,
-                               ws.aiv.p, ws.tcu.p + tcdel, ws.tcv.p + tcdel, ws.dcnt);
+                               ws.aiw.p, ws.aipos.p, 0, F.off.p, F.col.p, F.w.p, F.doff.p, F.dcol.p, F.dw.p,
+                               F.deg.p, F.ttomb.p, B, (uint64_t *)nullptr, (int32_t *)nullptr,
+                               ws.dcnt);
+            if (!und)
+                hipLaunchKernelGGL(k_revive, dim3(grid_wide(ains)), dim3(WIDE_T), 0, s, ains, ws.aiu.p, ws.aiv.p,
+                                   ws.aiw.p, ws.aipos.p, 1, R.off.p, R.col.p, R.w.p, R.doff.p, R.dcol.p,
+                                   R.dw.p, R.deg.p, R.ttomb.p, B, ws.rkey.p, ws.rw.p,
+                                   ws.dcnt + 8);
+            if (und)
+                hipLaunchKernelGGL(k_list_tc_inserts, dim3(grid_wide(ains)), dim3(WIDE_T), 0, s, ains, ws.aiu.p,
+                                   ws.aiv.p, ws.tcu.p + tcdel, ws.tcv.p + tcdel, ws.dcnt);
+        }
+        DG_HIP(hipGetLastError());
+        DG_TRY(counters_read(g));
     }
-    DG_HIP(hipGetLastError());
-    DG_TRY(counters_read(g));
     const int64_t killed_base_f = ws.hcnt[C_AUX2 + KILL_F], killed_diff_f = ws.hcnt[C_AUX3 + KILL_F];
     const int64_t killed_base_r = und ? 0 : ws.hcnt[C_AUX2 + KILL_R];
     const int64_t killed_diff_r = und ? 0 : ws.hcnt[C_AUX3 + KILL_R];
@@ -1633,21 +1962,35 @@ int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, 
     const int64_t nnew_r = und ? 0 : ws.hcnt[C_AUX1 + 8];
     const int64_t tcins = ws.hcnt[C_TCINS];
     F.tomb_base += killed_base_f - revived_base_f;
-    {
+    if (small) {
+        // the keys left for the diff level: all of them where there was no hole to take
+        auto rebuild = [&](Dir &d, const uint64_t *key, const int32_t *w2, const uint64_t *left, const int32_t *left_w,
+                           int64_t nk, int64_t filled, int64_t killed) -> int {
+            const bool reuse = nk > 0 && !g->cfg.diff_only && d.tomb_base > 0;
+            d.tomb_base -= filled;
+            return diff_rebuild(g, d, reuse ? left : key, reuse ? left_w : w2, nk - filled, killed);
+        };
+        const int64_t filled_f = ws.hcnt[FILL_F], filled_r = ws.hcnt[FILL_R];
+        DG_TRY(rebuild(F, ws.nkey.p, ws.nw.p, ws.vkey.p, ws.vw.p, nnew, filled_f, killed_diff_f));
+        if (!und) {
+            R.tomb_base += killed_base_r - revived_base_r;
+            DG_TRY(rebuild(R, ws.rkey_s.p, ws.rw_s.p, ws.rkey.p, ws.rw.p, nnew_r, filled_r, killed_diff_r));
+        }
+    } else {
         const uint64_t *fk;
         const int32_t *fw;
         int64_t fn;
         DG_TRY(fill_vacancies(g, F, ws.nkey.p, ws.nw.p, nnew, &fk, &fw, &fn));
         DG_TRY(diff_rebuild(g, F, fk, fw, fn, killed_diff_f));
-    }
-    if (!und) {
-        R.tomb_base += killed_base_r - revived_base_r;
-        DG_TRY(sort_pairs(g, ws.rkey.p, ws.rkey_s.p, ws.rw.p, ws.rw_s.p, nnew_r, 2 * B));
-        const uint64_t *rk;
-        const int32_t *rw;
-        int64_t rn;
-        DG_TRY(fill_vacancies(g, R, ws.rkey_s.p, ws.rw_s.p, nnew_r, &rk, &rw, &rn));
-        DG_TRY(diff_rebuild(g, R, rk, rw, rn, killed_diff_r));
+        if (!und) {
+            R.tomb_base += killed_base_r - revived_base_r;
+            DG_TRY(sort_pairs(g, ws.rkey.p, ws.rkey_s.p, ws.rw.p, ws.rw_s.p, nnew_r, 2 * B));
+            const uint64_t *rk;
+            const int32_t *rw;
+            int64_t rn;
+            DG_TRY(fill_vacancies(g, R, ws.rkey_s.p, ws.rw_s.p, nnew_r, &rk, &rw, &rn));
+            DG_TRY(diff_rebuild(g, R, rk, rw, rn, killed_diff_r));
+        }
     }
     g->m_live += ains - adel;
     t_upd.stop();

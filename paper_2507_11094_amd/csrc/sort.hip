@@ -136,18 +136,6 @@ __device__ __forceinline__ uint32_t take_tile(uint32_t *ctr, uint32_t *s_tile) {
     return *s_tile;
 }
 
-// Lanes of the wave whose d (8 bits) equals this lane's, among `active`.
-__device__ __forceinline__ uint64_t match8(uint32_t d, uint64_t active) {
-    uint64_t m = active;
-#pragma unroll
-    for (int b = 0; b < RS_BITS; ++b) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t bb = ballot(bit);
-        m &= bit ? bb : ~bb;
-    }
-    return m;
-}
-
 // ---- radix sort kernels -----------------------------------------------------------------
 
 // Digit counts of every pass, added to ghist[pass][digit].

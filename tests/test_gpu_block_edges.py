@@ -97,3 +97,49 @@ def test_build_order_and_directions(dg, n, m, und):
     want, _, _ = oracle.pagerank(n, as_, ad, 0.85, 1e-9, 1000)
     assert np.max(np.abs(G.pr_static(0.85, 1e-9, 1000)[0] - want)) <= 1e-10
     G.close()
+
+
+# batches around the limit of the one-workgroup path, in every mode, over several batches
+# (revivals and reused slots)
+@pytest.mark.parametrize("und", [False, True])
+@pytest.mark.parametrize("k", [1, 63, 65, 1023, 1025, 2047, 2048, 2049, 4095, 4096, 4097])
+@pytest.mark.parametrize("diff_only", [0, 1])
+def test_small_batch_sequences(dg, k, und, diff_only):
+    rng = np.random.default_rng(7 * k + und)
+    n = 3001
+    if und:
+        _, s, d = graphgen.rmat_undirected(12, 20000, 5)
+    else:
+        _, s, d, _ = graphgen.rmat_directed(12, 30000, 5)
+    keep = (s < n) & (d < n)
+    s, d = s[keep], d[keep]
+    w = rng.integers(1, 100, s.size).astype(np.int32)
+    c = dg.Config()
+    c.diff_only = diff_only
+    G = dg.Graph(n, s, d, w, undirected=und, config=c)
+    q = G.tc_attach() if und else G.sssp_attach(0)
+    for step in range(4):
+        # half existing edges, half random pairs, random ops, each pair once
+        i = rng.integers(0, s.size, k)
+        a, b = rng.integers(0, n, k), rng.integers(0, n, k)
+        old = rng.random(k) < 0.5
+        bs, bd = np.where(old, s[i], a), np.where(old, d[i], b)
+        bd = np.where(bs == bd, (bd + 1) % n, bd)
+        op = rng.integers(0, 2, k)
+        one = np.unique(np.minimum(bs, bd) * n + np.maximum(bs, bd) if und else bs * n + bd, return_index=True)[1]
+        bs, bd, op = bs[one], bd[one], op[one]
+        bw = rng.integers(1, 100, bs.size)
+        if und:  # weights of an undirected pair are not part of the comparison
+            bw[:] = 1
+        batch = (bs.astype(np.int32), bd.astype(np.int32), bw.astype(np.int32), op.astype(np.uint8))
+        G.apply(*batch)
+        s, d, w, _ = oracle.apply(n, s, d, w, *batch, undirected=und)
+        es, ed, ew = G.export()
+        o = np.argsort(s.astype(np.int64) << 32 | d)
+        assert np.array_equal(es, s[o]) and np.array_equal(ed, d[o])
+        if und:
+            assert q.read() == oracle.triangles(n, s, d)
+        else:
+            assert np.array_equal(ew, w[o])
+            assert np.array_equal(q.read()[0], oracle.sssp(n, s, d, w, 0))
+    G.close()
