@@ -1250,7 +1250,7 @@ __device__ __forceinline__ void revive_body(int64_t na, const int32_t *aiu, cons
                                             int32_t *deg, int32_t *ttomb, int B, uint64_t *rkey, int32_t *rw,
                                             int64_t *cnt) {
     __shared__ BlockScratch sc;
-    int64_t nrev = 0;
+    int64_t nrev = 0, ndiff = 0;  // revived base and diff entries
     for (int64_t c0 = (int64_t)blockIdx.x * WIDE_T; c0 < na; c0 += gstride()) {
         const int64_t i = c0 + threadIdx.x;
         const bool ok = i < na;
@@ -1272,6 +1272,7 @@ __device__ __forceinline__ void revive_body(int64_t na, const int32_t *aiu, cons
         } else if (p <= -2) {
             dcol[-2 - p] = (int32_t)(c | MARK);
             dw[-2 - p] = wt;
+            ++ndiff;
         }
         // degree bumps are summed over neighbouring lanes of one row (insertions come
         // sorted by row in the forward direction)
@@ -1290,6 +1291,7 @@ __device__ __forceinline__ void revive_body(int64_t na, const int32_t *aiu, cons
         }
     }
     block_count<WIDE_T>(&cnt[C_AUX2], nrev, sc);
+    block_count<WIDE_T>(&cnt[C_AUX3], ndiff, sc);
 }
 __global__ __launch_bounds__(WIDE_T) void k_revive(int64_t na, const int32_t *aiu, const int32_t *aiv,
                                                    const int32_t *aiw, const int64_t *aipos, int reverse,
@@ -1952,9 +1954,12 @@ int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, 
         DG_HIP(hipGetLastError());
         DG_TRY(counters_read(g));
     }
-    const int64_t killed_base_f = ws.hcnt[C_AUX2 + KILL_F], killed_diff_f = ws.hcnt[C_AUX3 + KILL_F];
+    const int64_t killed_base_f = ws.hcnt[C_AUX2 + KILL_F];
     const int64_t killed_base_r = und ? 0 : ws.hcnt[C_AUX2 + KILL_R];
-    const int64_t killed_diff_r = und ? 0 : ws.hcnt[C_AUX3 + KILL_R];
+    // diff entries that died and were not revived: the level holds live ones only
+    // between batches, so each revival there undoes a deletion of this batch
+    const int64_t killed_diff_f = ws.hcnt[C_AUX3 + KILL_F] - ws.hcnt[C_AUX3];
+    const int64_t killed_diff_r = und ? 0 : ws.hcnt[C_AUX3 + KILL_R] - ws.hcnt[C_AUX3 + 8];
     const int64_t revived_base_f = ws.hcnt[C_AUX2];
     const int64_t revived_base_r = und ? 0 : ws.hcnt[C_AUX2 + 8];
     // arcs new to the reverse store: the forward NEW arcs plus revivals whose reverse

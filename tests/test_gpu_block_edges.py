@@ -100,7 +100,7 @@ def test_build_order_and_directions(dg, n, m, und):
 
 
 # batches around the limit of the one-workgroup path, in every mode, over several batches
-# (revivals and reused slots)
+# (revivals, reused slots, repeats within a batch, deletions with re-insertions)
 @pytest.mark.parametrize("und", [False, True])
 @pytest.mark.parametrize("k", [1, 63, 65, 1023, 1025, 2047, 2048, 2049, 4095, 4096, 4097])
 @pytest.mark.parametrize("diff_only", [0, 1])
@@ -119,16 +119,17 @@ def test_small_batch_sequences(dg, k, und, diff_only):
     G = dg.Graph(n, s, d, w, undirected=und, config=c)
     q = G.tc_attach() if und else G.sssp_attach(0)
     for step in range(4):
-        # half existing edges, half random pairs, random ops, each pair once
+        # half existing edges, half random pairs, some of them repeated, random ops
         i = rng.integers(0, s.size, k)
         a, b = rng.integers(0, n, k), rng.integers(0, n, k)
         old = rng.random(k) < 0.5
         bs, bd = np.where(old, s[i], a), np.where(old, d[i], b)
+        rep = rng.integers(0, k, k)
+        again = rng.random(k) < 0.1
+        bs, bd = np.where(again, bs[rep], bs), np.where(again, bd[rep], bd)
         bd = np.where(bs == bd, (bd + 1) % n, bd)
         op = rng.integers(0, 2, k)
-        one = np.unique(np.minimum(bs, bd) * n + np.maximum(bs, bd) if und else bs * n + bd, return_index=True)[1]
-        bs, bd, op = bs[one], bd[one], op[one]
-        bw = rng.integers(1, 100, bs.size)
+        bw = rng.integers(1, 100, k)
         if und:  # weights of an undirected pair are not part of the comparison
             bw[:] = 1
         batch = (bs.astype(np.int32), bd.astype(np.int32), bw.astype(np.int32), op.astype(np.uint8))
