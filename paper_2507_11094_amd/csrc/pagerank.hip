@@ -277,6 +277,75 @@ constexpr double EX_MAX_LAM = 0.9;  // no move for slower ratios (factor <= 9)
 constexpr int EX_TRACK = 24;        // plain steps without a move before the fits stop
 constexpr int EX_LAG2_AFTER = 4;    // plain steps without a move before s_{k-2} is kept,
 constexpr double EX_LAG2_RES = 0.95;  // and the one-step fit explaining at most 5 % of |s_k|^2
+// One thread, with the step's L1 size and the new dangling mass in prs[0] and prs[1] and,
+// where the apply kept the step vector (fit), the sums of the fits.
+__device__ __forceinline__ void pr_decide(bool fit, double sq, double dot, double dot2, int global, double S,
+                                          double damp, double ninv, double tol, int first, int extrap, double *prs,
+                                          double *step_out) {
+    // S < 0: the conserved mass is prs[13], set by the set-up call (first) to the
+    // sum of the start vector (prs[0] then), and tol is relative to it
+    if (first && S < 0.0) prs[13] = prs[0];
+    if (S < 0.0) {
+        S = prs[13];
+        tol *= prs[13];
+    }
+    prs[2] = global ? ((1.0 - damp) * S + damp * prs[1]) * ninv : (1.0 - damp) * ninv;
+    *step_out = prs[0];
+    if (first) {
+        prs[3] = 0.0;
+        prs[4] = 0.0;
+        for (int k = 6; k <= 10; ++k) prs[k] = 0.0;
+        prs[11] = extrap ? 1.0 : 0.0;
+        prs[12] = 0.0;
+        prs[14] = 0.0;
+        prs[15] = 0.0;
+        return;
+    }
+    prs[4] += 1.0;
+    const double step = prs[0];
+    const bool moved = prs[8] != 0.0;
+    prs[8] = 0.0;
+    prs[14] = 0.0;
+    if (moved) {
+        // the step just taken moved further than Jacobi: the fits start again
+        prs[6] = 0.0;
+        prs[7] = 0.0;
+        prs[9] = 0.0;
+        prs[12] = 0.0;
+        prs[11] = extrap ? 1.0 : 0.0;
+        return;
+    }
+    if (step <= tol) {
+        prs[3] = 1.0;
+        return;
+    }
+    if (!fit) return;
+    prs[9] += 1.0;
+    const bool lag2 = prs[15] != 0.0;  // the apply just run kept s_{k-2} as well
+    const double s2 = sq, sd = dot, sd2 = dot2, p2 = prs[6], q2 = prs[12];
+    const double lam = p2 > 0.0 ? sd / p2 : 0.0;
+    const bool aligned = p2 > 0.0 && s2 - sd * lam <= EX_FIT * EX_FIT * s2;
+    const double mu = q2 > 0.0 ? sd2 / q2 : 0.0;
+    const bool aligned2 = q2 > 0.0 && s2 - sd2 * mu <= EX_FIT2 * EX_FIT2 * s2;
+    if (aligned && lam > 0.0 && lam <= EX_MAX_LAM && prs[9] >= 2.0 && lam * step > 2.0 * tol) {
+        prs[8] = lam / (1.0 - lam);
+        prs[10] += 1.0;
+    } else if (aligned2 && mu > 0.0 && mu <= EX_MAX_LAM * EX_MAX_LAM && mu * step > 2.0 * tol) {
+        prs[8] = mu / (1.0 - mu);
+        prs[14] = 1.0;
+        prs[10] += 1.0;
+    }
+    prs[7] = aligned ? lam : 0.0;
+    prs[12] = lag2 ? p2 : 0.0;  // the apply just run stored s_{k-1} as the older vector
+    prs[6] = s2;
+    if (prs[9] >= (double)EX_LAG2_AFTER && p2 > 0.0 && s2 - sd * lam >= EX_LAG2_RES * s2) prs[15] = 1.0;
+    // a two-step move needs the step vector in the next apply: tracking stops
+    // only on a step that decided no move, after EX_TRACK plain steps or once
+    // the step is too small for any move (the move tests above fail for it)
+    if (prs[8] == 0.0 && (prs[9] >= (double)EX_TRACK || EX_MAX_LAM * EX_MAX_LAM * step <= 2.0 * tol))
+        prs[11] = 0.0;
+}
+
 __device__ __forceinline__ void pr_reduce_body(const double *partials, const double *partials2, int np, int global,
                                                double S, double damp, double ninv, double tol, int first, int extrap,
                                                double *prs, double *step_out) {
@@ -298,70 +367,9 @@ __device__ __forceinline__ void pr_reduce_body(const double *partials, const dou
         block_sum_more<3>(v, fs);
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        // S < 0: the conserved mass is prs[13], set by the set-up call (first) to the
-        // sum of the start vector (prs[0] then), and tol is relative to it
-        if (first && S < 0.0) prs[13] = prs[0];
-        if (S < 0.0) {
-            S = prs[13];
-            tol *= prs[13];
-        }
-        prs[2] = global ? ((1.0 - damp) * S + damp * prs[1]) * ninv : (1.0 - damp) * ninv;
-        *step_out = prs[0];
-        if (first) {
-            prs[3] = 0.0;
-            prs[4] = 0.0;
-            for (int k = 6; k <= 10; ++k) prs[k] = 0.0;
-            prs[11] = extrap ? 1.0 : 0.0;
-            prs[12] = 0.0;
-            prs[14] = 0.0;
-            prs[15] = 0.0;
-            return;
-        }
-        prs[4] += 1.0;
-        const double step = prs[0];
-        const bool moved = prs[8] != 0.0;
-        prs[8] = 0.0;
-        prs[14] = 0.0;
-        if (moved) {
-            // the step just taken moved further than Jacobi: the fits start again
-            prs[6] = 0.0;
-            prs[7] = 0.0;
-            prs[9] = 0.0;
-            prs[12] = 0.0;
-            prs[11] = extrap ? 1.0 : 0.0;
-            return;
-        }
-        if (step <= tol) {
-            prs[3] = 1.0;
-            return;
-        }
-        if (!fit) return;
-        prs[9] += 1.0;
-        const bool lag2 = prs[15] != 0.0;  // the apply just run kept s_{k-2} as well
-        const double s2 = fs[0], sd = fs[1], sd2 = fs[2], p2 = prs[6], q2 = prs[12];
-        const double lam = p2 > 0.0 ? sd / p2 : 0.0;
-        const bool aligned = p2 > 0.0 && s2 - sd * lam <= EX_FIT * EX_FIT * s2;
-        const double mu = q2 > 0.0 ? sd2 / q2 : 0.0;
-        const bool aligned2 = q2 > 0.0 && s2 - sd2 * mu <= EX_FIT2 * EX_FIT2 * s2;
-        if (aligned && lam > 0.0 && lam <= EX_MAX_LAM && prs[9] >= 2.0 && lam * step > 2.0 * tol) {
-            prs[8] = lam / (1.0 - lam);
-            prs[10] += 1.0;
-        } else if (aligned2 && mu > 0.0 && mu <= EX_MAX_LAM * EX_MAX_LAM && mu * step > 2.0 * tol) {
-            prs[8] = mu / (1.0 - mu);
-            prs[14] = 1.0;
-            prs[10] += 1.0;
-        }
-        prs[7] = aligned ? lam : 0.0;
-        prs[12] = lag2 ? p2 : 0.0;  // the apply just run stored s_{k-1} as the older vector
-        prs[6] = s2;
-        if (prs[9] >= (double)EX_LAG2_AFTER && p2 > 0.0 && s2 - sd * lam >= EX_LAG2_RES * s2) prs[15] = 1.0;
-        // a two-step move needs the step vector in the next apply: tracking stops
-        // only on a step that decided no move, after EX_TRACK plain steps or once
-        // the step is too small for any move (the move tests above fail for it)
-        if (prs[8] == 0.0 && (prs[9] >= (double)EX_TRACK || EX_MAX_LAM * EX_MAX_LAM * step <= 2.0 * tol))
-            prs[11] = 0.0;
-    }
+    if (threadIdx.x == 0)
+        pr_decide(fit, fit ? fs[0] : 0.0, fit ? fs[1] : 0.0, fit ? fs[2] : 0.0, global, S, damp, ninv, tol, first,
+                  extrap, prs, step_out);
 }
 
 __global__ void k_pr_reduce(const double *partials, const double *partials2, int np, int global, double S,
@@ -711,13 +719,13 @@ __global__ __launch_bounds__(MP_THREADS) void k_pr_tiles(const int32_t *__restri
 // A row r is split when its first entry and its end fall in different tiles of the
 // merged sequence: items r + off[r] and r + off[r + 1] (a row's end comes after
 // its entries and before the next row's first entry).
-__global__ void k_pr_rows(int64_t nb, int items, const int32_t *__restrict__ mp_row,
-                          const int64_t *__restrict__ mp_edge, const int64_t *__restrict__ off, const double *pf,
-                          const double *pl, int64_t dm, const uint64_t *__restrict__ dkey,
-                          const int64_t *__restrict__ doff, const int32_t *__restrict__ dcol, int keybits,
-                          const double *__restrict__ contrib, const double *cterm, double damp, double *xn,
-                          const double *done) {
-    if (*done != 0.0) return;
+__device__ __forceinline__ void pr_rows_body(int64_t nb, int items, const int32_t *__restrict__ mp_row,
+                                             const int64_t *__restrict__ mp_edge,
+                                             const int64_t *__restrict__ off, const double *pf, const double *pl,
+                                             int64_t dm, const uint64_t *__restrict__ dkey,
+                                             const int64_t *__restrict__ doff, const int32_t *__restrict__ dcol,
+                                             int keybits, const double *__restrict__ contrib,
+                                             const double *cterm, double damp, double *xn) {
     const double base = *cterm;
     for (int64_t k = gtid(); k < nb + dm; k += gstride()) {
         if (k < nb) {
@@ -749,6 +757,94 @@ __global__ void k_pr_rows(int64_t nb, int items, const int32_t *__restrict__ mp_
             if (acc != 0.0) xn[r] += damp * acc;
         }
     }
+}
+__global__ void k_pr_rows(int64_t nb, int items, const int32_t *__restrict__ mp_row,
+                          const int64_t *__restrict__ mp_edge, const int64_t *__restrict__ off, const double *pf,
+                          const double *pl, int64_t dm, const uint64_t *__restrict__ dkey,
+                          const int64_t *__restrict__ doff, const int32_t *__restrict__ dcol, int keybits,
+                          const double *__restrict__ contrib, const double *cterm, double damp, double *xn,
+                          const double *done) {
+    if (*done != 0.0) return;
+    pr_rows_body(nb, items, mp_row, mp_edge, off, pf, pl, dm, dkey, doff, dcol, keybits, contrib, cterm, damp, xn);
+}
+
+// Rows, apply and reduce of one step in one launch, for graphs of up to FIN_N vertices:
+// one workgroup finishes the rows, applies the step and decides the next one.  At this
+// size each of the three launches does about 4 us of work and costs as much again, and
+// the host issues four launches a step no faster than the device runs them (16k
+// vertices, 262k arcs: 37 us a step with four launches, 31 with two, of which this
+// kernel takes 16; the batches' paths and ranks together 1610 -> 1435 us per pass).  One
+// workgroup moves about 60 GB/s, so the line lies where its time passes that of the
+// three launches: with FIN_N = 2^17 a graph of 100k vertices took 2579 us in place of 1155.
+constexpr int FIN_T = 1024;
+constexpr int32_t FIN_N = 1 << 15;
+__global__ __launch_bounds__(FIN_T) void k_pr_finish_small(
+    int64_t nb, int items, const int32_t *__restrict__ mp_row, const int64_t *__restrict__ mp_edge,
+    const int64_t *__restrict__ off, const double *pf, const double *pl, int64_t dm,
+    const uint64_t *__restrict__ dkey, const int64_t *__restrict__ doff, const int32_t *__restrict__ dcol, int keybits,
+    double *contrib, double damp, double *xn, int32_t n, const double *x_o, const int32_t *deg, float *dprev,
+    float *dprev2, int global, double S, double ninv, double tol, int extrap, double *prs, double *step_out) {
+    if (prs[3] != 0.0) return;
+    pr_rows_body(nb, items, mp_row, mp_edge, off, pf, pl, dm, dkey, doff, dcol, keybits, contrib, prs + 2, damp, xn);
+    const double f = prs[8];
+    const bool two = prs[14] != 0.0, fit = extrap && prs[11] != 0.0, lag2 = fit && prs[15] != 0.0;
+    __syncthreads();
+    // as k_pr_apply
+    double acc = 0.0, dang = 0.0, sq = 0.0, dot = 0.0, dot2 = 0.0;
+    constexpr int U = 8;
+    for (int i0 = threadIdx.x; i0 < n; i0 += U * FIN_T) {
+        int32_t dg[U];
+        double nv[U], ov[U], pv[U], pv2[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int v = min(i0 + u * FIN_T, n - 1);
+            nv[u] = xn[v];
+            ov[u] = x_o[v];
+            dg[u] = deg[v];
+            pv[u] = fit ? (double)dprev[v] : 0.0;
+            pv2[u] = lag2 ? (double)dprev2[v] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int v = i0 + u * FIN_T;
+            if (v >= n) continue;
+            const double dl = nv[u] - ov[u];
+            acc += fabs(dl);
+            if (fit) {
+                sq += dl * dl;
+                dot += dl * pv[u];
+                if (lag2) {
+                    dot2 += dl * pv2[u];
+                    dprev2[v] = (float)pv[u];
+                }
+                dprev[v] = (float)dl;
+            }
+            double y = nv[u];
+            if (f != 0.0) {
+                y = nv[u] + f * (two ? dl + pv[u] : dl);
+                xn[v] = y;
+            }
+            contrib[v] = dg[u] > 0 ? y / (double)dg[u] : 0.0;
+            if (dg[u] == 0) dang += y;
+        }
+    }
+    __shared__ double s[5][FIN_T / WAVE];
+    double v5[5] = {acc, dang, sq, dot, dot2};
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        v5[q] = wave_sum(v5[q]);
+        if (lane_id() == 0) s[q][threadIdx.x / WAVE] = v5[q];
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        v5[q] = 0.0;
+        for (int w = 0; w < FIN_T / WAVE; ++w) v5[q] += s[q][w];
+    }
+    prs[0] = v5[0];
+    prs[1] = v5[1];
+    pr_decide(fit, v5[2], v5[3], v5[4], global, S, damp, ninv, tol, 0, extrap, prs, step_out);
 }
 
 // ---- gather floor --------------------------------------------------------------------
@@ -914,7 +1010,7 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
     int32_t it = 0, launched = 0;
     *conv = 0;
     std::vector<std::pair<int, int>> slots;  // profiled launches of the group (pull, apply)
-    // one Jacobi step (four launches: pull, rows / heavy rows, apply, reduce)
+    // one Jacobi step (four launches: pull, rows / heavy rows, apply, reduce; two on small graphs)
     auto launch_step = [&]() -> int {
         if (!tiles) DG_TRY(counters_clear(g));  // the heavy-row queue counters of the pull
         int ps;
@@ -924,6 +1020,16 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
             hipLaunchKernelGGL(tiles_kernel, dim3((unsigned)nb), dim3(MP_THREADS), 0, s, ws.mp_row.p, ws.mp_edge.p,
                                R.off.p, R.col.p, contrib, prs + 2, damping, xn, pf, pl, done);
             prof_end(ps, s, 16.0 * (double)g->n + 12.0 * (double)R.m);
+            if (g->n <= FIN_N) {
+                hipLaunchKernelGGL(k_pr_finish_small, dim3(1), dim3(FIN_T), 0, s, nb, items, ws.mp_row.p,
+                                   ws.mp_edge.p, R.off.p, pf, pl, R.dm, R.dkey.p, R.doff.p, R.dcol.p, R.keybits,
+                                   contrib, damping, xn, g->n, x, g->fwd.deg.p, dprev, dprev2, (int)global, S, ninv,
+                                   tol, extrap, prs, step_out);
+                DG_HIP(hipGetLastError());
+                std::swap(x, xn);
+                slots.emplace_back(ps, -1);
+                return DG_OK;
+            }
             hipLaunchKernelGGL(k_pr_rows, dim3(grid_for(nb + R.dm)), dim3(256), 0, s, nb, items, ws.mp_row.p,
                                ws.mp_edge.p, R.off.p, pf, pl, R.dm, R.dkey.p, R.doff.p, R.dcol.p, R.keybits,
                                contrib, prs + 2, damping, xn, done);
@@ -983,11 +1089,12 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
                 ++queued;
                 return DG_OK;
             };
-            while (queued < std::min(SIDE_GROUP, grp)) DG_TRY(queue_one());
+            while (queued < std::min(g->n <= FIN_N ? 1 : SIDE_GROUP, grp)) DG_TRY(queue_one());
             int prc = DG_OK;
+            // (one step per call: the SSSP rounds wait for the host meanwhile)
             std::function<void()> pump = [&]() {
-                while (prc == DG_OK && queued < grp &&
-                       (queued < AHEAD || hipEventQuery(ws.step_ev[(queued - AHEAD) % RING]) == hipSuccess))
+                if (prc == DG_OK && queued < grp &&
+                    (queued < AHEAD || hipEventQuery(ws.step_ev[(queued - AHEAD) % RING]) == hipSuccess))
                     prc = queue_one();
             };
             g->pump = &pump;

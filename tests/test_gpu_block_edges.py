@@ -144,3 +144,29 @@ def test_small_batch_sequences(dg, k, und, diff_only):
             assert np.array_equal(ew, w[o])
             assert np.array_equal(q.read()[0], oracle.sssp(n, s, d, w, 0))
     G.close()
+
+
+# one-workgroup end of a rank step: sizes around its threads and its limit, plain and
+# extrapolated steps, rows over several tiles, dangling vertices
+@pytest.mark.parametrize("extrap", [0, 1])
+@pytest.mark.parametrize("n", [3, 1023, 1025, 4096, 4097, 32767, 32768, 32769])
+def test_rank_step_end(dg, n, extrap):
+    rng = np.random.default_rng(n)
+    m = min(6 * n, n * (n - 1) // 2)
+    u, v = (n * rng.random(4 * m) ** 2).astype(np.int64), rng.integers(0, n, 4 * m)
+    v = np.where(rng.random(4 * m) < 0.15, n // 2, v)  # one row of many entries
+    key = rng.permutation(np.unique((u << 32 | v)[u != v]))[:m]
+    s, d = (key >> 32).astype(np.int32), (key & 0xFFFFFFFF).astype(np.int32)
+    c = dg.Config()
+    c.pr_extrapolate = extrap
+    G = dg.Graph(n, s, d, None, config=c)
+    q = G.pr_attach(0.85, 1e-9, 1000)
+    for step in range(3):
+        want, _, _ = oracle.pagerank(n, s, d, 0.85, 1e-9, 1000)
+        rank, _, conv = q.read()
+        assert conv and np.max(np.abs(rank - want)) <= 1e-10
+        if n > 100:
+            b = graphgen.update_batch(n, s, d, n // 20, step)
+            G.apply(*b)
+            s, d, _, _ = oracle.apply(n, s, d, np.ones(s.size, np.int32), *b)
+    G.close()
