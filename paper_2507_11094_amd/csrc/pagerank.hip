@@ -55,6 +55,7 @@ static inline int grid_wide(int64_t n) {
 }
 
 constexpr int APPLY_GROUPS = 1024;
+constexpr int32_t APPLY_STREAM = 1 << 23;
 
 __global__ void k_pr_init(int32_t n, double *x, double *contrib, const int32_t *deg) {
     const double x0 = 1.0 / (double)n;
@@ -379,12 +380,31 @@ __global__ void k_pr_reduce(const double *partials, const double *partials2, int
     pr_reduce_body(partials, partials2, np, global, S, damp, ninv, tol, first, extrap, prs, step_out);
 }
 
+// Loads and stores of data that one launch passes over once, with the non-temporal hint
+// where STREAM is set.
+template <bool STREAM, class T>
+__device__ __forceinline__ T ld_stream(const T *p) {
+    return STREAM ? __builtin_nontemporal_load(p) : *p;
+}
+template <bool STREAM, class T>
+__device__ __forceinline__ void st_stream(T *p, T v) {
+    if (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+
 // contrib := xn / outdeg on A, and x := xn unless x_w is null (the whole-graph
 // steps alternate two buffers instead of copying); fixed-order partials of the L1
 // step |xn - x_o| and of the new mass on dangling vertices (k_pr_reduce sums
 // them).  Summing them in the last workgroup to finish instead (an atomic ticket
 // after a device-scope fence per workgroup) took 62-68 us per step against 22 + 4
 // us for the two launches: the fence writes the L2 back in every workgroup.
+// PAIRS: whole vectors whose arrays are 16-byte aligned, two elements per lane.
+// STREAM: hints for vectors that the next launch cannot find in a cache any more; the
+// shares are written without, since the next step gathers them.  Bandwidth bounds it,
+// 36 bytes a vertex: 4096^2 grid 147 us with one element per lane, 131 with pairs, 109
+// (5.6 TB/s) with the hints; R-MAT 22 (4M vertices) 33, 26 and 27 us, 1M vertices 9.1,
+// 8.5 and 9.5, so the hints start at APPLY_STREAM vertices (288 MB).
+template <bool PAIRS, bool STREAM>
 __global__ __launch_bounds__(256) void k_pr_apply(const int32_t *A, int64_t na, double *xn,
                                                   const double *x_o, double *x_w, double *contrib,
                                                   const int32_t *deg, double *partials, double *partials2,
@@ -402,14 +422,62 @@ __global__ __launch_bounds__(256) void k_pr_apply(const int32_t *A, int64_t na, 
     if (dprev && prs[11] == 0.0) dprev = nullptr;
     if (!dprev || prs[15] == 0.0) dprev2 = nullptr;
     double acc = 0.0, dang = 0.0, sq = 0.0, dot = 0.0, dot2 = 0.0;
+    const auto one = [&](double nv, double ov, int32_t dg, float pv, float pv2, double &y, double &c) {
+        const double dl = nv - ov;
+        acc += fabs(dl);
+        if (dprev) {
+            sq += dl * dl;
+            dot += dl * (double)pv;
+            if (dprev2) dot2 += dl * (double)pv2;
+        }
+        y = f != 0.0 ? nv + f * (two ? dl + (double)pv : dl) : nv;
+        c = dg > 0 ? y / (double)dg : 0.0;
+        if (dg == 0) dang += y;
+        return (float)dl;
+    };
+    const int64_t st = gstride();
+    if (PAIRS) {
+        // whole vectors, two neighbouring elements per lane
+        typedef double D2 __attribute__((ext_vector_type(2)));
+        typedef float F2 __attribute__((ext_vector_type(2)));
+        typedef int32_t I2 __attribute__((ext_vector_type(2)));
+        constexpr int U = 2;
+        const int64_t np = na / 2;
+        for (int64_t i0 = gtid(); i0 < np; i0 += U * st) {
+            D2 nv[U], ov[U];
+            I2 dg[U];
+            F2 pv[U], pv2[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t i = min(i0 + u * st, np - 1);
+                nv[u] = ld_stream<STREAM>(reinterpret_cast<const D2 *>(xn) + i);
+                ov[u] = ld_stream<STREAM>(reinterpret_cast<const D2 *>(x_o) + i);
+                dg[u] = ld_stream<STREAM>(reinterpret_cast<const I2 *>(deg) + i);
+                pv[u] = dprev ? ld_stream<STREAM>(reinterpret_cast<const F2 *>(dprev) + i) : F2{0.0f, 0.0f};
+                pv2[u] = dprev2 ? ld_stream<STREAM>(reinterpret_cast<const F2 *>(dprev2) + i) : F2{0.0f, 0.0f};
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t i = i0 + u * st;
+                if (i >= np) continue;
+                double y0, y1, c0, c1;
+                const float d0 = one(nv[u].x, ov[u].x, dg[u].x, pv[u].x, pv2[u].x, y0, c0);
+                const float d1 = one(nv[u].y, ov[u].y, dg[u].y, pv[u].y, pv2[u].y, y1, c1);
+                if (dprev2) st_stream<STREAM>(reinterpret_cast<F2 *>(dprev2) + i, pv[u]);
+                if (dprev) st_stream<STREAM>(reinterpret_cast<F2 *>(dprev) + i, F2{d0, d1});
+                if (f != 0.0) st_stream<STREAM>(reinterpret_cast<D2 *>(xn) + i, D2{y0, y1});
+                reinterpret_cast<D2 *>(contrib)[i] = D2{c0, c1};
+            }
+        }
+    }
     // four strided elements per pass, every load issued before the stores (x_w may be
     // x_o, so the compiler could not reorder them itself); the sums keep the order
     // of a plain strided loop
     constexpr int U = 4;
-    const int64_t st = gstride();
-    for (int64_t i0 = gtid(); i0 < na; i0 += U * st) {
+    for (int64_t i0 = (PAIRS ? na / 2 * 2 : 0) + gtid(); i0 < na; i0 += U * st) {
         int32_t v[U], dg[U];
-        double nv[U], ov[U], pv[U], pv2[U];
+        double nv[U], ov[U];
+        float pv[U], pv2[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t i = i0 + u * st;
@@ -421,31 +489,19 @@ __global__ __launch_bounds__(256) void k_pr_apply(const int32_t *A, int64_t na, 
             nv[u] = xn[v[u]];
             ov[u] = x_o[v[u]];
             dg[u] = deg[v[u]];
-            pv[u] = dprev ? (double)dprev[v[u]] : 0.0;
-            pv2[u] = dprev2 ? (double)dprev2[v[u]] : 0.0;
+            pv[u] = dprev ? dprev[v[u]] : 0.0f;
+            pv2[u] = dprev2 ? dprev2[v[u]] : 0.0f;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (v[u] < 0) continue;
-            const double dl = nv[u] - ov[u];
-            acc += fabs(dl);
-            if (dprev) {
-                sq += dl * dl;
-                dot += dl * pv[u];
-                if (dprev2) {
-                    dot2 += dl * pv2[u];
-                    dprev2[v[u]] = (float)pv[u];
-                }
-                dprev[v[u]] = (float)dl;
-            }
-            double y = nv[u];
-            if (f != 0.0) {
-                y = nv[u] + f * (two ? dl + pv[u] : dl);
-                if (!x_w) xn[v[u]] = y;
-            }
+            double y, c;
+            const float d = one(nv[u], ov[u], dg[u], pv[u], pv2[u], y, c);
+            if (dprev2) dprev2[v[u]] = pv[u];
+            if (dprev) dprev[v[u]] = d;
             if (x_w) x_w[v[u]] = y;
-            contrib[v[u]] = dg[u] > 0 ? y / (double)dg[u] : 0.0;
-            if (dg[u] == 0) dang += y;
+            else if (f != 0.0) xn[v[u]] = y;
+            contrib[v[u]] = c;
         }
     }
     block_sum2(acc, dang, &partials[2 * blockIdx.x], &partials[2 * blockIdx.x + 1]);
@@ -615,19 +671,16 @@ __global__ void k_mp_partition(const int64_t *__restrict__ off, int32_t n, int64
 // STREAM: the column and offset streams are read, and the results written, with
 // non-temporal hints, so that they do not displace the gathered contributions
 // from L2.
-template <bool STREAM>
-__device__ __forceinline__ int32_t ld_stream(const int32_t *p) {
-    return STREAM ? __builtin_nontemporal_load(p) : *p;
-}
-template <bool STREAM>
-__device__ __forceinline__ int64_t ld_stream(const int64_t *p) {
-    return STREAM ? __builtin_nontemporal_load(p) : *p;
-}
-template <bool STREAM>
-__device__ __forceinline__ void st_stream(double *p, double v) {
-    if (STREAM) __builtin_nontemporal_store(v, p);
-    else *p = v;
-}
+// The tile's LDS, and how many workgroups share a CU (by the LDS the launch asks for).
+// Where rows are short the time goes into the streams of offsets and values, and eight
+// workgroups hide it best: 4096^2 grid, 4 arcs a vertex, 146 us a launch against 166
+// with six.  Where the gathers at scattered columns bound the kernel, more workgroups
+// only compete for the L1 that holds the most used shares: R-MAT 22, 16 arcs a vertex,
+// 363 us with eight, 354 with six, 345 with five or four.
+template <int ITEMS>
+constexpr int TILE_LDS = 8 * ITEMS + 8;
+constexpr int64_t TILE_DENSE = 8;         // arcs a vertex from which the gathers bound it
+constexpr int TILE_LDS_DENSE = 30 << 10;  // five workgroups a CU
 
 template <bool STREAM, int ITEMS>
 __global__ __launch_bounds__(MP_THREADS) void k_pr_tiles(const int32_t *__restrict__ mp_row,
@@ -639,8 +692,9 @@ __global__ __launch_bounds__(MP_THREADS) void k_pr_tiles(const int32_t *__restri
                                                          const double *done) {
     if (*done != 0.0) return;
     constexpr int IPT = ITEMS / MP_THREADS;
-    __shared__ double s_val[ITEMS];
-    __shared__ int32_t s_off[ITEMS + 1];
+    // entries (8 bytes each) from the front, row starts (4 each) from the back of the
+    // first TILE_LDS<ITEMS> bytes: a tile has ITEMS of both together, so they never meet
+    extern __shared__ __align__(8) char s_raw[];
     __shared__ int32_t s_long[ITEMS / MP_LONG + 2];
     __shared__ int32_t s_nlong;
     const int64_t b = blockIdx.x;
@@ -649,6 +703,8 @@ __global__ __launch_bounds__(MP_THREADS) void k_pr_tiles(const int32_t *__restri
     const int32_t ne = (int32_t)(mp_edge[b + 1] - e0);
     const int32_t nr = r1 - r0;
     const int t = threadIdx.x;
+    double *s_val = reinterpret_cast<double *>(s_raw);
+    int32_t *s_off = reinterpret_cast<int32_t *>(s_raw + TILE_LDS<ITEMS>) - (nr + 1);
     if (t == 0) s_nlong = 0;
     // stage the entries: all column loads first, the row starts while they are in
     // flight, then all gathers (IPT in flight per lane)
@@ -987,6 +1043,7 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
     auto tiles_kernel = items == 1024 ? (nt ? k_pr_tiles<true, 1024> : k_pr_tiles<false, 1024>)
                       : items == 4096 ? (nt ? k_pr_tiles<true, 4096> : k_pr_tiles<false, 4096>)
                                       : (nt ? k_pr_tiles<true, 2048> : k_pr_tiles<false, 2048>);
+    const size_t tile_lds = std::max(8 * items + 8, R.m >= TILE_DENSE * (int64_t)g->n ? TILE_LDS_DENSE : 0);
     int64_t nb = 0;
     if (tiles) {
         nb = ((int64_t)g->n + R.m + items - 1) / items;
@@ -999,6 +1056,10 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
     }
     double *pf = ws.mp_part.p, *pl = ws.mp_part.p + nb + 1;
     const double *done = prs + 3;
+    // 16-byte access to the whole vectors (an allocator of the caller's may align less)
+    const bool wide = ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(xn) |
+                        reinterpret_cast<uintptr_t>(contrib) | reinterpret_cast<uintptr_t>(g->fwd.deg.p) |
+                        reinterpret_cast<uintptr_t>(dprev) | reinterpret_cast<uintptr_t>(dprev2)) % 16) == 0;
     // Steps are launched in groups without a host round trip; the convergence
     // test runs on the device (k_pr_reduce), and once it passes the remaining
     // launches of the group return at once.  The host reads the flag per group.
@@ -1017,7 +1078,7 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
         if (tiles) {
             // tiles: off 8 + xn 8 per row, col 4 + contrib 8 per base entry
             ps = prof_begin("pr_tiles", s);
-            hipLaunchKernelGGL(tiles_kernel, dim3((unsigned)nb), dim3(MP_THREADS), 0, s, ws.mp_row.p, ws.mp_edge.p,
+            hipLaunchKernelGGL(tiles_kernel, dim3((unsigned)nb), dim3(MP_THREADS), tile_lds, s, ws.mp_row.p, ws.mp_edge.p,
                                R.off.p, R.col.p, contrib, prs + 2, damping, xn, pf, pl, done);
             prof_end(ps, s, 16.0 * (double)g->n + 12.0 * (double)R.m);
             if (g->n <= FIN_N) {
@@ -1048,12 +1109,15 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
         int pa = prof_begin("pr_apply", s);
         if (tiles) {
             // the step just written becomes the current vector: no copy
-            hipLaunchKernelGGL(k_pr_apply, dim3(APPLY_GROUPS), dim3(256), 0, s, A, na, xn, x, (double *)nullptr,
+            auto apply = !wide               ? k_pr_apply<false, false>
+                       : g->n >= APPLY_STREAM ? k_pr_apply<true, true>
+                                              : k_pr_apply<true, false>;
+            hipLaunchKernelGGL(apply, dim3(APPLY_GROUPS), dim3(256), 0, s, A, na, xn, x, (double *)nullptr,
                                contrib, g->fwd.deg.p, partials, partials2, dprev, dprev2, prs);
             prof_end(pa, s, 28.0 * (double)na);
             std::swap(x, xn);
         } else {
-            hipLaunchKernelGGL(k_pr_apply, dim3(APPLY_GROUPS), dim3(256), 0, s, A, na, xn, x, x, contrib,
+            hipLaunchKernelGGL((k_pr_apply<false, false>), dim3(APPLY_GROUPS), dim3(256), 0, s, A, na, xn, x, x, contrib,
                                g->fwd.deg.p, partials, partials2, dprev, dprev2, prs);
             prof_end(pa, s, 40.0 * (double)na);
         }

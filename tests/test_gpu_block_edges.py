@@ -170,3 +170,24 @@ def test_rank_step_end(dg, n, extrap):
             G.apply(*b)
             s, d, _, _ = oracle.apply(n, s, d, np.ones(s.size, np.int32), *b)
     G.close()
+
+
+# ranks of odd and even vertex counts on both sides of the tiles' arcs-per-vertex line and
+# of the apply's streaming line.  Each side stops at an L1 step of tol, which leaves it
+# within tol d / (1 - d) of the fixed point.
+@pytest.mark.parametrize("n,deg", [(40000, 4), (40001, 4), (40001, 12), ((1 << 23) - 1, 0.1), ((1 << 23) + 1, 0.1)])
+def test_rank_vectors(dg, n, deg):
+    rng = np.random.default_rng(n)
+    key = np.unique(rng.integers(0, n, int(n * deg)) << 32 | (n * rng.random(int(n * deg)) ** 2).astype(np.int64))
+    key = key[(key >> 32) != (key & 0xFFFFFFFF)]
+    s, d = (key >> 32).astype(np.int32), (key & 0xFFFFFFFF).astype(np.int32)
+    G = dg.Graph(n, s, d, None)
+    q = G.pr_attach(0.85, 1e-9, 1000)
+    for step in range(2):
+        want, _, _ = oracle.pagerank(n, s, d, 0.85, 1e-9, 1000)
+        rank, _, conv = q.read()
+        assert conv and np.sum(np.abs(rank - want)) <= 2 * 1e-9 * 0.85 / 0.15
+        b = graphgen.update_batch(n, s, d, 5000, step)
+        G.apply(*b)
+        s, d, _, _ = oracle.apply(n, s, d, np.ones(s.size, np.int32), *b)
+    G.close()
