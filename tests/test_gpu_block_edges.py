@@ -191,3 +191,30 @@ def test_rank_vectors(dg, n, deg):
         G.apply(*b)
         s, d, _, _ = oracle.apply(n, s, d, np.ones(s.size, np.int32), *b)
     G.close()
+
+
+# static triangle count on the rows' beginnings (degree order as built) and on built lists
+# (after batches changed the degrees), with forward lists around the group sizes, ids on
+# both sides of the bitmap's 32,768 and lists long enough to be searched
+@pytest.mark.parametrize("n,core,m", [(3, 3, 0), (300, 65, 200), (2000, 130, 3000), (40000, 513, 60000), (70000, 1100, 120000)])
+def test_static_count_lists(dg, n, core, m):
+    rng = np.random.default_rng(n)
+    ids = rng.permutation(n)
+    a, b = np.triu_indices(core, 1)
+    keep = rng.random(a.size) < 0.9
+    u = np.concatenate([ids[a[keep]], rng.integers(0, n, m), ids[rng.integers(0, core, m)]])
+    v = np.concatenate([ids[b[keep]], rng.integers(0, n, m), rng.integers(0, n, m)])
+    far = ids[-200:] if n > 40000 else ids[:0]  # a second clique of low degree: ids past the bitmap
+    fa, fb = np.triu_indices(far.size, 1)
+    pick = rng.random(fa.size) < 0.05
+    u, v = np.concatenate([u, far[fa[pick]]]), np.concatenate([v, far[fb[pick]]])
+    key = np.unique((np.minimum(u, v) << 32 | np.maximum(u, v))[u != v])
+    s, d = (key >> 32).astype(np.int32), (key & 0xFFFFFFFF).astype(np.int32)
+    G = dg.Graph(n, s, d, None, undirected=True)
+    assert G.tc_static() == oracle.triangles(n, s, d)
+    if n > 3:
+        batch = graphgen.update_batch(n, s, d, max(40, m // 20), 1)
+        G.apply(*batch)
+        s, d, _, _ = oracle.apply(n, s, d, np.ones(s.size, np.int32), *batch, undirected=True)
+        assert G.tc_static() == oracle.triangles(n, s, d)
+    G.close()
