@@ -331,14 +331,15 @@ __global__ __launch_bounds__(256) void k_tc_prefix(int32_t n, const int64_t *__r
 // (when it fits) and walks y over N+(x).  For each y the lanes either stream
 // N+(y) and look its elements up in the LDS copy (one coalesced load per 64 elements),
 // or, when N+(y) is much longer, take the elements of N+(x) and binary-search N+(y)
-// in memory.  The lookups bound the kernel (262k vertices, 4.2M edges: about 600M).
+// in memory (262k vertices, 4.2M edges: 620M lookups and 0.5M searched lists).
 //
 // BITS (graphs in the degree order): forward lists point to vertices of higher degree,
 // so most of their ids are small, and the copy is a bitmap of the ids below TCF_IDS: a
 // lookup is one LDS read where the search of a sorted copy takes up to ten.  Larger
 // ids are searched in the list's tail in memory.  Graphs in the order given keep the
 // sorted copy.  (A hash set of the same size was slower than either: 2.44 ms against
-// 1.56 ms for the search.)
+// 1.56 ms for the search; the bitmap took 0.80 ms, bound by the instructions around a
+// lookup, and 0.41 ms with the lists whose ids are all in its range read by bits_hits.)
 constexpr int TCF_CAP = 1024;  // forward-list entries of a row staged in LDS, per wave
 constexpr int TCF_IDS = 32 * TCF_CAP;
 constexpr int TCF_BLOCKS = 8192;  // four or more grids of resident blocks, few enough adds to the total
@@ -351,6 +352,53 @@ __device__ __forceinline__ bool lds_has(const int32_t *a, int len, int32_t v) {
         else hi = mid;
     }
     return lo < len && a[lo] == v;
+}
+
+constexpr int TCF_LISTS = 4, TCF_LOADS = 2;  // lists together, and loads of each in flight
+// A list more than this many times longer than N+(x) is searched: a search is ten dependent
+// reads, a 64-entry step of the list about six instructions (6: 429 us, 16 to 64: 415)
+constexpr int TCF_LONG = 16;
+
+// How many entries of the lists of the lanes in `lists` (ys, len: bounds of a lane's list,
+// all ids below TCF_IDS) are in the bitmap sx; summed over the lanes' results.
+// The lists of a group are read through buffer descriptors of their lengths, which
+// answer 0 past the end: neither addresses nor bounds cost vector instructions, and the
+// zeros, looked up like any entry, are taken off at the end if id 0 is in the bitmap.
+__device__ __forceinline__ uint64_t bits_hits(const int32_t *sx, const int32_t *ocol, int64_t ys, int32_t len,
+                                              uint64_t lists, int l) {
+    uint32_t hits = 0;
+    uint64_t zeros = 0;
+    while (lists) {
+        __amdgpu_buffer_rsrc_t src[TCF_LISTS];
+        int32_t n[TCF_LISTS], most = 0;
+#pragma unroll
+        for (int q = 0; q < TCF_LISTS; ++q) {
+            const int k = lists ? __builtin_ctzll(lists) : 0;
+            const uint64_t at = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(ys >> 32), k) << 32 |
+                                (uint32_t)__builtin_amdgcn_readlane((int)ys, k);
+            n[q] = lists ? __builtin_amdgcn_readlane(len, k) : 0;
+            src[q] = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t *>(ocol + at), 0, 4 * n[q], 0x00027000);
+            most = max(most, n[q]);
+            lists &= lists - 1;
+        }
+        for (int32_t j0 = 0; j0 < most; j0 += TCF_LOADS * WAVE) {
+            uint32_t v[TCF_LISTS][TCF_LOADS];
+#pragma unroll
+            for (int q = 0; q < TCF_LISTS; ++q)
+#pragma unroll
+                for (int u = 0; u < TCF_LOADS; ++u)
+                    v[q][u] = __builtin_amdgcn_raw_buffer_load_b32(src[q], 4 * (j0 + l) + 4 * u * WAVE, 0, 0);
+#pragma unroll
+            for (int q = 0; q < TCF_LISTS; ++q)
+#pragma unroll
+                for (int u = 0; u < TCF_LOADS; ++u) {
+                    if (j0 + u * WAVE >= n[q]) continue;
+                    hits += ((uint32_t)sx[v[q][u] >> 5] >> (v[q][u] & 31)) & 1u;
+                    zeros += max(0, j0 + (u + 1) * WAVE - n[q]);
+                }
+        }
+    }
+    return (uint64_t)hits - (l == 0 && (sx[0] & 1) ? zeros : 0);
 }
 
 template <bool BITS>
@@ -402,8 +450,16 @@ __global__ __launch_bounds__(256) void k_tc_forward(int32_t n, const int64_t *__
                 mys = ob[y];
                 mye = oe[y];
             }
-            const int cnt = (int)(dx - p0 < WAVE ? dx - p0 : WAVE);
-            for (int k = 0; k < cnt; ++k) {
+            uint64_t rest = ballot(mye > mys);
+            if (BITS) {
+                const int32_t last = mye > mys ? ocol[mye - 1] : TCF_IDS;
+                uint64_t low = ballot(last < TCF_IDS && mye - mys <= TCF_LONG * rx * WAVE);
+                rest &= ~low;
+                acc += bits_hits(sx, ocol, mys, (int32_t)(mye - mys), low, l);
+            }
+            while (rest) {
+                const int k = __builtin_ctzll(rest);
+                rest &= rest - 1;
                 const int64_t ys = __shfl(mys, k, WAVE), ye = __shfl(mye, k, WAVE);
                 const int64_t dy = ye - ys;
                 if (staged && (dy + WAVE - 1) / WAVE <= 4 * rx) {
