@@ -18,6 +18,7 @@
 // algorithm, whose degree ordering bounds every forward list by sqrt(2m) on skewed
 // graphs.
 #include <algorithm>
+#include <type_traits>
 
 #include "dg_device.h"
 
@@ -26,6 +27,12 @@ namespace dg {
 static inline int grid_for(int64_t n) {
     int64_t g = (n + 255) / 256;
     return (int)(g < 1 ? 1 : (g > 8192 ? 8192 : g));
+}
+
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ int64_t wave_first(int64_t v) {
+    return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+                     (uint32_t)__builtin_amdgcn_readfirstlane((int)v));
 }
 
 struct RowRef {
@@ -71,25 +78,78 @@ constexpr int TC_FSTRIDE_MAX = 2048;
 constexpr int TC_FCAP = 128;  // fences per wave (rows up to 262,144 entries are fenced)
 constexpr int TC_FMIN = 128;
 
-// Position of neighbour x in the base row [ob, ob + db) whose fences f[k] =
-// id(col[ob + k * stride]), k < nf, are in LDS; -1 if absent.
-__device__ __forceinline__ int64_t find_fenced(const int32_t *__restrict__ col, int64_t ob, int64_t db,
-                                               int stride, const uint32_t *f, int nf, uint32_t x) {
-    if (x < f[0]) return -1;
-    int lo = 0, hi = nf - 1;  // the last k with f[k] <= x
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (f[mid] <= x) lo = mid;
-        else hi = mid - 1;
+// Searches of the neighbours x[u] in a sorted row of len entries: e[u] becomes the entry
+// (with its flags) of x[u] if the row has one, else some other entry.  Each starts
+// at s[u], with e[u] there, and covers the next size entries (a power of two); the steps go
+// side by side, so that U gathers are in flight per lane instead of one, and the last four
+// entries are read at once.
+struct __attribute__((packed, aligned(4))) Four {
+    uint32_t e[4];
+};
+template <int U>
+__device__ __forceinline__ void find_step(const int32_t *__restrict__ row, uint32_t len, int size,
+                                          const uint32_t (&x)[U], uint32_t (&s)[U], uint32_t (&e)[U]) {
+    const bool four = size >= 4 && len >= 4;
+    for (int h = size >> 1; h > (four ? 2 : 0); h >>= 1) {
+        uint32_t y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) y[u] = (uint32_t)row[min(s[u] + h, len - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool go = s[u] + h < len && (y[u] & ID_MASK) <= x[u];
+            s[u] += go ? h : 0;
+            e[u] = go ? y[u] : e[u];
+        }
     }
-    const int64_t s0 = ob + (int64_t)lo * stride;
-    return find_sorted(col, s0, min(s0 + stride, ob + db), x);
+    if (!four) return;
+    Four y[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) y[u] = *reinterpret_cast<const Four *>(row + min(s[u], len - 4));
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if ((y[u].e[k] & ID_MASK) == x[u]) e[u] = y[u].e[k];
+}
+
+// The start of find_step from a row's fences, f[k] = entry k * stride for k < nf.  False
+// if every x of the wave lies below the row.
+template <int U>
+__device__ __forceinline__ bool find_fenced(const uint32_t *f, int nf, int stride, const uint32_t (&xs)[U],
+                                            uint32_t (&s)[U], uint32_t (&e)[U]) {
+    const auto first = [](const uint32_t (&f)[1], uint32_t x) {
+        if (x < f[0]) return -1;
+        return 0;
+    };
+    const uint32_t head[1] = {f[0] & ID_MASK};  // the row's first id
+    bool some = false;
+#pragma unroll
+    for (int u = 0; u < U; ++u) some |= first(head, xs[u]) == 0;
+    if (ballot(some) == 0) return false;
+    int top = 1;
+    while (top < nf) top <<= 1;
+#pragma unroll
+    for (int u = 0; u < U; ++u) s[u] = 0;
+    for (int h = top >> 1; h > 0; h >>= 1) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t k = min(s[u] + h, (uint32_t)(nf - 1));
+            if ((f[k] & ID_MASK) <= xs[u]) s[u] = k;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        e[u] = f[s[u]];
+        s[u] *= stride;
+    }
+    return true;
 }
 
 // Work items: a changed edge's shorter row is cut into pieces of TC_CHUNK entries,
 // so that an edge between two hubs (tens of thousands of common candidates) is
 // spread over many waves instead of holding one wave for the whole launch.
 constexpr int TC_CHUNK = 256;
+constexpr uint32_t ABSENT = ~0u;  // no entry: dead, and of no id
 
 // cnt[i] = pieces of changed edge i (0 when its shorter row is empty); cnt[ne] = 0.
 __global__ void k_tc_items(int64_t ne, const int32_t *__restrict__ eu, const int32_t *__restrict__ ev,
@@ -108,6 +168,11 @@ __global__ void k_tc_items(int64_t ne, const int32_t *__restrict__ eu, const int
 
 // One wave per work item; lanes walk the item's piece of the smaller row and probe
 // the larger one.  start = exclusive scan of the piece counts (start[ne] = total).
+// The gathers of the searches bound it, one line per lane and step (R-MAT 20 without 84k
+// of its edges, 39M candidates: 77 % of the time).  With one candidate per lane it waited for
+// each step instead, 500 us a launch; with a piece's four side by side 350, and with the
+// last two steps read as one group of four entries 325.  (More fences cost as much to
+// read as they save; pieces of 128 took 445 us.)
 __global__ __launch_bounds__(256) void k_tc_delta(int64_t ne, const int32_t *eu, const int32_t *ev,
                                                   const int64_t *__restrict__ start,
                                                   const int64_t *__restrict__ off,
@@ -115,7 +180,7 @@ __global__ __launch_bounds__(256) void k_tc_delta(int64_t ne, const int32_t *eu,
                                                   const int64_t *__restrict__ doff,
                                                   const int32_t *__restrict__ dcol, int64_t *part) {
     __shared__ uint32_t s_fence[256 / WAVE][TC_FCAP];
-    const int64_t wave_global = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
+    const int64_t wave_global = wave_first(((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE);
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / WAVE;
     const int l = lane_id();
     uint32_t *f = s_fence[threadIdx.x / WAVE];
@@ -132,7 +197,7 @@ __global__ __launch_bounds__(256) void k_tc_delta(int64_t ne, const int32_t *eu,
             lo += (int64_t)__popcll(le) * step;
             hi = min(hi, lo + step);
         }
-        const int64_t i = lo, piece = it - start[i];
+        const int64_t i = wave_first(lo), piece = it - start[i];  // (the same in every lane: scalar from here)
         int32_t a = eu[i], b = ev[i];
         RowRef ra = row_ref(off, doff, a), rb = row_ref(off, doff, b);
         if (ra.db + ra.dd > rb.db + rb.dd) {
@@ -146,7 +211,7 @@ __global__ __launch_bounds__(256) void k_tc_delta(int64_t ne, const int32_t *eu,
         const int nf = fenced ? (int)nf64 : 0;
         if (fenced) {
             wave_sync();  // every lane is done with the previous edge's fences
-            for (int k = l; k < nf; k += WAVE) f[k] = (uint32_t)col[rb.ob + (int64_t)k * stride] & ID_MASK;
+            for (int k = l; k < nf; k += WAVE) f[k] = (uint32_t)col[rb.ob + (int64_t)k * stride];
             wave_sync();
         }
         // global reads of one probe: the whole binary search, or the segment's
@@ -157,34 +222,54 @@ __global__ __launch_bounds__(256) void k_tc_delta(int64_t ne, const int32_t *eu,
             walked += (j1 - j0) + nf;
             probes += (j1 - j0) * depth;
         }
-        for (int64_t j = j0 + l; j < j1; j += WAVE) {
-            uint32_t e = j < ra.db ? (uint32_t)col[ra.ob + j] : (uint32_t)dcol[ra.od + (j - ra.db)];
-            if (e & DEAD) continue;
-            uint32_t c = e & ID_MASK;
-            uint32_t e2;
-            bool hit;
-            if (fenced) {
-                const int64_t p = find_fenced(col, rb.ob, rb.db, stride, f, nf, c);
-                if (p >= 0) {
-                    e2 = (uint32_t)col[p];
-                    hit = !(e2 & DEAD);
-                } else {
-                    hit = false;
-                    if (rb.dd > 0) {
-                        const int64_t q = find_sorted(dcol, rb.od, rb.od + rb.dd, c);
-                        if (q >= 0) {
-                            e2 = (uint32_t)dcol[q];
-                            hit = !(e2 & DEAD);
-                        }
-                    }
-                }
-            } else {
-                hit = row_find(col, dcol, rb, c, e2);
+        const int32_t *row = col + rb.ob, *drow = dcol + rb.od;
+        int whole = 1, dwhole = 1;  // powers of two that cover the rows
+        while (whole < rb.db) whole <<= 1;
+        while (dwhole < rb.dd) dwhole <<= 1;
+        // U candidates per lane, 64 apart
+        const auto probe = [&](auto uc, int64_t j) {
+            constexpr int U = decltype(uc)::value;
+            uint32_t e[U], c[U], s[U], e2[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u, j += WAVE) {
+                const int64_t k = min(j, j1 - 1);
+                e[u] = (uint32_t)*(k < ra.db ? col + ra.ob + k : dcol + ra.od + (k - ra.db));
+                if (j >= j1) e[u] = DEAD;
+                c[u] = e[u] & ID_MASK;
+                e2[u] = ABSENT;
+                s[u] = 0;
             }
-            if (!hit) continue;
-            int k = 1 + ((e & MARK) ? 1 : 0) + ((e2 & MARK) ? 1 : 0);
-            acc += (uint64_t)(6 / k);
-        }
+            if (rb.db > 0) {
+                if (fenced) {
+                    if (find_fenced<U>(f, nf, stride, c, s, e2)) find_step<U>(row, rb.db, stride, c, s, e2);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) e2[u] = (uint32_t)row[0];
+                    find_step<U>(row, rb.db, whole, c, s, e2);
+                }
+            }
+            if (rb.dd > 0) {
+                uint32_t d2[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    s[u] = 0;
+                    d2[u] = (uint32_t)drow[0];
+                }
+                find_step<U>(drow, rb.dd, dwhole, c, s, d2);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if ((e2[u] & ID_MASK) != c[u]) e2[u] = d2[u];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool hit = (e2[u] & ID_MASK) == c[u] && !((e[u] | e2[u]) & DEAD);
+                const int k = 1 + ((e[u] & MARK) ? 1 : 0) + ((e2[u] & MARK) ? 1 : 0);
+                acc += hit ? (uint64_t)(6 / k) : 0;
+            }
+        };
+        if (j1 <= j0) continue;
+        if (j1 - j0 <= WAVE) probe(std::integral_constant<int, 1>(), j0 + l);
+        else probe(std::integral_constant<int, TC_CHUNK / WAVE>(), j0 + l);
     }
     // per-block partials (no contended atomics; summed in block order by k_tc_sum)
     __shared__ uint64_t s_p[3][256 / WAVE];

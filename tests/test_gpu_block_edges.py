@@ -218,3 +218,40 @@ def test_static_count_lists(dg, n, core, m):
         s, d, _, _ = oracle.apply(n, s, d, np.ones(s.size, np.int32), *batch, undirected=True)
         assert G.tc_static() == oracle.triangles(n, s, d)
     G.close()
+
+
+# triangles of changed edges between rows whose lengths lie around the steps of the search
+# (groups of four, the fenced length, pieces of 64 and 256), before and after the longer row
+# holds tombstones, marks and diff-level entries at its ends
+@pytest.mark.parametrize("long", [1, 3, 4, 5, 127, 129, 1025, 20000])
+@pytest.mark.parametrize("short", [1, 64, 65, 257])
+def test_changed_edge_rows(dg, long, short):
+    rng = np.random.default_rng(1000 * short + long)
+    n = 30000
+    hub, low = 15000, 20000  # the two ends of every changed edge
+    nb = np.sort(rng.choice(np.setdiff1d(np.arange(n), [hub, low]), max(long, short) + 40, replace=False))
+    a = nb[:long] if long < nb.size else nb
+    b = np.unique(rng.choice(nb, short, replace=False))
+    s = np.concatenate([np.full(a.size, hub), np.full(b.size, low)]).astype(np.int32)
+    d = np.concatenate([a, b]).astype(np.int32)
+    u, v = np.minimum(s, d), np.maximum(s, d)
+    G = dg.Graph(n, u, v, None, undirected=True)
+    q = G.tc_attach()
+    for step in range(4):
+        # the edge itself appears and goes; the rows' ends go, and come back as new entries
+        bs, bd, op = [hub], [low], [1 - step % 2]
+        ends = [a[0], a[-1], b[0], b[-1]]
+        if step in (1, 2):
+            for x, r in ((ends[0], hub), (ends[1], hub), (ends[2], low), (ends[3], low)):
+                bs.append(r), bd.append(x), op.append(step - 1)
+        if step == 3:
+            far = np.setdiff1d(np.arange(10), np.concatenate([a, b]))[:2]
+            for x in far:
+                bs += [hub, low]
+                bd += [x, x]
+                op += [1, 1]
+        batch = (np.array(bs, np.int32), np.array(bd, np.int32), np.ones(len(bs), np.int32), np.array(op, np.uint8))
+        G.apply(*batch)
+        u, v, _, _ = oracle.apply(n, u, v, np.ones(u.size, np.int32), *batch, undirected=True)
+        assert q.read() == oracle.triangles(n, u, v), step
+    G.close()
