@@ -145,6 +145,26 @@ __device__ __forceinline__ bool find_fenced(const uint32_t *f, int nf, int strid
     return true;
 }
 
+// Per-block partials (no contended atomics; summed in block order by k_tc_sum).
+__device__ __forceinline__ void tc_block_part(uint64_t acc, uint64_t walked, uint64_t probes, int64_t *part) {
+    __shared__ uint64_t s_p[3][256 / WAVE];
+    acc = wave_sum(acc);
+    walked = wave_sum(walked);
+    probes = wave_sum(probes);
+    const int wv = threadIdx.x / WAVE;
+    if (lane_id() == 0) {
+        s_p[0][wv] = acc;
+        s_p[1][wv] = walked;
+        s_p[2][wv] = probes;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        uint64_t s = 0;
+        for (int q = 0; q < (int)blockDim.x / WAVE; ++q) s += s_p[threadIdx.x][q];
+        part[3 * (int64_t)blockIdx.x + threadIdx.x] = (int64_t)s;
+    }
+}
+
 // Work items: a changed edge's shorter row is cut into pieces of TC_CHUNK entries,
 // so that an edge between two hubs (tens of thousands of common candidates) is
 // spread over many waves instead of holding one wave for the whole launch.
@@ -152,18 +172,66 @@ constexpr int TC_CHUNK = 256;
 constexpr uint32_t ABSENT = ~0u;  // no entry: dead, and of no id
 
 // cnt[i] = pieces of changed edge i (0 when its shorter row is empty); cnt[ne] = 0.
-__global__ void k_tc_items(int64_t ne, const int32_t *__restrict__ eu, const int32_t *__restrict__ ev,
-                           const int64_t *__restrict__ off, const int64_t *__restrict__ doff, int64_t *cnt) {
-    for (int64_t i = gtid(); i <= ne; i += gstride()) {
-        if (i == ne) {
-            cnt[i] = 0;
-            continue;
+// Edges of at most TC_SHORT candidates are finished here and get no pieces: a wave takes
+// TC_WINDOW edges and its lanes take their candidates in turn, each searching its own edge's
+// longer row.  As work items of their own, a few candidates each, they left most lanes
+// idle over the whole chain of dependent reads (1M vertices, 84k new edges with 230k
+// candidates: 6 + 80 us for this launch and the next, now 23 + 16).
+constexpr int TC_SHORT = 32, TC_WINDOW = 16;
+
+__global__ __launch_bounds__(256) void k_tc_items(int64_t ne, const int32_t *__restrict__ eu,
+                                                  const int32_t *__restrict__ ev, const int64_t *__restrict__ off,
+                                                  const int32_t *__restrict__ col, const int64_t *__restrict__ doff,
+                                                  const int32_t *__restrict__ dcol, int64_t *cnt, int64_t *part) {
+    const int l = lane_id();
+    uint64_t acc = 0, walked = 0, probes = 0;
+    const int64_t nwaves = gstride() / WAVE;
+    for (int64_t w = gtid() / WAVE; w * TC_WINDOW <= ne; w += nwaves) {
+        const int64_t i = w * TC_WINDOW + l;
+        int64_t ta = 0, tb = 0;
+        int32_t a = 0, b = 0;  // the rows' vertices, the shorter first
+        if (l < TC_WINDOW && i < ne) {
+            a = eu[i];
+            b = ev[i];
+            ta = (off[a + 1] - off[a]) + (doff[a + 1] - doff[a]);
+            tb = (off[b + 1] - off[b]) + (doff[b + 1] - doff[b]);
+            if (ta > tb) {
+                int32_t v = a;
+                a = b;
+                b = v;
+                ta = tb;
+            }
         }
-        const int32_t a = eu[i], b = ev[i];
-        const int64_t ta = (off[a + 1] - off[a]) + (doff[a + 1] - doff[a]);
-        const int64_t tb = (off[b + 1] - off[b]) + (doff[b + 1] - doff[b]);
-        cnt[i] = (min(ta, tb) + TC_CHUNK - 1) / TC_CHUNK;
+        const int mine = ta <= TC_SHORT ? (int)ta : 0;
+        if (l < TC_WINDOW && i <= ne) cnt[i] = mine ? 0 : (ta + TC_CHUNK - 1) / TC_CHUNK;
+        int upto = mine;  // candidates of the lanes up to this one
+#pragma unroll
+        for (int d = 1; d < TC_WINDOW; d <<= 1) {
+            const int y = __shfl_up(upto, d, WAVE);
+            if (l >= d) upto += y;
+        }
+        const int total = __shfl(upto, TC_WINDOW - 1, WAVE);
+        for (int e0 = 0; e0 < total; e0 += WAVE) {
+            const int e = min(e0 + l, total - 1);
+            int k = 0;  // the first edge whose candidates reach past e
+#pragma unroll
+            for (int h = TC_WINDOW / 2; h > 0; h >>= 1)
+                if (__shfl(upto, k + h - 1, WAVE) <= e) k += h;
+            const int j = e - (__shfl(upto, k, WAVE) - __shfl(mine, k, WAVE));
+            const int32_t sv = __shfl(a, k, WAVE), lv = __shfl(b, k, WAVE);
+            const RowRef ra = row_ref(off, doff, sv), rb = row_ref(off, doff, lv);
+            const uint32_t x = j < ra.db ? (uint32_t)col[ra.ob + j] : (uint32_t)dcol[ra.od + (j - ra.db)];
+            if (e0 + l >= total || (x & DEAD)) continue;
+            uint32_t x2;
+            if (!row_find(col, dcol, rb, x & ID_MASK, x2)) continue;
+            acc += (uint64_t)(6 / (1 + ((x & MARK) ? 1 : 0) + ((x2 & MARK) ? 1 : 0)));
+        }
+        if (l == 0) {
+            walked += total;
+            probes += total * 12;
+        }
     }
+    tc_block_part(acc, walked, probes, part);
 }
 
 // One wave per work item; lanes walk the item's piece of the smaller row and probe
@@ -271,23 +339,7 @@ __global__ __launch_bounds__(256) void k_tc_delta(int64_t ne, const int32_t *eu,
         if (j1 - j0 <= WAVE) probe(std::integral_constant<int, 1>(), j0 + l);
         else probe(std::integral_constant<int, TC_CHUNK / WAVE>(), j0 + l);
     }
-    // per-block partials (no contended atomics; summed in block order by k_tc_sum)
-    __shared__ uint64_t s_p[3][256 / WAVE];
-    acc = wave_sum(acc);
-    walked = wave_sum(walked);
-    probes = wave_sum(probes);
-    const int wv = threadIdx.x / WAVE;
-    if (l == 0) {
-        s_p[0][wv] = acc;
-        s_p[1][wv] = walked;
-        s_p[2][wv] = probes;
-    }
-    __syncthreads();
-    if (threadIdx.x < 3) {
-        uint64_t s = 0;
-        for (int q = 0; q < (int)blockDim.x / WAVE; ++q) s += s_p[threadIdx.x][q];
-        part[3 * (int64_t)blockIdx.x + threadIdx.x] = (int64_t)s;
-    }
+    tc_block_part(acc, walked, probes, part);
 }
 
 // Sum of the per-block partials (triangle weight, entries walked, search steps).
@@ -322,12 +374,15 @@ int tc_delta(dg_graph *g, const int32_t *eu, const int32_t *ev, int64_t ne, uint
     if (ne <= 0) return DG_OK;
     hipStream_t s = g->stream;
     Dir &F = g->fwd;
-    // four waves per block; 16,384 blocks measured faster than a resident-size grid
-    int64_t blocks = std::min<int64_t>((ne + 3) / 4, 16384);
-    DG_TRY(g->ws.bpart.ensure(3 * (size_t)blocks + 8));
+    // four waves per block; 16,384, 8,192 and 4,096 blocks: 310, 320 and 340 us where the
+    // items are many, 30, 16 and 12 us where they are few
+    int64_t blocks = std::min<int64_t>((ne + 3) / 4, 8192);
+    const int64_t iblocks = std::min<int64_t>((ne / TC_WINDOW + 4) / 4, 8192);
+    DG_TRY(g->ws.bpart.ensure(3 * (size_t)(blocks + iblocks) + 8));
     DG_TRY(g->ws.tcitems.ensure(2 * ((size_t)ne + 1)));
     int64_t *cnt = g->ws.tcitems.p, *start = g->ws.tcitems.p + ne + 1;
-    hipLaunchKernelGGL(k_tc_items, dim3(grid_for(ne + 1)), dim3(256), 0, s, ne, eu, ev, F.off.p, F.doff.p, cnt);
+    hipLaunchKernelGGL(k_tc_items, dim3((unsigned)iblocks), dim3(256), 0, s, ne, eu, ev, F.off.p, F.col.p, F.doff.p,
+                       F.dcol.p, cnt, g->ws.bpart.p + 3 * blocks);
     DG_HIP(hipGetLastError());
     DG_TRY(scan_excl(g, cnt, start, ne + 1));
     int ps = prof_begin("tc_delta", s);
@@ -336,7 +391,7 @@ int tc_delta(dg_graph *g, const int32_t *eu, const int32_t *ev, int64_t ne, uint
     prof_end(ps, s, 0.0);
     // counters C_AUX1, C_AUX2, C_AUX3 = 6 x changed triangles, entries walked, search steps
     static_assert(C_AUX2 == C_AUX1 + 1 && C_AUX3 == C_AUX1 + 2, "three consecutive counters");
-    hipLaunchKernelGGL(k_tc_sum, dim3(1), dim3(1024), 0, s, g->ws.bpart.p, blocks, g->ws.dcnt + C_AUX1);
+    hipLaunchKernelGGL(k_tc_sum, dim3(1), dim3(1024), 0, s, g->ws.bpart.p, blocks + iblocks, g->ws.dcnt + C_AUX1);
     DG_HIP(hipGetLastError());
     DG_TRY(counters_read(g));
     *sum6 = (uint64_t)g->ws.hcnt[C_AUX1];

@@ -255,3 +255,22 @@ def test_changed_edge_rows(dg, long, short):
         u, v, _, _ = oracle.apply(n, u, v, np.ones(u.size, np.int32), *batch, undirected=True)
         assert q.read() == oracle.triangles(n, u, v), step
     G.close()
+
+
+# changed edges finished by windows of 16, rows on both sides of the 32 candidates
+@pytest.mark.parametrize("k", [1, 15, 16, 17, 65, 400])
+@pytest.mark.parametrize("density", [0.15, 0.4, 0.7])
+def test_changed_edges_of_short_rows(dg, k, density):
+    rng = np.random.default_rng(k)
+    n = 80
+    a, b = np.triu_indices(n, 1)
+    keep = rng.random(a.size) < density * rng.random(n)[a] * 1.5
+    s, d = a[keep].astype(np.int32), b[keep].astype(np.int32)
+    G = dg.Graph(n, s, d, None, undirected=True)
+    q = G.tc_attach()
+    for step in range(3):
+        batch = graphgen.update_batch(n, s, d, min(k, s.size), step, undirected=True)
+        G.apply(*batch)
+        s, d, _, _ = oracle.apply(n, s, d, np.ones(s.size, np.int32), *batch, undirected=True)
+        assert q.read() == oracle.triangles(n, s, d), step
+    G.close()
