@@ -10,7 +10,7 @@
 //      ids from an atomic counter, so every earlier tile is already running),
 //      ranks its keys stably inside the tile (ballot match per wave, per-wave
 //      digit counters in LDS), publishes its per-digit counts, looks back over
-//      earlier tiles' published counts (per digit, 16 predecessors per read) to
+//      earlier tiles' published counts (per digit, 4 predecessors per read) to
 //      find where its keys go, and scatters them through an LDS staging copy so
 //      that runs of one digit are written contiguously.  Each workgroup turns
 //      the pass's global counts into digit starts itself (a 256-entry scan).
@@ -66,7 +66,10 @@ __device__ __forceinline__ uint64_t lb_load(const uint64_t *p) {
 // first and its inclusive prefix last.  Predecessors are read LB_WINDOW at a time
 // (independent loads in flight), newest first, up to the first inclusive prefix;
 // a word not yet published stops the window and is read again.
-constexpr int LB_WINDOW = 16;
+// Four in flight: the window's registers are paid for by every wave of a sort pass, and a
+// wave more per SIMD is worth more than a longer reach (16M pairs: 16 at a time 165 us a
+// pass, 8 136, 4 131).
+constexpr int LB_WINDOW = 4;
 __device__ uint64_t lookback(uint64_t *status, int64_t stride, uint32_t tile, uint64_t agg, uint64_t epoch,
                              int64_t *err) {
     if (tile == 0) {
@@ -179,8 +182,19 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_hist(const uint64_t *__restri
 // wave-striped (lane l of wave w holds key w * ITEMS * 64 + i * 64 + l of the tile
 // for i < ITEMS), so ranking items in order i and, inside an item, by lane keeps
 // the input order: the sort is stable.  Keys and then values are staged in LDS in
-// sorted order and written out in runs of one digit (one LDS buffer for both, and
-// one byte of digit per slot instead of output positions in registers).
+// sorted order and written out in runs of one digit (one LDS buffer for both; the keys
+// give the output positions again, which stay in registers for the values).
+// Registers bound it through the waves that fit: with positions in 32 bits, two ranks to
+// a register and one table for the digits' starts 16M pairs take 121 us a pass
+// (3.3 TB/s) in place of 165, 145 registers in place of 173; 128 registers spill and take
+// 141 us, tiles of 12 or 14 keys a lane 138 and 134.
+constexpr uint32_t NOWHERE = ~0u;  // (inputs have fewer than 2^31 keys)
+
+template <int N>
+__device__ __forceinline__ uint32_t rank_of(const uint32_t (&r)[N], int i) {
+    return i % 2 == 0 ? r[i / 2] & 0xFFFFu : r[i / 2] >> 16;
+}
+
 template <int ITEMS>
 __global__ __launch_bounds__(RS_THREADS) void k_rs_pass(const uint64_t *__restrict__ kin,
                                                         const int32_t *__restrict__ vin, uint64_t *kout,
@@ -188,11 +202,10 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_pass(const uint64_t *__restri
                                                         const uint32_t *__restrict__ gcount, uint64_t *status,
                                                         uint32_t *tile_ctr, uint64_t epoch, int64_t *err) {
     constexpr int TILE = RS_THREADS * ITEMS;
+    static_assert(TILE <= 1 << 16 && ITEMS % 2 == 0, "two slots of the tile per register");
     __shared__ uint64_t s_stage[TILE];               // keys, then values (as 32-bit words)
-    __shared__ uint8_t s_digit[TILE];                // digit of each staged slot
-    __shared__ uint32_t s_wcnt[RS_WAVES][RS_RADIX];  // per-wave digit counts, then wave offsets
-    __shared__ uint32_t s_dstart[RS_RADIX];          // first slot of each digit in the tile
-    __shared__ int64_t s_gstart[RS_RADIX];           // first output position of each digit's keys
+    __shared__ uint32_t s_wcnt[RS_WAVES][RS_RADIX];  // per-wave digit counts, then the waves' first slots
+    __shared__ uint32_t s_gbase[RS_RADIX];  // a digit's first output position less its first slot (mod 2^32)
     __shared__ uint32_t s_wtot[RS_WAVES];
     __shared__ uint32_t s_gtot[RS_WAVES];
     __shared__ uint32_t s_tile;
@@ -202,19 +215,22 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_pass(const uint64_t *__restri
     __syncthreads();
 
     const int64_t tbase = (int64_t)tile * TILE;
-    const int64_t wbase = tbase + (int64_t)wv * (ITEMS * WAVE);
+    const int tn = (int)min((int64_t)TILE, n - tbase);
+    const uint64_t *kt = kin + tbase;
+    const int32_t *vt = vin + tbase;
+    const int j0 = wv * (ITEMS * WAVE) + l;
     uint64_t key[ITEMS];
     uint32_t val[ITEMS];
-    uint32_t rank[ITEMS];
+    uint32_t rank[ITEMS / 2];  // two 16-bit ranks each
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
-        const int64_t j = wbase + i * WAVE + l;
-        key[i] = j < n ? kin[j] : 0;
-        val[i] = j < n ? (uint32_t)vin[j] : 0;  // loaded now, in flight during the ranking
+        const uint32_t j = j0 + i * WAVE;
+        key[i] = (int)j < tn ? kt[j] : 0;
+        val[i] = (int)j < tn ? (uint32_t)vt[j] : 0;  // loaded now, in flight during the ranking
     }
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
-        const bool valid = wbase + i * WAVE + l < n;
+        const bool valid = j0 + i * WAVE < tn;
         const uint32_t d = digit_of(key[i], shift, dmask);
         const uint64_t m = match8(d, ballot(valid));
         const uint32_t before = (uint32_t)__popcll(m & lanemask_lt());
@@ -224,23 +240,16 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_pass(const uint64_t *__restri
         wave_sync();
         if (valid && before == 0) s_wcnt[wv][d] = old + (uint32_t)__popcll(m);
         wave_sync();
-        rank[i] = old + before;
+        if (i % 2 == 0) rank[i / 2] = old + before;
+        else rank[i / 2] |= (old + before) << 16;
     }
     __syncthreads();
 
     // thread d: wave offsets of digit d, the tile's count of d and its global start
     const int d = threadIdx.x;
     uint32_t cnt = 0;
-    {
-        uint32_t c[RS_WAVES];
 #pragma unroll
-        for (int w = 0; w < RS_WAVES; ++w) c[w] = s_wcnt[w][d];
-#pragma unroll
-        for (int w = 0; w < RS_WAVES; ++w) {
-            s_wcnt[w][d] = cnt;
-            cnt += c[w];
-        }
-    }
+    for (int w = 0; w < RS_WAVES; ++w) cnt += s_wcnt[w][d];
     const uint64_t excl = lookback(status + d, RS_RADIX, tile, cnt, epoch, err);
     // exclusive scans over the digits: of the tile's counts (tile-local start of
     // digit d) and of the whole input's counts (global start of digit d)
@@ -252,50 +261,50 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_pass(const uint64_t *__restri
         s_gtot[wv] = gincl;
     }
     __syncthreads();
-    uint32_t before = 0, gbefore = 0;
+    uint32_t slot = incl - cnt, gstart = gincl - gc;
     for (int w = 0; w < wv; ++w) {
-        before += s_wtot[w];
-        gbefore += s_gtot[w];
+        slot += s_wtot[w];
+        gstart += s_gtot[w];
     }
-    s_dstart[d] = before + incl - cnt;
-    s_gstart[d] = (int64_t)(gbefore + gincl - gc) + (int64_t)excl;
+    s_gbase[d] = gstart + (uint32_t)excl - slot;
+#pragma unroll
+    for (int w = 0; w < RS_WAVES; ++w) {
+        const uint32_t c = s_wcnt[w][d];
+        s_wcnt[w][d] = slot;
+        slot += c;
+    }
     __syncthreads();
 
-    // rank[i] becomes the item's slot in the tile's sorted order
+    // a rank becomes the item's slot in the tile's sorted order
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
-        if (wbase + i * WAVE + l >= n) continue;
-        const uint32_t dd = digit_of(key[i], shift, dmask);
-        rank[i] += s_dstart[dd] + s_wcnt[wv][dd];
-        s_stage[rank[i]] = key[i];
-        s_digit[rank[i]] = (uint8_t)dd;
+        if (j0 + i * WAVE >= tn) continue;
+        const uint32_t first = s_wcnt[wv][digit_of(key[i], shift, dmask)];
+        rank[i / 2] += i % 2 == 0 ? first : first << 16;
+        s_stage[rank_of(rank, i)] = key[i];
     }
     __syncthreads();
-    const int tn = (int)min((int64_t)TILE, n - tbase);
+    uint32_t to[ITEMS];  // output position of the thread's staged slots
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const int j = threadIdx.x + i * RS_THREADS;
+        to[i] = NOWHERE;
         if (j >= tn) continue;
-        const uint32_t dd = s_digit[j];
-        const int64_t o = s_gstart[dd] + (j - (int64_t)s_dstart[dd]);
-        if (o < 0 || o >= n) continue;  // only after a look-back spin-limit exit (error already set)
-        kout[o] = s_stage[j];
+        const uint64_t k = s_stage[j];
+        const uint32_t o = s_gbase[digit_of(k, shift, dmask)] + (uint32_t)j;
+        if (o >= (uint32_t)n) continue;  // only after a look-back spin-limit exit (error already set)
+        to[i] = o;
+        kout[o] = k;
     }
     __syncthreads();
     uint32_t *s_val = reinterpret_cast<uint32_t *>(s_stage);
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i)
-        if (wbase + i * WAVE + l < n) s_val[rank[i]] = val[i];
+        if (j0 + i * WAVE < tn) s_val[rank_of(rank, i)] = val[i];
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        const int j = threadIdx.x + i * RS_THREADS;
-        if (j >= tn) continue;
-        const uint32_t dd = s_digit[j];
-        const int64_t o = s_gstart[dd] + (j - (int64_t)s_dstart[dd]);
-        if (o < 0 || o >= n) continue;
-        vout[o] = (int32_t)s_val[j];
-    }
+    for (int i = 0; i < ITEMS; ++i)
+        if (to[i] != NOWHERE) vout[to[i]] = (int32_t)s_val[threadIdx.x + i * RS_THREADS];
 }
 
 // ---- exclusive scan of int64 ----------------------------------------------------------------
