@@ -165,10 +165,16 @@ __global__ __launch_bounds__(RS_THREADS) void k_rs_hist(const uint64_t *__restri
     __syncthreads();
     const int wv = threadIdx.x / WAVE;
     const int64_t stride = gstride();
-    for (int64_t i = gtid(); i < n; i += stride) {
-        const uint64_t k = keys[i];
+    constexpr int U = 4;  // keys in flight per lane
+    for (int64_t i0 = gtid(); i0 < n; i0 += U * stride) {
+        uint64_t k[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) k[u] = keys[min(i0 + u * stride, n - 1)];
         for (int p = 0; p < passes; ++p)
-            atomicAdd(&h[wv][p][digit_of(k, shift0 + RS_BITS * p, digit_mask(bits, RS_BITS * p))], 1u);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (i0 + u * stride < n)
+                    atomicAdd(&h[wv][p][digit_of(k[u], shift0 + RS_BITS * p, digit_mask(bits, RS_BITS * p))], 1u);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < passes * RS_RADIX; i += RS_THREADS) {
