@@ -826,14 +826,14 @@ __global__ void k_pr_rows(int64_t nb, int items, const int32_t *__restrict__ mp_
 
 // Rows, apply and reduce of one step in one launch, for graphs of up to FIN_N vertices:
 // one workgroup finishes the rows, applies the step and decides the next one.  At this
-// size each of the three launches does about 4 us of work and costs as much again, and
-// the host issues four launches a step no faster than the device runs them (16k
-// vertices, 262k arcs: 37 us a step with four launches, 31 with two, of which this
-// kernel takes 16; the batches' paths and ranks together 1610 -> 1435 us per pass).  One
-// workgroup moves about 60 GB/s, so the line lies where its time passes that of the
-// three launches: with FIN_N = 2^17 a graph of 100k vertices took 2579 us in place of 1155.
+// size each of the three launches does little and costs about 4 us.  One workgroup
+// moves about 60 GB/s, so it loses where its time passes that of the three launches:
+// ranks of a batch, in us with this kernel and with the three, 1k vertices 285 and
+// 318, 4k 240 and 282, 8k 274 and 253, 16k 333 and 264, 32k 455 and 291.  The same holds for
+// many tiles and diff-level entries, of which it takes a chain of reads per FIN_T.
 constexpr int FIN_T = 1024;
-constexpr int32_t FIN_N = 1 << 15;
+constexpr int32_t FIN_N = 1 << 12;
+constexpr int64_t FIN_ROWS = 4 * FIN_T;
 __global__ __launch_bounds__(FIN_T) void k_pr_finish_small(
     int64_t nb, int items, const int32_t *__restrict__ mp_row, const int64_t *__restrict__ mp_edge,
     const int64_t *__restrict__ off, const double *pf, const double *pl, int64_t dm,
@@ -1054,6 +1054,7 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
                            ws.mp_row.p, ws.mp_edge.p);
         DG_HIP(hipGetLastError());
     }
+    const bool small_end = tiles && g->n <= FIN_N && nb + R.dm <= FIN_ROWS;
     double *pf = ws.mp_part.p, *pl = ws.mp_part.p + nb + 1;
     const double *done = prs + 3;
     // 16-byte access to the whole vectors (an allocator of the caller's may align less)
@@ -1066,12 +1067,16 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
     constexpr int GROUP = 4;
     constexpr int SIDE_GROUP = 6;  // steps queued before the SSSP work starts beside them
     constexpr int AHEAD = 5;       // steps kept in flight while the host drives the SSSP rounds
+    // On small graphs the rounds end later than the steps, so they start after one step
+    // (16k vertices, both queries: 1,600 us per two batches with SIDE_GROUP first and
+    // AHEAD at every wait, 1,280 with one first and one a wait).
+    constexpr int32_t PUMP_N = 1 << 15;
     constexpr int RING = (int)(sizeof(ws.step_ev) / sizeof(ws.step_ev[0]));
     static_assert(RING > AHEAD, "the ring must hold the events of every step in flight");
     int32_t it = 0, launched = 0;
     *conv = 0;
     std::vector<std::pair<int, int>> slots;  // profiled launches of the group (pull, apply)
-    // one Jacobi step (four launches: pull, rows / heavy rows, apply, reduce; two on small graphs)
+    // one Jacobi step (four launches: pull, rows / heavy rows, apply, reduce; two on the smallest graphs)
     auto launch_step = [&]() -> int {
         if (!tiles) DG_TRY(counters_clear(g));  // the heavy-row queue counters of the pull
         int ps;
@@ -1081,7 +1086,7 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
             hipLaunchKernelGGL(tiles_kernel, dim3((unsigned)nb), dim3(MP_THREADS), tile_lds, s, ws.mp_row.p, ws.mp_edge.p,
                                R.off.p, R.col.p, contrib, prs + 2, damping, xn, pf, pl, done);
             prof_end(ps, s, 16.0 * (double)g->n + 12.0 * (double)R.m);
-            if (g->n <= FIN_N) {
+            if (small_end) {
                 hipLaunchKernelGGL(k_pr_finish_small, dim3(1), dim3(FIN_T), 0, s, nb, items, ws.mp_row.p,
                                    ws.mp_edge.p, R.off.p, pf, pl, R.dm, R.dkey.p, R.doff.p, R.dcol.p, R.keybits,
                                    contrib, damping, xn, g->n, x, g->fwd.deg.p, dprev, dprev2, (int)global, S, ninv,
@@ -1153,7 +1158,7 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
                 ++queued;
                 return DG_OK;
             };
-            while (queued < std::min(g->n <= FIN_N ? 1 : SIDE_GROUP, grp)) DG_TRY(queue_one());
+            while (queued < std::min(g->n <= PUMP_N ? 1 : SIDE_GROUP, grp)) DG_TRY(queue_one());
             int prc = DG_OK;
             // (one step per call: the SSSP rounds wait for the host meanwhile)
             std::function<void()> pump = [&]() {

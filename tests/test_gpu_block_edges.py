@@ -146,7 +146,7 @@ def test_small_batch_sequences(dg, k, und, diff_only):
     G.close()
 
 
-# one-workgroup end of a rank step: sizes around its threads and its limit, plain and
+# one-workgroup end of a rank step: sizes around its threads and its limits, plain and
 # extrapolated steps, rows over several tiles, dangling vertices
 @pytest.mark.parametrize("extrap", [0, 1])
 @pytest.mark.parametrize("n", [3, 1023, 1025, 4096, 4097, 32767, 32768, 32769])
@@ -273,4 +273,23 @@ def test_changed_edges_of_short_rows(dg, k, density):
         G.apply(*batch)
         s, d, _, _ = oracle.apply(n, s, d, np.ones(s.size, np.int32), *batch, undirected=True)
         assert q.read() == oracle.triangles(n, s, d), step
+    G.close()
+
+
+# the same step ends with diff levels around the entries that one workgroup takes
+@pytest.mark.parametrize("k", [3500, 4500])
+def test_rank_step_end_diff_entries(dg, k):
+    rng = np.random.default_rng(k)
+    n = 3000
+    key = rng.permutation(n * n)[: 12000 + k]
+    key = key[key // n != key % n]
+    s, d = (key // n).astype(np.int32), (key % n).astype(np.int32)
+    c = dg.Config()
+    c.merge_threshold, c.diff_only = 10.0, 1
+    G = dg.Graph(n, s[k:], d[k:], None, config=c)
+    q = G.pr_attach(0.85, 1e-9, 1000)
+    G.apply(s[:k], d[:k], np.ones(k, np.int32), np.ones(k, np.uint8))
+    want, _, _ = oracle.pagerank(n, s, d, 0.85, 1e-9, 1000)
+    rank, _, conv = q.read()
+    assert conv and np.max(np.abs(rank - want)) <= 1e-10
     G.close()
