@@ -1410,7 +1410,10 @@ __global__ void k_vacancy_rest(int64_t nk, const uint64_t *nkey, const int32_t *
 // a batch runs the same steps in two launches of one workgroup, one before the
 // pre-hooks and one after them, with its sorts in LDS.  Between steps the workgroup
 // passes a barrier and drops what its L1 holds, as a kernel boundary would.
-constexpr int SMALL_MAX = 4096;
+// The line lies where the work of one workgroup outgrows the launches: batches of 2,000
+// arcs and a path query took 277 us here and 338 in the general kernels (16k vertices),
+// 304 and 369 (1M), 3,000 arcs 354 and 351, 399 and 389, 4,000 arcs 388 and 367.
+constexpr int SMALL_MAX = 3 * WIDE_T;
 constexpr int SMALL_ITEMS = SMALL_MAX / WIDE_T;
 constexpr int SMALL_WAVES = WIDE_T / WAVE;
 

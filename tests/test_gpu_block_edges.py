@@ -102,7 +102,7 @@ def test_build_order_and_directions(dg, n, m, und):
 # batches around the limit of the one-workgroup path, in every mode, over several batches
 # (revivals, reused slots, repeats within a batch, deletions with re-insertions)
 @pytest.mark.parametrize("und", [False, True])
-@pytest.mark.parametrize("k", [1, 63, 65, 1023, 1025, 2047, 2048, 2049, 4095, 4096, 4097])
+@pytest.mark.parametrize("k", [1, 63, 65, 1023, 1025, 2047, 2048, 2049, 3071, 3072, 3073, 4095, 4096, 4097])
 @pytest.mark.parametrize("diff_only", [0, 1])
 def test_small_batch_sequences(dg, k, und, diff_only):
     rng = np.random.default_rng(7 * k + und)
