@@ -251,8 +251,13 @@ __device__ __forceinline__ uint64_t sssp_pack(int32_t dist, int32_t parent) {
 __device__ __forceinline__ int32_t sssp_dist(uint64_t k) { return (int32_t)(k >> 32); }
 __device__ __forceinline__ int32_t sssp_parent(uint64_t k) { return (int32_t)(uint32_t)(k & 0xffffffffu); }
 
+// Until this wave's stores have arrived in the L2.  A workgroup barrier does not wait for
+// them: it orders the waves among themselves, through the L1 they share.
+__device__ __forceinline__ void stores_arrive() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // The end of a kernel whose results the host polls for (publish_wait): one wave, after
-// the results are stored (by other waves: and a block barrier passed).
+// the results are stored.  Where other waves store some of them, each of those calls
+// stores_arrive() and a barrier follows: the fence here waits for its own wave only.
 __device__ __forceinline__ void publish_seq(int64_t *host_seq, int64_t seq) {
     __threadfence_system();  // the wave's stores before the number
     if (lane_id() == 0) __hip_atomic_store(host_seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);

@@ -102,6 +102,7 @@ __global__ __launch_bounds__(UNPACK_T) void k_set_unpack_one(int64_t nl, const u
             }
         }
     }
+    stores_arrive();
     __syncthreads();
     if (threadIdx.x < WAVE) publish_seq(host_seq, seq);
 }
