@@ -29,6 +29,12 @@ static inline int grid_for(int64_t n) {
     return (int)(g < 1 ? 1 : (g > 8192 ? 8192 : g));
 }
 
+// Blocks of WIDE_T threads (kernels that add into one shared counter).
+static inline int grid_wide(int64_t n) {
+    const int64_t g = (n + WIDE_T - 1) / WIDE_T;
+    return (int)(g < 1 ? 1 : (g > 512 ? 512 : g));
+}
+
 // A value that is the same in every lane, in scalar registers.
 __device__ __forceinline__ int64_t wave_first(int64_t v) {
     return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
@@ -448,22 +454,31 @@ __global__ __launch_bounds__(256) void k_tc_orient(int32_t n, const int64_t *__r
 // ends pend[x] are needed.  *out_of_order becomes non-zero if a degree rises with the id;
 // the lists are then built, because order by outdated degrees could leave a list
 // as long as its row.  262k vertices, 8.4M entries: 12 us in place of 450 for the two
-// passes of k_tc_orient and their scan.
-__global__ __launch_bounds__(256) void k_tc_prefix(int32_t n, const int64_t *__restrict__ off,
-                                                   const int32_t *__restrict__ col, const int32_t *__restrict__ deg,
-                                                   int64_t *pend, int64_t *out_of_order) {
-    bool bad = false;
-    for (int64_t x = gtid(); x < n; x += gstride()) {
-        bad |= x + 1 < n && deg[x] < deg[x + 1];
-        int64_t lo = off[x], hi = off[x + 1];
+// passes of k_tc_orient and their scan.  *low counts the entries below x that are below
+// `ids` too (k_tc_forward's choice).
+__global__ __launch_bounds__(WIDE_T) void k_tc_prefix(int32_t n, const int64_t *__restrict__ off,
+                                                      const int32_t *__restrict__ col,
+                                                      const int32_t *__restrict__ deg, int32_t ids, int64_t *pend,
+                                                      int64_t *out_of_order, int64_t *low) {
+    __shared__ BlockScratch sc;
+    const auto below = [&](int64_t lo, int64_t hi, uint32_t v) {
         while (lo < hi) {
             const int64_t mid = (lo + hi) >> 1;
-            if (((uint32_t)col[mid] & ID_MASK) < (uint32_t)x) lo = mid + 1;
+            if (((uint32_t)col[mid] & ID_MASK) < v) lo = mid + 1;
             else hi = mid;
         }
-        pend[x] = lo;
+        return lo;
+    };
+    bool bad = false;
+    int64_t few = 0;
+    for (int64_t x = gtid(); x < n; x += gstride()) {
+        bad |= x + 1 < n && deg[x] < deg[x + 1];
+        const int64_t s = off[x], e = below(s, off[x + 1], (uint32_t)x);
+        pend[x] = e;
+        few += (x <= ids ? e : below(s, e, (uint32_t)ids)) - s;
     }
     if (ballot(bad) != 0 && lane_id() == 0) *out_of_order = 1;
+    block_count<WIDE_T>(low, few, sc);
 }
 
 // Every triangle, ranked a < b < c, is counted once: at x = a and y = b, as the
@@ -473,16 +488,25 @@ __global__ __launch_bounds__(256) void k_tc_prefix(int32_t n, const int64_t *__r
 // or, when N+(y) is much longer, take the elements of N+(x) and binary-search N+(y)
 // in memory (262k vertices, 4.2M edges: 620M lookups and 0.5M searched lists).
 //
-// BITS (graphs in the degree order): forward lists point to vertices of higher degree,
-// so most of their ids are small, and the copy is a bitmap of the ids below TCF_IDS: a
-// lookup is one LDS read where the search of a sorted copy takes up to ten.  Larger
-// ids are searched in the list's tail in memory.  Graphs in the order given keep the
-// sorted copy.  (A hash set of the same size was slower than either: 2.44 ms against
-// 1.56 ms for the search; the bitmap took 0.80 ms, bound by the instructions around a
-// lookup, and 0.41 ms with the lists whose ids are all in its range read by bits_hits.)
+// BITS: forward lists of skewed graphs in the degree order point to vertices of higher
+// degree, so most of their ids are small, and the copy is a bitmap of the ids below
+// TCF_IDS: a lookup is one LDS read where the search of a sorted copy takes up to ten.
+// Larger ids are searched in the list's tail in memory, which costs more than the sorted
+// copy where many entries are large, so the bitmap is taken from TCF_LOW of the entries
+// below TCF_IDS on (us a count with the bitmap and with the copy, lists in place:
+// R-MAT 18 with 16 edges a vertex, share 0.99, 425 and 1516; R-MAT 22, 0.79, 6081 and 14310;
+// a power law of 1M vertices, 0.65, 1283 and 1338; even degrees, 100k vertices, 0.61, 600
+// and 543; 262k, 0.28, 2279 and 1334; 1M, 0.08, 10830 and 5135).  (A hash set of the same
+// size was slower than either: 2.44 ms against 1.56 ms for the search; the bitmap took
+// 0.80 ms, bound by the instructions around a lookup, and 0.41 ms with the lists whose ids
+// are all in its range read by bits_hits.)
+constexpr double TCF_LOW = 0.625;
 constexpr int TCF_CAP = 1024;  // forward-list entries of a row staged in LDS, per wave
 constexpr int TCF_IDS = 32 * TCF_CAP;
-constexpr int TCF_BLOCKS = 8192;  // four or more grids of resident blocks, few enough adds to the total
+// Four or more grids of resident blocks, few enough adds to the total.  The copy's counts are
+// longer and gain from shorter blocks: R-MAT 20 in the order given 90.9 and 74.2 ms with
+// 8,192 and 32,768, the bitmap's R-MAT 18 425 and 604 us.
+constexpr int TCF_BLOCKS = 8192, TCF_BLOCKS_COPY = 32768;
 
 __device__ __forceinline__ bool lds_has(const int32_t *a, int len, int32_t v) {
     int lo = 0, hi = len;
@@ -546,21 +570,28 @@ __global__ __launch_bounds__(256) void k_tc_forward(int32_t n, const int64_t *__
                                                     const int64_t *__restrict__ oe,
                                                     const int32_t *__restrict__ ocol,
                                                     unsigned long long *total) {
-    __shared__ int32_t s_nx[256 / WAVE][TCF_CAP];
+    __shared__ __align__(8) int32_t s_nx[256 / WAVE][TCF_CAP];
     const int64_t wave_global = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / WAVE;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) / WAVE;
     const int l = lane_id();
     int32_t *sx = s_nx[threadIdx.x / WAVE];
     uint64_t acc = 0;
+    // the copy leaves the last words of the first wave's LDS to the block's sum (with more
+    // LDS than 16 KB fewer blocks share a CU)
+    unsigned long long *s_sum = reinterpret_cast<unsigned long long *>(&s_nx[0][TCF_CAP - 4]);
+    int32_t *s_ended = &s_nx[0][TCF_CAP - 2];
     if (BITS) {
         for (int j = l; j < TCF_CAP; j += WAVE) sx[j] = 0;
         wave_sync();
+    } else {
+        if (threadIdx.x < 4) s_nx[0][TCF_CAP - 4 + threadIdx.x] = 0;
+        __syncthreads();
     }
     for (int64_t x = wave_global; x < n; x += nwaves) {
         const int64_t xs = ob[x], xe = oe[x];
         const int64_t dx = xe - xs;
         if (dx < 2) continue;
-        const bool staged = BITS || dx <= TCF_CAP;
+        const bool staged = BITS || dx <= TCF_CAP - 4;
         int64_t tail = xe;  // BITS: the first entry with an id of TCF_IDS or more
         if (BITS) {
             int64_t small = 0;
@@ -575,10 +606,8 @@ __global__ __launch_bounds__(256) void k_tc_forward(int32_t n, const int64_t *__
             for (int64_t j = l; j < dx; j += WAVE) sx[j] = ocol[xs + j];
             wave_sync();
         }
-        // whether v (-1: none) is in N+(x)
-        auto has = [&](int32_t v) {
-            if (!BITS) return v >= 0 && lds_has(sx, (int)dx, v);
-            if (v < TCF_IDS) return v >= 0 && ((uint32_t)sx[v >> 5] >> (v & 31) & 1u) != 0;
+        const auto in_bits = [&](int32_t v) {
+            if (v < TCF_IDS) return ((uint32_t)sx[v >> 5] >> (v & 31) & 1u) != 0;
             return tail < xe && find_sorted(ocol, tail, xe, (uint32_t)v) >= 0;
         };
         const int64_t rx = (dx + WAVE - 1) / WAVE;
@@ -597,9 +626,12 @@ __global__ __launch_bounds__(256) void k_tc_forward(int32_t n, const int64_t *__
                 rest &= ~low;
                 acc += bits_hits(sx, ocol, mys, (int32_t)(mye - mys), low, l);
             }
-            while (rest) {
-                const int k = __builtin_ctzll(rest);
-                rest &= rest - 1;
+            const int cnt = (int)(dx - p0 < WAVE ? dx - p0 : WAVE);
+            for (int k = 0; BITS ? rest != 0 : k < cnt; ++k) {
+                if (BITS) {
+                    k = __builtin_ctzll(rest);
+                    rest &= rest - 1;
+                }
                 const int64_t ys = __shfl(mys, k, WAVE), ye = __shfl(mye, k, WAVE);
                 const int64_t dy = ye - ys;
                 if (staged && (dy + WAVE - 1) / WAVE <= 4 * rx) {
@@ -610,7 +642,7 @@ __global__ __launch_bounds__(256) void k_tc_forward(int32_t n, const int64_t *__
                         for (int u = 0; u < 4; ++u) v[u] = j0 + u * WAVE < ye ? ocol[j0 + u * WAVE] : -1;
 #pragma unroll
                         for (int u = 0; u < 4; ++u)
-                            if (has(v[u])) ++acc;
+                            if (v[u] >= 0 && (BITS ? in_bits(v[u]) : lds_has(sx, (int)dx, v[u]))) ++acc;
                     }
                 } else {
                     for (int64_t j = xs + l; j < xe; j += WAVE)
@@ -626,13 +658,24 @@ __global__ __launch_bounds__(256) void k_tc_forward(int32_t n, const int64_t *__
     }
     // one add per block: a wave's add to the one total costs about 12 ns of a serial
     // chain (262k rows, 131k waves: 2.19 ms with an add per wave)
-    __shared__ uint64_t s_acc[256 / WAVE];
     acc = wave_sum(acc);
-    if (l == 0) s_acc[threadIdx.x / WAVE] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int q = 1; q < 256 / WAVE; ++q) acc += s_acc[q];
-        if (acc) atomicAdd(total, (unsigned long long)acc);
+    if (BITS) {
+        __shared__ uint64_t s_acc[256 / WAVE];
+        if (l == 0) s_acc[threadIdx.x / WAVE] = acc;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int q = 1; q < 256 / WAVE; ++q) acc += s_acc[q];
+            if (acc) atomicAdd(total, (unsigned long long)acc);
+        }
+    } else if (l == 0) {
+        // the last wave to end adds; waves that end before it do not wait in their slots
+        // (a barrier here: R-MAT 20 in the order given 74.1 ms, without 67.9)
+        atomicAdd(s_sum, (unsigned long long)acc);
+        wave_sync();
+        if (atomicAdd(s_ended, 1) == 256 / WAVE - 1) {
+            const unsigned long long all = atomicAdd(s_sum, 0ull);
+            if (all) atomicAdd(total, all);
+        }
     }
 }
 
@@ -646,14 +689,16 @@ int tc_count_static(dg_graph *g, uint64_t *count) {
     // the forward list of x: entries ob[x] to oe[x] of ocol
     const int64_t *ob = F.off.p, *oe = g->ws.scan64.p;
     const int32_t *ocol = F.col.p;
-    bool ordered = false;
+    bool ordered = false, bits = false;
     if (g->relabeled) {
         DG_TRY(counters_clear(g));
-        hipLaunchKernelGGL(k_tc_prefix, dim3(grid_for(n)), dim3(256), 0, s, n, F.off.p, F.col.p, F.deg.p,
-                           g->ws.scan64.p, g->ws.dcnt + C_TC0);
+        hipLaunchKernelGGL(k_tc_prefix, dim3(grid_wide(n)), dim3(WIDE_T), 0, s, n, F.off.p, F.col.p, F.deg.p, TCF_IDS,
+                           g->ws.scan64.p, g->ws.dcnt + C_TC0, g->ws.dcnt + C_AUX0);
         DG_HIP(hipGetLastError());
         DG_TRY(counters_read(g));
         ordered = g->ws.hcnt[C_TC0] == 0;
+        // (out of order the built lists differ, but batches change few of their entries)
+        bits = (double)g->ws.hcnt[C_AUX0] >= TCF_LOW * (double)(F.m / 2);
     }
     if (!ordered) {
         // the merge's spare target buffers hold the oriented lists (m / 2 entries)
@@ -672,8 +717,9 @@ int tc_count_static(dg_graph *g, uint64_t *count) {
     }
     DG_TRY(counters_clear(g));
     unsigned long long *acc = reinterpret_cast<unsigned long long *>(g->ws.dcnt + C_TC1);
-    hipLaunchKernelGGL(g->relabeled ? k_tc_forward<true> : k_tc_forward<false>, dim3(std::min(blocks, TCF_BLOCKS)),
-                       dim3(256), 0, s, n, ob, oe, ocol, acc);
+    hipLaunchKernelGGL(bits ? k_tc_forward<true> : k_tc_forward<false>,
+                       dim3(std::min(blocks, bits ? TCF_BLOCKS : TCF_BLOCKS_COPY)), dim3(256), 0, s, n, ob, oe, ocol,
+                       acc);
     DG_HIP(hipGetLastError());
     DG_TRY(counters_read(g));
     *count = (uint64_t)g->ws.hcnt[C_TC1];
