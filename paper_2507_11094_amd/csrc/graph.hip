@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <cstring>
 
+#include "degree_plan.h"
 #include "dg_device.h"
 
 namespace dg {
@@ -374,13 +375,8 @@ static int dir_from_sorted(dg_graph *g, Dir &d, const uint64_t *keys, const int3
 }
 
 // Degrees of an edge list.  One add in memory per arc would run at 14 G/s (1.2 ms for
-// 16.7M arcs), so the ids are first parted by their top bits (one pass of the radix
-// sort) and each part is counted in LDS by DEG_COPIES blocks, one share of the part
-// and one copy of the counts each.
-constexpr int DEG_PARTS_BITS = 8, DEG_PARTS = 1 << DEG_PARTS_BITS;
-constexpr int DEG_COPIES = 8;
-constexpr int DEG_RANGE = 8192;  // ids counted at a time (32 KB)
-
+// 16.7M arcs), so the ids are first parted by their top bits (passes of the radix sort)
+// and each part is counted in LDS by a few blocks (degree_plan.h).
 __global__ void k_degree_keys(int64_t m, const int32_t *a, const int32_t *b, uint64_t *keys) {
     for (int64_t i = gtid(); i < m; i += gstride()) {
         keys[i] = (uint64_t)a[i];
@@ -388,17 +384,18 @@ __global__ void k_degree_keys(int64_t m, const int32_t *a, const int32_t *b, uin
     }
 }
 
-// cnt[copy * n + v] = keys equal to v in this copy's share of v's part.  Parts hold the
-// ids p << shift .. (p + 1) << shift and are the ranges start[p] .. start[p + 1] of keys.
+// cnt[copy * n + v] = keys equal to v in this copy's share of v's part, block p * copies +
+// copy.  Parts hold the ids p << shift .. (p + 1) << shift and are the ranges start[p] ..
+// start[p + 1] of keys.
 // (A skewed part may be a tenth of the arcs: four keys per thread in flight.)
 __global__ __launch_bounds__(WIDE_T) void k_degree_count(const uint64_t *keys, const int64_t *start, int shift,
-                                                         int32_t n, int32_t *cnt) {
+                                                         int copies, int32_t n, int32_t *cnt) {
     __shared__ int32_t h[DEG_RANGE];
-    const int p = blockIdx.x / DEG_COPIES, copy = blockIdx.x % DEG_COPIES;
+    const int64_t p = blockIdx.x / copies, copy = blockIdx.x % copies;
     const int64_t s = start[p], len = start[p + 1] - s;
-    const int64_t e0 = s + len * copy / DEG_COPIES, e1 = s + len * (copy + 1) / DEG_COPIES;
-    const int64_t v1 = min((int64_t)(p + 1) << shift, (int64_t)n);
-    for (int64_t v0 = (int64_t)p << shift; v0 < v1; v0 += DEG_RANGE) {
+    const int64_t e0 = s + len * copy / copies, e1 = s + len * (copy + 1) / copies;
+    const int64_t v1 = min((p + 1) << shift, (int64_t)n);
+    for (int64_t v0 = p << shift; v0 < v1; v0 += DEG_RANGE) {
         const int r = (int)min((int64_t)DEG_RANGE, v1 - v0);
         for (int i = threadIdx.x; i < r; i += WIDE_T) h[i] = 0;
         __syncthreads();
@@ -414,7 +411,7 @@ __global__ __launch_bounds__(WIDE_T) void k_degree_count(const uint64_t *keys, c
             }
         }
         __syncthreads();
-        for (int i = threadIdx.x; i < r; i += WIDE_T) cnt[(int64_t)copy * n + v0 + i] = h[i];
+        for (int i = threadIdx.x; i < r; i += WIDE_T) cnt[copy * n + v0 + i] = h[i];
         __syncthreads();
     }
 }
@@ -453,22 +450,23 @@ static int vertex_order_build(dg_graph *g, int64_t m, const int32_t *src, const 
     DG_TRY(ws.iw_s.ensure(cap));
     DG_TRY(g->perm.ensure((size_t)n + 1));
     DG_TRY(g->iperm.ensure((size_t)n + 1));
+    const DegreePlan plan = degree_plan(B, n, arcs);
+    const int parts = 1 << plan.part_bits, shift = B - plan.part_bits;
     DBuf<int32_t> cnt;
-    DG_TRY(cnt.ensure((size_t)DEG_COPIES * n));
-    DG_TRY(ws.scan64.ensure(DEG_PARTS + 1));
-    const int shift = std::max(0, B - DEG_PARTS_BITS);
+    DG_TRY(cnt.ensure((size_t)plan.copies * n));
+    DG_TRY(ws.scan64.ensure((size_t)parts + 1));
     if (m > 0)
         hipLaunchKernelGGL(k_degree_keys, dim3(grid_for(m)), dim3(256), 0, s, m, src,
                            g->undirected ? dst : (const int32_t *)nullptr, ws.ikey.p);
     DG_HIP(hipGetLastError());
     // (the values the sort carries along mean nothing here)
-    DG_TRY(radix_sort_pairs(s, ws.sw, ws.ikey.p, ws.ikey_s.p, ws.iw.p, ws.iw_s.p, arcs, B - shift,
-                            ws.dcnt + C_SORT_ERR, shift));
-    hipLaunchKernelGGL(k_row_offsets, dim3(grid_for(DEG_PARTS + 1)), dim3(256), 0, s, DEG_PARTS, ws.ikey_s.p, arcs,
-                       shift, ws.scan64.p);
-    hipLaunchKernelGGL(k_degree_count, dim3(DEG_PARTS * DEG_COPIES), dim3(WIDE_T), 0, s, ws.ikey_s.p, ws.scan64.p, shift,
-                       n, cnt.p);
-    hipLaunchKernelGGL(k_order_keys, dim3(grid_for(n)), dim3(256), 0, s, n, DEG_COPIES, cnt.p, ws.ikey.p, ws.iw.p);
+    DG_TRY(radix_sort_pairs(s, ws.sw, ws.ikey.p, ws.ikey_s.p, ws.iw.p, ws.iw_s.p, arcs,
+                            plan.part_bits, ws.dcnt + C_SORT_ERR, shift));
+    hipLaunchKernelGGL(k_row_offsets, dim3(grid_for(parts + 1)), dim3(256), 0, s, parts, ws.ikey_s.p, arcs, shift,
+                       ws.scan64.p);
+    hipLaunchKernelGGL(k_degree_count, dim3(parts * plan.copies), dim3(WIDE_T), 0, s, ws.ikey_s.p, ws.scan64.p, shift,
+                       plan.copies, n, cnt.p);
+    hipLaunchKernelGGL(k_order_keys, dim3(grid_for(n)), dim3(256), 0, s, n, plan.copies, cnt.p, ws.ikey.p, ws.iw.p);
     DG_HIP(hipGetLastError());
     DG_TRY(sort_pairs(g, ws.ikey.p, ws.ikey_s.p, ws.iw.p, ws.iw_s.p, n, B));
     hipLaunchKernelGGL(k_perm_from_order, dim3(grid_for(n)), dim3(256), 0, s, n, ws.iw_s.p, g->perm.p,
