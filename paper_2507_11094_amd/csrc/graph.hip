@@ -438,7 +438,9 @@ __global__ void k_perm_from_order(int32_t n, const int32_t *order, int32_t *perm
 // perm / iperm of the degree order of a validated edge list: the out-degree (the
 // degree, undirected) of every given id, then a sort by it.  Counting takes the place
 // of a whole sort of the arcs, which only served to find the row lengths.
-static int vertex_order_build(dg_graph *g, int64_t m, const int32_t *src, const int32_t *dst, int B) {
+// (cnt: memory for the counts)
+static int vertex_order_fill(dg_graph *g, int64_t m, const int32_t *src, const int32_t *dst, int B,
+                             DBuf<int32_t> &cnt) {
     hipStream_t s = g->stream;
     Work &ws = g->ws;
     const int32_t n = g->n;
@@ -452,7 +454,6 @@ static int vertex_order_build(dg_graph *g, int64_t m, const int32_t *src, const 
     DG_TRY(g->iperm.ensure((size_t)n + 1));
     const DegreePlan plan = degree_plan(B, n, arcs);
     const int parts = 1 << plan.part_bits, shift = B - plan.part_bits;
-    DBuf<int32_t> cnt;
     DG_TRY(cnt.ensure((size_t)plan.copies * n));
     DG_TRY(ws.scan64.ensure((size_t)parts + 1));
     if (m > 0)
@@ -473,9 +474,18 @@ static int vertex_order_build(dg_graph *g, int64_t m, const int32_t *src, const 
                        g->iperm.p);
     DG_HIP(hipGetLastError());
     DG_HIP(hipStreamSynchronize(s));
-    IdleFrees idle;
-    cnt.release();
     return DG_OK;
+}
+
+static int vertex_order_build(dg_graph *g, int64_t m, const int32_t *src, const int32_t *dst, int B) {
+    DBuf<int32_t> cnt;
+    const int rc = vertex_order_fill(g, m, src, dst, B, cnt);
+    if (rc == DG_OK) {
+        IdleFrees idle;
+        cnt.release();
+    }
+    cnt.release();
+    return rc;
 }
 
 int vertex_in(dg_graph *g, int32_t v, int32_t *out) {
