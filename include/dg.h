@@ -186,10 +186,14 @@ const char *dg_last_error(void);
 /* Device allocator hook for all library allocations (default hipMalloc/hipFree,
  * with up to 4 GiB of what destroyed graphs and queries held kept for later
  * allocations of the process).  Must be set before any graph exists; alloc returns
- * NULL on failure.  Every call gives the kept memory back, also
+ * NULL on failure.  Every accepted call gives the kept memory back, also
  * dg_set_allocator(NULL, NULL, NULL). */
 int dg_set_allocator(void *(*alloc)(size_t bytes, void *ctx), void (*free_fn)(void *p, void *ctx),
                      void *ctx);
+
+/* Give the kept memory back to the device, at any time and from any thread: for a
+ * program whose other allocations need it while graphs stay resident. */
+int dg_release_memory(void);
 
 /* ---- graph ----------------------------------------------------------------------- */
 

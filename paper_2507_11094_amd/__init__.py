@@ -36,7 +36,7 @@ DG_NOALLOC_MAX_HOST_N = 522240
 
 # Every symbol include/dg.h declares (checked by the tests against the .so).
 EXPORTS = (
-    "dg_last_error", "dg_set_allocator", "dg_graph_create", "dg_graph_destroy",
+    "dg_last_error", "dg_set_allocator", "dg_release_memory", "dg_graph_create", "dg_graph_destroy",
     "dg_graph_set_stream", "dg_graph_info", "dg_graph_export", "dg_graph_merge",
     "dg_apply_batch", "dg_snapshot_save", "dg_snapshot_restore", "dg_snapshot_free",
     "dg_sssp_attach", "dg_pr_attach", "dg_tc_attach", "dg_query_detach", "dg_sssp_read",
@@ -113,6 +113,7 @@ def load_library() -> ctypes.CDLL:
     sig = {
         "dg_last_error": ([], ctypes.c_char_p),
         "dg_set_allocator": ([P, P, P], ctypes.c_int),
+        "dg_release_memory": ([], ctypes.c_int),
         "dg_graph_create": ([I32, I64, P, P, P, U32, P, ctypes.POINTER(P)], ctypes.c_int),
         "dg_graph_destroy": ([P], ctypes.c_int),
         "dg_graph_set_stream": ([P, P], ctypes.c_int),
@@ -315,6 +316,11 @@ def use_default_allocator() -> None:
     global _hook
     _check(load_library().dg_set_allocator(None, None, None))
     _hook = None
+
+
+def release_memory() -> None:
+    """Give the device memory kept from closed graphs back (graphs may be open)."""
+    _check(load_library().dg_release_memory())
 
 
 # ---------------------------------------------------------------------------- classes

@@ -35,8 +35,8 @@ int set_error(int code, const char *fmt, ...) {
 // up goes to a pool, from which dmalloc serves blocks of about the same size.  Only
 // memory that no queued work uses enters it (IdleFrees: the owner has waited for its
 // streams); every other free still is a hipFree.  The pool holds at most POOL_MAX bytes
-// per process (oldest blocks leave first) and is emptied when an allocation fails and
-// by dg_set_allocator; a caller's allocator bypasses it.  It knows blocks by their
+// per process (oldest blocks leave first) and is emptied when an allocation fails, by
+// dg_release_memory and by dg_set_allocator; a caller's allocator bypasses it.  It knows blocks by their
 // address only while they are in use, and serves any thread and stream.
 constexpr size_t POOL_MAX = (size_t)4 << 30;
 
@@ -290,6 +290,11 @@ int dg_set_allocator(void *(*alloc)(size_t, void *), void (*free_fn)(void *, voi
     g_alloc = alloc;
     g_free = free_fn;
     g_ctx = ctx;
+    return DG_OK;
+}
+
+int dg_release_memory(void) {
+    pool().trim();
     return DG_OK;
 }
 
