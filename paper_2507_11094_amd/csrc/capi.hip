@@ -5,12 +5,11 @@
 #include <atomic>
 #include <cstdarg>
 #include <cstring>
-#include <map>
 #include <mutex>
-#include <unordered_map>
 #include <vector>
 
 #include "dg_internal.h"
+#include "memory_pool.h"
 
 namespace dg {
 
@@ -32,99 +31,26 @@ int set_error(int code, const char *fmt, ...) {
 // hipMalloc and hipFree map and unmap pages and hipFree waits for the device: a graph of
 // 1M vertices and 16M arcs spent 6 of 14.5 ms per load in them, one of 262k vertices and 4M
 // edges 9 of 13.  So memory that a destroyed graph or query, or a finished build, gives
-// up goes to a pool, from which dmalloc serves blocks of about the same size.  Only
-// memory that no queued work uses enters it (IdleFrees: the owner has waited for its
-// streams); every other free still is a hipFree.  The pool holds at most POOL_MAX bytes
-// per process (oldest blocks leave first) and is emptied when an allocation fails, by
-// dg_release_memory and by dg_set_allocator; a caller's allocator bypasses it.  It knows blocks by their
-// address only while they are in use, and serves any thread and stream.
+// up goes to a pool (memory_pool.h), from which dmalloc serves blocks of about the same
+// size.  Only memory that no queued work uses enters it (IdleFrees: the owner has waited
+// for its streams); every other free still is a hipFree.  The pool holds at most POOL_MAX
+// bytes per process (oldest blocks leave first) and is emptied when an allocation fails, by
+// dg_release_memory and by dg_set_allocator; a caller's allocator bypasses it.  It knows
+// blocks by their address only while they are in use, and serves any thread and stream.
 constexpr size_t POOL_MAX = (size_t)4 << 30;
 
 namespace {
-struct Pool {
-    struct Block {
-        void *p;
-        size_t bytes;
-        int dev;
-        uint64_t age;
-    };
-    std::mutex mu;
-    std::multimap<size_t, Block> idle;                             // by size
-    std::unordered_map<void *, std::pair<size_t, int>> allocated;  // of blocks in use
-    size_t held = 0;
-    uint64_t clock = 0;
-
-    // Sizes step by an eighth of their power of two, so that blocks of about the same
-    // size are of the same size.
-    static size_t round(size_t n) {
-        size_t g = 256;
-        while (g * 16 <= n) g *= 2;
-        return (n + g - 1) / g * g;
-    }
-    void *take(size_t bytes, int dev) {
-        std::lock_guard<std::mutex> l(mu);
-        for (auto it = idle.lower_bound(bytes); it != idle.end() && it->first <= bytes + bytes / 4; ++it) {
-            if (it->second.dev != dev) continue;
-            void *p = it->second.p;
-            allocated[p] = {it->first, dev};
-            held -= it->first;
-            idle.erase(it);
-            return p;
-        }
-        return nullptr;
-    }
-    void note(void *p, size_t bytes, int dev) {
-        std::lock_guard<std::mutex> l(mu);
-        allocated[p] = {bytes, dev};
-    }
-    // False: the caller frees p itself.
-    bool give(void *p, bool keep) {
-        std::vector<void *> out;
-        bool kept = false;
-        {
-            std::lock_guard<std::mutex> l(mu);
-            auto it = allocated.find(p);
-            if (it == allocated.end()) return false;
-            const size_t bytes = it->second.first;
-            const int dev = it->second.second;
-            allocated.erase(it);
-            if (keep && bytes <= POOL_MAX) {
-                while (held + bytes > POOL_MAX) {
-                    auto old = idle.begin();
-                    for (auto i = idle.begin(); i != idle.end(); ++i)
-                        if (i->second.age < old->second.age) old = i;
-                    held -= old->first;
-                    out.push_back(old->second.p);
-                    idle.erase(old);
-                }
-                idle.emplace(bytes, Block{p, bytes, dev, ++clock});
-                held += bytes;
-                kept = true;
-            }
-        }
-        for (void *q : out) (void)hipFree(q);
-        return kept;
-    }
-    void trim() {
-        std::multimap<size_t, Block> out;
-        {
-            std::lock_guard<std::mutex> l(mu);
-            out.swap(idle);
-            held = 0;
-        }
-        for (auto &b : out) (void)hipFree(b.second.p);
-    }
-};
 // (never destroyed: graphs may outlive the statics of other files, and the memory goes
 // with the process)
-Pool &pool() {
-    static Pool *p = new Pool();
+MemoryPool &pool() {
+    static MemoryPool *p = new MemoryPool(POOL_MAX, [](void *q) { (void)hipFree(q); });
     return *p;
 }
 thread_local bool t_idle_frees = false;
 std::mutex g_blocks_mu;
-std::vector<int64_t *> g_blocks;  // counter blocks given up (pinned host memory, 3 KB each)
-constexpr size_t BLOCKS_MAX = 64;
+constexpr int BLOCKS_MAX = 64;
+int64_t *g_blocks[BLOCKS_MAX];  // counter blocks given up (pinned host memory, 3 KB each)
+int g_nblocks = 0;
 }  // namespace
 
 IdleFrees::IdleFrees() : before(t_idle_frees) { t_idle_frees = true; }
@@ -135,7 +61,7 @@ void *dmalloc(size_t bytes) {
     if (g_alloc) return g_alloc(bytes, g_ctx);
     int dev = 0;
     (void)hipGetDevice(&dev);
-    bytes = Pool::round(bytes);
+    bytes = MemoryPool::round(bytes);
     void *p = pool().take(bytes, dev);
     if (p) return p;
     if (hipMalloc(&p, bytes) != hipSuccess) {
@@ -161,10 +87,7 @@ int64_t *counter_block_alloc() {
     int64_t *p = nullptr;
     {
         std::lock_guard<std::mutex> l(g_blocks_mu);
-        if (!g_blocks.empty()) {
-            p = g_blocks.back();
-            g_blocks.pop_back();
-        }
+        if (g_nblocks > 0) p = g_blocks[--g_nblocks];
     }
     if (!p && hipHostMalloc((void **)&p, bytes, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) !=
                   hipSuccess) {
@@ -178,8 +101,8 @@ int64_t *counter_block_alloc() {
 void counter_block_free(int64_t *p) {
     {
         std::lock_guard<std::mutex> l(g_blocks_mu);
-        if (t_idle_frees && g_blocks.size() < BLOCKS_MAX) {
-            g_blocks.push_back(p);
+        if (t_idle_frees && g_nblocks < BLOCKS_MAX) {
+            g_blocks[g_nblocks++] = p;
             return;
         }
     }
