@@ -1,5 +1,5 @@
-"""The pool of kept device memory (csrc/memory_pool.h), compiled by the host compiler: its
-bound, the oldest block leaving first, one device's blocks
+"""The pool of kept device memory (csrc/memory_pool.h), compiled by the host compiler: what
+it takes beyond a request, its bound, the oldest block leaving first, one device's blocks
 not serving another, and a host that runs out of memory at every point in turn."""
 import os
 import subprocess
@@ -57,7 +57,7 @@ int main(int, char **a) {
     if (a[1][0] == 'r') {
         for (size_t n = 1; n < ((size_t)1 << 40); n += 1 + n / 7) {
             const size_t r = Pool::round(n);
-            assert(r >= n && r - n <= 256 + n / 8);
+            assert(r >= n && r - n < (64 << 10) && r - n <= 256 + n / 8);
         }
     } else if (a[1][0] == 'b') {
         Pool q(1000, dev_free);
