@@ -151,7 +151,9 @@ __device__ __forceinline__ bool find_fenced(const uint32_t *f, int nf, int strid
     return true;
 }
 
-// Per-block partials (no contended atomics; summed in block order by k_tc_sum).
+// Per-block partials (no contended atomics; summed in block order by k_tc_sum): 6 x the
+// changed triangles, the entries walked, and the other words of 4 bytes read (row bounds
+// and search steps).
 __device__ __forceinline__ void tc_block_part(uint64_t acc, uint64_t walked, uint64_t probes, int64_t *part) {
     __shared__ uint64_t s_p[3][256 / WAVE];
     acc = wave_sum(acc);
@@ -169,6 +171,11 @@ __device__ __forceinline__ void tc_block_part(uint64_t acc, uint64_t walked, uin
         for (int q = 0; q < (int)blockDim.x / WAVE; ++q) s += s_p[threadIdx.x][q];
         part[3 * (int64_t)blockIdx.x + threadIdx.x] = (int64_t)s;
     }
+}
+
+// Reads of a binary search of len entries.
+__device__ __forceinline__ int search_steps(int64_t len) {
+    return len > 0 ? 64 - __clzll((unsigned long long)len) : 0;
 }
 
 // Work items: a changed edge's shorter row is cut into pieces of TC_CHUNK entries,
@@ -227,15 +234,15 @@ __global__ __launch_bounds__(256) void k_tc_items(int64_t ne, const int32_t *__r
             const int32_t sv = __shfl(a, k, WAVE), lv = __shfl(b, k, WAVE);
             const RowRef ra = row_ref(off, doff, sv), rb = row_ref(off, doff, lv);
             const uint32_t x = j < ra.db ? (uint32_t)col[ra.ob + j] : (uint32_t)dcol[ra.od + (j - ra.db)];
-            if (e0 + l >= total || (x & DEAD)) continue;
+            if (e0 + l >= total) continue;
+            probes += search_steps(rb.db) + search_steps(rb.dd);
+            if (x & DEAD) continue;
             uint32_t x2;
             if (!row_find(col, dcol, rb, x & ID_MASK, x2)) continue;
             acc += (uint64_t)(6 / (1 + ((x & MARK) ? 1 : 0) + ((x2 & MARK) ? 1 : 0)));
         }
-        if (l == 0) {
-            walked += total;
-            probes += total * 12;
-        }
+        if (l < TC_WINDOW && i < ne) probes += 8;
+        if (l == 0) walked += total;
     }
     tc_block_part(acc, walked, probes, part);
 }
@@ -289,12 +296,10 @@ __global__ __launch_bounds__(256) void k_tc_delta(int64_t ne, const int32_t *eu,
             wave_sync();
         }
         // global reads of one probe: the whole binary search, or the segment's
-        const int64_t seg = fenced ? stride : rb.db;
-        const int depth = (seg > 0 ? 64 - __clzll((unsigned long long)seg) : 0) +
-                          (rb.dd > 0 ? 64 - __clzll((unsigned long long)rb.dd) : 0);
+        const int depth = search_steps(fenced ? stride : rb.db) + search_steps(rb.dd);
         if (l == 0) {
             walked += (j1 - j0) + nf;
-            probes += (j1 - j0) * depth;
+            probes += (j1 - j0) * depth + (piece == 0 ? 8 : 0);
         }
         const int32_t *row = col + rb.ob, *drow = dcol + rb.od;
         int whole = 1, dwhole = 1;  // powers of two that cover the rows
@@ -348,10 +353,17 @@ __global__ __launch_bounds__(256) void k_tc_delta(int64_t ne, const int32_t *eu,
     tc_block_part(acc, walked, probes, part);
 }
 
-// Sum of the per-block partials (triangle weight, entries walked, search steps).
-__global__ __launch_bounds__(1024) void k_tc_sum(const int64_t *part, int64_t nblocks, int64_t *out) {
+// Sums of the per-block partials: block 0 those of nblocks blocks of k_tc_delta, block 1
+// those of the niblocks blocks of k_tc_items that follow them.
+__global__ __launch_bounds__(1024) void k_tc_sum(const int64_t *part, int64_t nblocks, int64_t niblocks, int64_t *out,
+                                                 int64_t *iout) {
     __shared__ int64_t s[3][1024 / WAVE];
     int64_t a0 = 0, a1 = 0, a2 = 0;
+    if (blockIdx.x == 1) {
+        part += 3 * nblocks;
+        nblocks = niblocks;
+        out = iout;
+    }
     for (int64_t b = threadIdx.x; b < nblocks; b += blockDim.x) {
         a0 += part[3 * b];
         a1 += part[3 * b + 1];
@@ -387,25 +399,29 @@ int tc_delta(dg_graph *g, const int32_t *eu, const int32_t *ev, int64_t ne, uint
     DG_TRY(g->ws.bpart.ensure(3 * (size_t)(blocks + iblocks) + 8));
     DG_TRY(g->ws.tcitems.ensure(2 * ((size_t)ne + 1)));
     int64_t *cnt = g->ws.tcitems.p, *start = g->ws.tcitems.p + ne + 1;
+    const int pi = prof_begin("tc_items", s);
     hipLaunchKernelGGL(k_tc_items, dim3((unsigned)iblocks), dim3(256), 0, s, ne, eu, ev, F.off.p, F.col.p, F.doff.p,
                        F.dcol.p, cnt, g->ws.bpart.p + 3 * blocks);
+    prof_end(pi, s, 0.0);
     DG_HIP(hipGetLastError());
     DG_TRY(scan_excl(g, cnt, start, ne + 1));
-    int ps = prof_begin("tc_delta", s);
+    const int ps = prof_begin("tc_delta", s);
     hipLaunchKernelGGL(k_tc_delta, dim3((unsigned)blocks), dim3(256), 0, s, ne, eu, ev, start, F.off.p, F.col.p,
                        F.doff.p, F.dcol.p, g->ws.bpart.p);
     prof_end(ps, s, 0.0);
-    // counters C_AUX1, C_AUX2, C_AUX3 = 6 x changed triangles, entries walked, search steps
-    static_assert(C_AUX2 == C_AUX1 + 1 && C_AUX3 == C_AUX1 + 2, "three consecutive counters");
-    hipLaunchKernelGGL(k_tc_sum, dim3(1), dim3(1024), 0, s, g->ws.bpart.p, blocks + iblocks, g->ws.dcnt + C_AUX1);
+    static_assert(C_AUX2 == C_AUX1 + 1 && C_AUX3 == C_AUX1 + 2 && C_RED0 + 3 <= C_EDGES, "three consecutive counters");
+    hipLaunchKernelGGL(k_tc_sum, dim3(2), dim3(1024), 0, s, g->ws.bpart.p, blocks, iblocks, g->ws.dcnt + C_AUX1,
+                       g->ws.dcnt + C_RED0);
     DG_HIP(hipGetLastError());
     DG_TRY(counters_read(g));
-    *sum6 = (uint64_t)g->ws.hcnt[C_AUX1];
-    if (entries) *entries = g->ws.hcnt[C_AUX2];  // shorter-row entries intersected
-    // per changed edge its endpoints' offsets (32 B); per entry of the shorter row
-    // and per fence of a long row 4 B; per global search step into the longer row
-    // (the whole row, or the segment a fence search selects) 4 B
-    prof_add(ps, 32.0 * (double)ne + 4.0 * (double)g->ws.hcnt[C_AUX2] + 4.0 * (double)g->ws.hcnt[C_AUX3]);
+    const int64_t *delta = g->ws.hcnt + C_AUX1, *items = g->ws.hcnt + C_RED0;
+    *sum6 = (uint64_t)(delta[0] + items[0]);
+    if (entries) *entries = delta[1] + items[1];  // shorter-row entries intersected
+    // of each launch: per changed edge that it looks at its endpoints' offsets (32 B); per
+    // entry of the shorter row and per fence of a long row 4 B; per global search step into
+    // the longer row (the whole row, or the segment a fence search selects) 4 B
+    prof_add(pi, 4.0 * (double)(items[1] + items[2]));
+    prof_add(ps, 4.0 * (double)(delta[1] + delta[2]));
     return DG_OK;
 }
 
