@@ -178,6 +178,7 @@ static int snap_dir(dg_snapshot *sn, const Dir &d, int32_t n, hipStream_t s) {
     sn->scalars.push_back(d.dm);
     sn->scalars.push_back(d.tomb_base);
     sn->scalars.push_back(d.tomb_diff);
+    sn->scalars.push_back(d.hot);
     return DG_OK;
 }
 
@@ -195,6 +196,7 @@ static int load_dir(const dg_snapshot *sn, size_t &idx, size_t &si, Dir &d, hipS
     d.dm = sn->scalars[si++];
     d.tomb_base = sn->scalars[si++];
     d.tomb_diff = sn->scalars[si++];
+    d.hot = sn->scalars[si++];
     return DG_OK;
 }
 

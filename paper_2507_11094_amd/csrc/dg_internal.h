@@ -28,6 +28,7 @@ constexpr uint32_t MARK = 0x40000000u;
 constexpr uint32_t DEAD = 0x80000000u;
 constexpr int32_t INF = DG_INF;
 constexpr int TILE = 256;   // base entries per tombstone counter block (ttomb)
+constexpr int HOT_TIMES = 8;
 
 // ---- errors ------------------------------------------------------------------------
 int set_error(int code, const char *fmt, ...);
@@ -105,6 +106,7 @@ struct Dir {
     DBuf<int32_t> ttomb;      // [ceil(m/TILE)] base tombstones per merge tile
     int64_t tomb_base = 0;    // host mirrors
     int64_t tomb_diff = 0;
+    int64_t hot = 0;          // base arcs of rows HOT_TIMES the mean length or longer (as built or merged)
     // spares used by merges and diff rebuilds
     DBuf<int64_t> off2;
     DBuf<int32_t> col2, w2;
@@ -201,7 +203,7 @@ struct GraphCache {
 enum Counter {
     C_ERR = 0, C_NDEL, C_NINS, C_ADEL, C_IGNDEL, C_DISTINCT, C_AINS, C_IGNINS, C_NEW,
     C_TCDEL, C_TCINS, C_F0, C_F1, C_HEAVY, C_AUX0, C_AUX1, C_AUX2, C_AUX3,
-    C_TC0, C_TC1, C_RED0 = 24,
+    C_TC0, C_TC1, C_HOT, C_RED0 = 24,
     C_EDGES = 30,  // adjacency entries examined by an SSSP step (base + diff, tombstones included)
     // an upper bound on the longest row (base + diff entries, tombstones included) of
     // either direction: set at build, raised by the rows that gain diff entries, never

@@ -319,17 +319,24 @@ __global__ void k_row_offsets_swapped(int32_t n, const uint64_t *k, int64_t m, i
     }
 }
 
-// Row lengths, and their maximum raised into *maxrow.
-__global__ __launch_bounds__(WIDE_T) void k_degrees(int32_t n, const int64_t *off, int32_t *deg, int64_t *maxrow) {
+// Row lengths, their maximum raised into *maxrow, and the arcs of rows of at least `limit`
+// added to *hot.
+__global__ __launch_bounds__(WIDE_T) void k_degrees(int32_t n, const int64_t *off, int32_t *deg, int64_t *maxrow,
+                                                    int64_t limit, int64_t *hot) {
     __shared__ BlockScratch sc;
-    int64_t mx = 0;
+    int64_t mx = 0, sum = 0;
     for (int64_t r = gtid(); r < n; r += gstride()) {
         const int64_t len = off[r + 1] - off[r];
         deg[r] = (int32_t)len;
         mx = max(mx, len);
+        sum += len >= limit ? len : 0;
     }
     block_raise<WIDE_T>(maxrow, mx, sc);
+    block_count<WIDE_T>(hot, sum, sc);
 }
+
+// The length from which a row of a graph of n rows and m arcs counts as hot.
+static int64_t hot_limit(int64_t n, int64_t m) { return std::max<int64_t>(1, (HOT_TIMES * m + n - 1) / n); }
 
 // The rows that gained the diff keys k[0, nk): their total lengths (base entries,
 // tombstones included, plus diff entries) raised into *maxrow.
@@ -367,7 +374,7 @@ static int dir_from_sorted(dg_graph *g, Dir &d, const uint64_t *keys, const int3
     hipLaunchKernelGGL(swapped ? k_row_offsets_swapped : k_row_offsets, dim3(grid_for(g->n + 1)), dim3(256), 0, s,
                        g->n, keys, m, B, d.off.p);
     hipLaunchKernelGGL(k_degrees, dim3(grid_wide(g->n)), dim3(WIDE_T), 0, s, g->n, d.off.p, d.deg.p,
-                       g->ws.dcnt + C_MAXROW);
+                       g->ws.dcnt + C_MAXROW, hot_limit(g->n, m), g->ws.dcnt + (swapped ? C_AUX0 : C_HOT));
     DG_HIP(hipGetLastError());
     DG_TRY(fill_i32(d.ttomb.p, 0, ntiles_for(m) + 2, s));
     DG_TRY(fill_i64(d.doff.p, 0, g->n + 1, s));
@@ -536,6 +543,7 @@ int graph_build(dg_graph *g, int64_t m, const int32_t *src, const int32_t *dst, 
     g->rev = g->undirected ? &g->fwd : &g->rev_own;
     g->m_live = arcs;
     DG_TRY(counters_read(g));  // also brings the longest-row bound to the host
+    g->fwd.hot = ws.hcnt[C_HOT];
     // the build-sized scratch is not needed again
     IdleFrees idle;
     ws.ikey.release(); ws.ikey_s.release(); ws.iw.release(); ws.iw_s.release(); ws.sw.release();
@@ -546,6 +554,18 @@ int graph_build(dg_graph *g, int64_t m, const int32_t *src, const int32_t *dst, 
 
 __global__ void k_deg_to_i64(int32_t n, const int32_t *deg, int64_t *out) {
     for (int64_t i = gtid(); i <= n; i += gstride()) out[i] = i < n ? deg[i] : 0;
+}
+// The same of a direction's degrees, with the hot rows' arcs (k_degrees).
+__global__ __launch_bounds__(WIDE_T) void k_live_degrees(int32_t n, const int32_t *deg, int64_t *out, int64_t limit,
+                                                         int64_t *hot) {
+    __shared__ BlockScratch sc;
+    int64_t sum = 0;
+    for (int64_t i = gtid(); i <= n; i += gstride()) {
+        const int64_t d = i < n ? deg[i] : 0;
+        out[i] = d;
+        sum += d >= limit ? d : 0;
+    }
+    block_count<WIDE_T>(hot, sum, sc);
 }
 
 // Merge of one direction on merge-path tiles: the row ends and the base entries
@@ -808,7 +828,9 @@ static int merge_into(dg_graph *g, Dir &d, int64_t *off2, int32_t *col2, int32_t
     int64_t *tsin = tmpa + (n + 1);
     int64_t *TB = tsin + (nblk + 2);
     // off2 = exclusive scan of live degrees
-    hipLaunchKernelGGL(k_deg_to_i64, dim3(grid_for(n + 1)), dim3(256), 0, s, n, d.deg.p, tmpa);
+    if (!side) DG_TRY(fill_i64(cnt, 0, C_MAXROW, s));  // the longest-row bound stays (rows only shrink here)
+    hipLaunchKernelGGL(k_live_degrees, dim3(grid_wide(n + 1)), dim3(WIDE_T), 0, s, n, d.deg.p, tmpa, hot_limit(n, m2),
+                       cnt + (&d == &g->fwd ? C_HOT : C_AUX0));
     DG_TRY(scan_excl_on(s, sw, cnt + C_SORT_ERR, tmpa, off2, n + 1));
     // TB = tombstones before each counter block
     hipLaunchKernelGGL(k_deg_to_i64, dim3(grid_for(nblk + 2)), dim3(256), 0, s, (int32_t)(nblk + 1), d.ttomb.p,
@@ -825,7 +847,6 @@ static int merge_into(dg_graph *g, Dir &d, int64_t *off2, int32_t *col2, int32_t
     hipLaunchKernelGGL(k_mg_partition, dim3(grid_for(nb + 1)), dim3(256), 0, s, d.off.p, d.doff.p, n, d.m, nb,
                        items, ws.mp_row.p, ws.mp_edge.p, mp_dlo, mp_dhi);
     DG_HIP(hipGetLastError());
-    DG_TRY(fill_i64(cnt, 0, C_MAXROW, s));  // the longest-row bound stays (rows only shrink here)
     // merge bytes: col+w read 8 per old entry, write 8 per new entry, and per row
     // off and doff (8 each)
     int pm = prof_begin("merge_base", s);
@@ -883,6 +904,7 @@ static int merge_dir_start(dg_graph *g, Dir &d, int64_t live, bool side) {
 static int merge_dir(dg_graph *g, Dir &d, int64_t live) {
     if (!merge_needed(d)) return DG_OK;
     DG_TRY(merge_dir_start(g, d, live, false));
+    if (&d == &g->fwd) d.hot = g->ws.hcnt[C_HOT];
     return merge_dir_commit(g, d, live);
 }
 
@@ -2061,6 +2083,7 @@ int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, 
                 DG_HIP(hipEventRecord(g->ev_fork, s));
                 DG_HIP(hipStreamWaitEvent(g->aux, g->ev_fork, 0));
                 const size_t m0 = plog.mark(g->aux);
+                DG_TRY(fill_i64(ws.dcnt_m, 0, C_MAXROW, g->aux));
                 if (merge_f) DG_TRY(merge_dir_start(g, F, g->m_live, true));
                 if (merge_r) DG_TRY(merge_dir_start(g, g->rev_own, g->m_live, true));
                 plog.spans.push_back({m0, plog.mark(g->aux), &st->t_merge_ms});
@@ -2140,6 +2163,7 @@ int apply_chunk(dg_graph *g, int64_t k, const int32_t *src, const int32_t *dst, 
     // ---- a merge beside the SSSP updates: check it, then swap in the merged arrays
     if (merge_pending) {
         DG_TRY(merge_side_check(g));
+        if (merge_f) F.hot = ws.hcnt_m[C_HOT];
         if (merge_f) DG_TRY(merge_dir_commit(g, F, g->m_live));
         if (merge_r) DG_TRY(merge_dir_commit(g, g->rev_own, g->m_live));
     }

@@ -672,15 +672,29 @@ __global__ void k_mp_partition(const int64_t *__restrict__ off, int32_t n, int64
 // non-temporal hints, so that they do not displace the gathered contributions
 // from L2.
 // The tile's LDS, and how many workgroups share a CU (by the LDS the launch asks for).
-// Where rows are short the time goes into the streams of offsets and values, and eight
-// workgroups hide it best: 4096^2 grid, 4 arcs a vertex, 146 us a launch against 166
-// with six.  Where the gathers at scattered columns bound the kernel, more workgroups
-// only compete for the L1 that holds the most used shares: R-MAT 22, 16 arcs a vertex,
-// 363 us with eight, 354 with six, 345 with five or four.
+// Where the gathers find their shares near by (grids and meshes of any density) more
+// workgroups hide the streams of offsets and values better; where they are scattered over
+// all shares it matters little; where a few hot shares take many of them, more workgroups
+// only compete for the L1 that holds those.  us a launch of 2,048-item tiles with eight,
+// six and five workgroups: 4096^2 grid of 4 neighbours 140, 162 and 179, of 8 neighbours
+// 219, 263 and 291, of 12 neighbours 279, 338 and 376; 4M vertices with 16 uniform arcs each
+// 1071, 1067 and 1066; R-MAT 22 with 16 arcs a vertex 364, 355 and 346, with 8 arcs 199, 195 and
+// 193, with 4 arcs 113, 111 and 111, with 3 arcs 91, 90 and 90 (R-MAT 20: 3 arcs 27, 28 and 28,
+// 4 arcs 33, 32 and 32).  So five are taken from TILE_DENSE arcs a vertex on, if rows of
+// HOT_TIMES the mean length hold at least 1 / TILE_HOT of the arcs (R-MAT 0.6 and more,
+// where a grid of 8 neighbours with hubs of 0.23 in all takes 80, 85 and 92 us, with hubs
+// of 0.49 168, 158 and 162).  Tiles of 1,024 items gain nothing from it (R-MAT 22 353 with eight,
+// 366 with five; the 8-neighbour grid 272 and 425).  Tiles of 4,096 leave room for four;
+// three are better only on shares that the L2s cannot hold, from 12 arcs a vertex on
+// (R-MAT 22 353 and 348, R-MAT 23 772 and 765, R-MAT 22 with 8 arcs 195 and 201, R-MAT 21 162 and
+// 165).
 template <int ITEMS>
 constexpr int TILE_LDS = 8 * ITEMS + 8;
-constexpr int64_t TILE_DENSE = 8;         // arcs a vertex from which the gathers bound it
+constexpr int64_t TILE_DENSE = 4, TILE_HOT = 4;
 constexpr int TILE_LDS_DENSE = 30 << 10;  // five workgroups a CU
+constexpr int64_t TILE_DENSE_4096 = 12;
+constexpr int32_t TILE_N_4096 = 1 << 22;
+constexpr int TILE_LDS_4096 = 41 << 10;   // three
 
 template <bool STREAM, int ITEMS>
 __global__ __launch_bounds__(MP_THREADS) void k_pr_tiles(const int32_t *__restrict__ mp_row,
@@ -1043,7 +1057,10 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
     auto tiles_kernel = items == 1024 ? (nt ? k_pr_tiles<true, 1024> : k_pr_tiles<false, 1024>)
                       : items == 4096 ? (nt ? k_pr_tiles<true, 4096> : k_pr_tiles<false, 4096>)
                                       : (nt ? k_pr_tiles<true, 2048> : k_pr_tiles<false, 2048>);
-    const size_t tile_lds = std::max(8 * items + 8, R.m >= TILE_DENSE * (int64_t)g->n ? TILE_LDS_DENSE : 0);
+    const bool hot = g->fwd.hot >= R.m / TILE_HOT;
+    int tile_lds = 8 * items + 8;
+    if (hot && items == 2048 && R.m >= TILE_DENSE * (int64_t)g->n) tile_lds = TILE_LDS_DENSE;
+    if (hot && items == 4096 && R.m >= TILE_DENSE_4096 * g->n && g->n >= TILE_N_4096) tile_lds = TILE_LDS_4096;
     int64_t nb = 0;
     if (tiles) {
         nb = ((int64_t)g->n + R.m + items - 1) / items;
