@@ -1084,10 +1084,12 @@ static int pr_iterate(dg_graph *g, const int32_t *A, int64_t na, int64_t edges, 
     constexpr int GROUP = 4;
     constexpr int SIDE_GROUP = 6;  // steps queued before the SSSP work starts beside them
     constexpr int AHEAD = 5;       // steps kept in flight while the host drives the SSSP rounds
-    // On small graphs the rounds end later than the steps, so they start after one step
-    // (16k vertices, both queries: 1,600 us per two batches with SIDE_GROUP first and
-    // AHEAD at every wait, 1,280 with one first and one a wait).
-    constexpr int32_t PUMP_N = 1 << 15;
+    // On small graphs the rounds end later than the steps, so they start after one step.
+    // us of two batches with SIDE_GROUP steps first and with one: R-MAT of 2^13 vertices 1218
+    // and 1057, 2^14 1290 and 1166, 2^16 1559 and 1442, 2^18 2023 and 1960, 2^20 4207 and 4202;
+    // 4 uniform arcs a vertex 2^13 1551 and 1608, 2^14 1572 and 1562, 2^16 1760 and 1705, 2^18
+    // 2407 and 2215, 2^20 4144 and 4139; grids of 2^12 to 2^16 vertices within 2.5 %.
+    constexpr int32_t PUMP_N = 1 << 18;
     constexpr int RING = (int)(sizeof(ws.step_ev) / sizeof(ws.step_ev[0]));
     static_assert(RING > AHEAD, "the ring must hold the events of every step in flight");
     int32_t it = 0, launched = 0;
