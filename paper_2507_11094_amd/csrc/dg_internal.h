@@ -201,9 +201,8 @@ struct GraphCache {
 };
 
 enum Counter {
-    C_ERR = 0, C_NDEL, C_NINS, C_ADEL, C_IGNDEL, C_DISTINCT, C_AINS, C_IGNINS, C_NEW,
-    C_TCDEL, C_TCINS, C_F0, C_F1, C_HEAVY, C_AUX0, C_AUX1, C_AUX2, C_AUX3,
-    C_TC0, C_TC1, C_HOT, C_RED0 = 24,
+    C_ERR = 0, C_NDEL, C_NINS, C_ADEL, C_AINS = 6, C_NEW = 8, C_TCDEL, C_TCINS,
+    C_F0, C_F1, C_HEAVY, C_AUX0, C_AUX1, C_AUX2, C_AUX3, C_TC0, C_TC1, C_HOT, C_RED0 = 24,
     C_EDGES = 30,  // adjacency entries examined by an SSSP step (base + diff, tombstones included)
     // an upper bound on the longest row (base + diff entries, tombstones included) of
     // either direction: set at build, raised by the rows that gain diff entries, never

@@ -1142,7 +1142,7 @@ __device__ __forceinline__ void classify_inserts_body(int64_t ni, const uint64_t
                                                       int64_t *cnt) {
     __shared__ BlockScratch sc;
     const uint64_t mask = (1ull << B) - 1;
-    int64_t nnew = 0, nign = 0, ndist = 0;
+    int64_t nnew = 0;
     for (int64_t c0 = (int64_t)blockIdx.x * WIDE_T; c0 < ni; c0 += gstride()) {
         const int64_t i = c0 + threadIdx.x;
         int64_t pos = -1;
@@ -1160,11 +1160,9 @@ __device__ __forceinline__ void classify_inserts_body(int64_t ni, const uint64_t
                 pos = find_arc(off, col, doff, dcol, u, v);
                 if (pos == -1) act = 1;
                 else act = (uint32_t)(pos >= 0 ? col[pos] : dcol[-2 - pos]) & (DEAD | MARK) ? 2 : 3;
-                ++ndist;
             }
             isnew[i] = act == 1;
             nnew += act == 1;
-            nign += act != 1 && act != 2;
         }
         const bool applied = act == 1 || act == 2;
         const int64_t slot = block_append<WIDE_T>(&cnt[C_AINS], applied, sc);
@@ -1176,8 +1174,6 @@ __device__ __forceinline__ void classify_inserts_body(int64_t ni, const uint64_t
         }
     }
     block_count<WIDE_T>(&cnt[C_NEW], nnew, sc);
-    block_count<WIDE_T>(&cnt[C_IGNINS], nign, sc);
-    block_count<WIDE_T>(&cnt[C_DISTINCT], ndist, sc);
 }
 __global__ __launch_bounds__(WIDE_T) void k_classify_inserts(int64_t ni, const uint64_t *key, int32_t *iw, int B,
     const int64_t *__restrict__ off, const int32_t *__restrict__ col, const int64_t *__restrict__ doff,
