@@ -842,8 +842,8 @@ __global__ void k_pr_rows(int64_t nb, int items, const int32_t *__restrict__ mp_
 // one workgroup finishes the rows, applies the step and decides the next one.  At this
 // size each of the three launches does little and costs about 4 us.  One workgroup
 // moves about 60 GB/s, so it loses where its time passes that of the three launches:
-// ranks of a batch, in us with this kernel and with the three, 1k vertices 285 and
-// 318, 4k 240 and 282, 8k 274 and 253, 16k 333 and 264, 32k 455 and 291.  The same holds for
+// ranks of a batch, in us with this kernel and with the three, 1k vertices 279 and
+// 318, 4k 245 and 282, 8k 274 and 253, 16k 333 and 264, 32k 455 and 291.  The same holds for
 // many tiles and diff-level entries, of which it takes a chain of reads per FIN_T.
 constexpr int FIN_T = 1024;
 constexpr int32_t FIN_N = 1 << 12;
@@ -861,7 +861,7 @@ __global__ __launch_bounds__(FIN_T) void k_pr_finish_small(
     __syncthreads();
     // as k_pr_apply
     double acc = 0.0, dang = 0.0, sq = 0.0, dot = 0.0, dot2 = 0.0;
-    constexpr int U = 8;
+    constexpr int U = FIN_N / FIN_T;  // every element in flight
     for (int i0 = threadIdx.x; i0 < n; i0 += U * FIN_T) {
         int32_t dg[U];
         double nv[U], ov[U], pv[U], pv2[U];
