@@ -79,8 +79,11 @@ __global__ void k_set_unpack(int64_t nl, const uint64_t *key, int64_t base, int3
 }
 
 // The same by one workgroup, which tells the host itself when its stores are done: a
-// read of one member is short (at most 16k vertices in one pass of 16 loads per
-// thread), and a set is read member by member, so the wait is what it costs.
+// read of one member is short and a set is read member by member, so the wait is what it
+// costs.  Up to UNPACK_ONE vertices, two passes of eight loads per thread: us a read (with
+// parents) by one workgroup and by many with a stream synchronisation, 1k vertices 8.7 (8.9)
+// and 12.4, 8k 9.3 (9.7) and 12.7, 16k 10.5 (11.4) and 12.7 (12.8), 32k 13.0 (14.9) and 12.7
+// (12.8), 64k 18.4 (22.0) and 12.7 (12.8).
 constexpr int UNPACK_T = 1024, UNPACK_U = 8;
 constexpr int64_t UNPACK_ONE = 2 * UNPACK_T * UNPACK_U;
 __global__ __launch_bounds__(UNPACK_T) void k_set_unpack_one(int64_t nl, const uint64_t *key, int64_t base,

@@ -72,10 +72,11 @@ struct SinkTarget {
     int64_t *count2 = nullptr;
 };
 
-// Threads per block of the expansion kernels.  They run beside the PageRank tiles,
-// which leave 13 KB of LDS, 8 waves and 128 registers a lane on a CU: a block of four
-// waves with 4 KB fits there, one of eight waves with 26 KB waited for whole tiles to
-// end (cut walk on R-MAT 22: 68 -> 172 us a level).
+// Threads per block of the expansion kernels.  They run beside the PageRank tiles: where
+// five workgroups of these share a CU (hot rows), they leave 10 KB of LDS and 12 waves, and
+// a block of four waves with 4 KB fits; where eight do, they hold every wave slot, and a
+// block takes the place of a tile that ends.  A block of eight waves with 26 KB waited for
+// several tiles to end (cut walk on R-MAT 22, beside six: 68 -> 172 us a level).
 constexpr int EX_T = 256;
 constexpr int EX_W = EX_T / WAVE;
 constexpr int EX_U = 4;             // slots per lane in flight
