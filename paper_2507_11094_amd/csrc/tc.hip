@@ -123,14 +123,11 @@ __device__ __forceinline__ void find_step(const int32_t *__restrict__ row, uint3
 template <int U>
 __device__ __forceinline__ bool find_fenced(const uint32_t *f, int nf, int stride, const uint32_t (&xs)[U],
                                             uint32_t (&s)[U], uint32_t (&e)[U]) {
-    const auto first = [](const uint32_t (&f)[1], uint32_t x) {
-        if (x < f[0]) return -1;
-        return 0;
-    };
-    const uint32_t head[1] = {f[0] & ID_MASK};  // the row's first id
+    // one search would begin with: if (x < f[0]) return -1;  a wave leaves if every lane would
+    const uint32_t head = f[0] & ID_MASK;
     bool some = false;
 #pragma unroll
-    for (int u = 0; u < U; ++u) some |= first(head, xs[u]) == 0;
+    for (int u = 0; u < U; ++u) some |= xs[u] >= head;
     if (ballot(some) == 0) return false;
     int top = 1;
     while (top < nf) top <<= 1;
