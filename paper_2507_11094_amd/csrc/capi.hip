@@ -53,7 +53,7 @@ int64_t *g_blocks[BLOCKS_MAX];  // counter blocks given up (pinned host memory, 
 int g_nblocks = 0;
 }  // namespace
 
-IdleFrees::IdleFrees() : before(t_idle_frees) { t_idle_frees = true; }
+IdleFrees::IdleFrees(bool ended) : before(t_idle_frees) { t_idle_frees = ended; }
 IdleFrees::~IdleFrees() { t_idle_frees = before; }
 
 void *dmalloc(size_t bytes) {
@@ -286,8 +286,7 @@ int dg_graph_destroy(dg_graph *g) {
     // the graph's work ends before its memory may serve another graph
     const bool ended = hipStreamSynchronize(g->stream) == hipSuccess &&
                        (!g->aux || hipStreamSynchronize(g->aux) == hipSuccess) && !g->broken;
-    IdleFrees idle;
-    if (!ended) t_idle_frees = false;
+    IdleFrees idle(ended);
     for (dg_query *q : g->queries) {
         query_free(q);
     }
@@ -477,8 +476,7 @@ int dg_query_detach(dg_query *q) {
     if (it == g->queries.end()) return set_error(DG_EINVAL, "query not attached");
     g->queries.erase(it);
     const bool ended = hipStreamSynchronize(g->stream) == hipSuccess && !g->broken;
-    IdleFrees idle;
-    if (!ended) t_idle_frees = false;
+    IdleFrees idle(ended);
     query_free(q);
     return DG_OK;
 }

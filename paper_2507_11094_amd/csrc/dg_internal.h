@@ -49,9 +49,10 @@ int set_error(int code, const char *fmt, ...);
 void *dmalloc(size_t bytes);
 void dfree(void *p);
 // While one is in scope, the calling thread's dfree calls may keep the memory for a
-// later dmalloc: nothing queued on any stream uses what it frees.
+// later dmalloc: nothing queued on any stream uses what it frees (if ended; else they
+// do not keep it).
 struct IdleFrees {
-    IdleFrees();
+    explicit IdleFrees(bool ended = true);
     ~IdleFrees();
     bool before;
 };

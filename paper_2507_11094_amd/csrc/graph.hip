@@ -952,7 +952,10 @@ int graph_export(dg_graph *g, int64_t *m, int32_t *src, int32_t *dst, int32_t *w
         }
     }
     hipError_t e = hipStreamSynchronize(s);
-    off2.release(); col2.release(); w2.release(); row.release();
+    {
+        IdleFrees idle(e == hipSuccess);
+        off2.release(); col2.release(); w2.release(); row.release();
+    }
     if (rc != DG_OK) return rc;
     if (e != hipSuccess) return set_error(DG_EDEVICE, "export copy failed: %s", hipGetErrorString(e));
     if (!g->relabeled) {

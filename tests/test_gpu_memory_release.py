@@ -32,3 +32,21 @@ def test_release_beside_an_open_graph():
     s, d, w, _ = oracle.apply(n, s, d, w, *b)
     assert np.array_equal(q.read()[0], oracle.sssp(n, s, d, w, 0))
     G.close()
+
+
+def test_export_scratch_is_kept_for_the_next_export():
+    import torch
+
+    gc.collect()
+    n, s, d, w = graphgen.rmat_directed(18, 16 << 18, graphgen.config_seed(0, 4))
+    G = dg.Graph(n, s, d, w)
+    dg.release_memory()
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    first = G.export()
+    assert before - torch.cuda.mem_get_info()[0] >= 3 * 4 * s.size  # rows, columns and weights
+    second = G.export()
+    assert all(np.array_equal(a, b) for a, b in zip(first, second))
+    dg.release_memory()
+    assert before - torch.cuda.mem_get_info()[0] < 4 * s.size
+    G.close()
