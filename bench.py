@@ -59,17 +59,17 @@ CSRC = os.path.join(ROOT, "paper_2507_11094_amd", "csrc")
 # figure stale and it is reported as null.
 MEASURED_TRAFFIC: dict = {
     ("k_pr_tiles", "rmat22-dynamic-sssp+pagerank"): {
-        "source": "pagerank.hip", "sha1": "0574e0f730155f07581ee12981ec958cc4f34672", "vertex_order": 0,
-        "fetch_kib": 585895.5, "write_kib": 33195.3, "fetch_factor": 0.5, "write_factor": 1.0},
+        "source": "pagerank.hip", "sha1": "814b19263243241e9e870079c4d29f5b31e6b7db", "vertex_order": 0,
+        "fetch_kib": 598212.3, "write_kib": 34053.9, "fetch_factor": 0.5, "write_factor": 1.0},
     ("k_pr_tiles", "grid4096x4096-dynamic-sssp+pagerank"): {
-        "source": "pagerank.hip", "sha1": "0574e0f730155f07581ee12981ec958cc4f34672", "vertex_order": 0,
-        "fetch_kib": 396397.8, "write_kib": 131599.9, "fetch_factor": 0.5, "write_factor": 1.0},
+        "source": "pagerank.hip", "sha1": "814b19263243241e9e870079c4d29f5b31e6b7db", "vertex_order": 0,
+        "fetch_kib": 386007.5, "write_kib": 127726.5, "fetch_factor": 0.5, "write_factor": 1.0},
     ("k_merge_tiles", "batched4096-rmat10to14-dynamic-sssp"): {
         "source": "graph.hip", "sha1": "42eb1ae1802d55bcf79c17e2dad7845aa22a545e",
         "fetch_kib": 2160799.4, "write_kib": 3510049.5, "fetch_factor": 0.5, "write_factor": 1.0},
     ("k_tc_delta", "rmat20-undirected-dynamic-tc"): {
-        "source": "tc.hip", "sha1": "b5076bb4a16ebdc8ac0ef337fe1ae942a48ca96a", "vertex_order": 0,
-        "fetch_kib": 408466.4, "write_kib": 768.0, "fetch_factor": 0.5, "write_factor": 1.0},
+        "source": "tc.hip", "sha1": "5da60b7a681ec8f9eb3e9e011854fee55ebe07dd", "vertex_order": 0,
+        "fetch_kib": 373548.7, "write_kib": 384.0, "fetch_factor": 0.5, "write_factor": 1.0},
 }
 
 # Serving objective stated up front: 99th percentile latency (submit -> result
